@@ -49,6 +49,7 @@ KERNEL_SOURCES = {
     "link_valu_kernel": "kernels_generic.hip",
     "link_small_kernel": "kernels_generic.hip",
     "link_lean_kernel": "kernels_generic.hip",
+    "link_stream_kernel": "kernels_stream.hip",
     "proj_kernel": "kernels_mla_proj.hip",
 }
 PROFILES = os.path.join(ROOT, "profiles")
@@ -434,9 +435,10 @@ def main(argv=None):
     tflops = flops / (step_ms * 1e-3) / 1e12
     gbs = nbytes / (step_ms * 1e-3) / 1e9
     if cfg.dtype == W.F32:
-        # fp32 products run on the matrix cores in the lean small-call kernel,
-        # on the vector ALUs in the generic ones
-        bound = "mfma" if kname.startswith("link_lean_kernel") else "alu"
+        # fp32 products run on the matrix cores in the lean and streaming
+        # kernels, on the vector ALUs in the generic ones
+        matrix = kname.startswith("link_lean_kernel") or "stream" in kname
+        bound = "mfma" if matrix else "alu"
         peak, unit, achieved = PEAK_FP32_TFLOPS, "TFLOP/s", flops / (kern_avg_ms * 1e-3) / 1e12
     elif flops / nbytes < PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
         # below the ridge point (about 312 FLOP/B): decode, and short questions

@@ -22,6 +22,7 @@ SOURCES = [
     "kernels_mfma_d128.hip",
     "kernels_decode_d128.hip",
     "kernels_mla.hip",
+    "kernels_stream.hip",
     "kernels_peaks.hip",
     "kernels_mla_proj.hip",
     "static_scratch.hip",

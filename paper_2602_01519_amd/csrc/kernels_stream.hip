@@ -1,0 +1,674 @@
+// GQA link attention on gfx950 matrix cores for fp32 caches and for bf16
+// caches with narrow heads (d_k = d_v = D): prefill- and decode-shaped calls.
+//
+// Every wave streams its own key range: 32-key tiles go from memory straight
+// into registers in the operand layout of the 16x16 matrix instructions, the
+// next tile's loads in flight under the current tile's arithmetic, with no
+// LDS staging and no barrier in the loop. Keys are walked as in the other
+// kernels: linked chunks in link order (Sec. 4.2: concatenated, no mask),
+// then the request's own KV (Sec. 4.1: causal, bottom-right aligned).
+//
+// A wave holds CB column blocks of 16 rows (a row is a query token and a
+// query head of the GQA group), so every K and V register feeds CB matrix
+// instructions. Per tile:
+//   S^T[32 keys][16 rows] = K Q^T        per column block
+//   softmax against a running max that only moves when a score passes it by
+//   2^64 (fp32 keeps its relative precision at any such magnitude)
+//   O^T[D][16 rows] += V^T P^T
+// The scores a lane receives are the keys its operand of the value product
+// needs, so probabilities never leave its registers:
+//   fp32 (v_mfma_f32_16x16x4_f32): A lane l = (row l % 16, k-slot l / 16);
+//     contraction step (j, i) takes head dims 16 j + 4 (l / 16) + i, so a
+//     lane's operands are whole 16-byte loads; score register i of key block
+//     b is key 16 b + 4 (l / 16) + i.
+//   bf16 (v_mfma_f32_16x16x32_bf16): key block b's M index m reads key row
+//     8 (m / 4) + 4 b + m % 4, so the registers of both blocks are keys
+//     8 (l / 16) + 0 .. 7.
+// The probabilities stay fp32. For bf16 caches the value product takes them
+// as the sum of two bf16 numbers (p = hi + lo, |p - hi - lo| <= 2^-17 p, far
+// below the rounding of the bf16 output), two matrix instructions per value
+// block; row sums add the fp32 probabilities.
+//
+// Work mapping: a workgroup's four waves are 4 / kpar row blocks times kpar
+// parts of one key range. Calls with many rows take kpar = 1: the four waves
+// walk the same tiles, which one of them brings into the CU's cache. Calls
+// with few rows split the keys over the waves too and merge the (m, l, O) of
+// the parts through LDS at the end. Workgroups that share keys (the row
+// blocks of one request, kv head and key split) run on one XCD, whose L2
+// then serves the repeated reads.
+//
+// What bounds it: fp32, the matrix cores (157 TFLOP/s; the exponentials are
+// a fiftieth of the matrix cycles); bf16 at D = 64, the vector ALU (about 36
+// cycles per score and lane for exponential, sum and the hi / lo split,
+// against 24 matrix cycles). Measured figures stand at launch_link_stream.
+#include "pic_internal.hpp"
+
+#include <cstddef>
+#include <type_traits>
+
+namespace pic {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kT = 32;            // keys per tile
+constexpr int kWaves = 4;
+constexpr float kJump = 64.0f;    // log2: the running max moves past it
+
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
+
+// Reductions over the 4 lane groups (l, l ^ 16, l ^ 32, l ^ 48) of a row.
+__device__ __forceinline__ float col_max(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float col_sum(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+template <typename T, int D>
+struct Shape {
+  static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr int E = 16 / (int)sizeof(T);          // elements per 16-byte unit
+  static constexpr int KU = D * (int)sizeof(T) / 64;     // 16-byte units per lane and key row
+  static constexpr int NB = D / 16;                      // value blocks
+  static constexpr int VU = F32 ? 2 : 1;                 // 16-byte units per lane and value block
+};
+
+// One tile's operands as loaded: K units [key block][unit], V^T units
+// [value block][unit].
+template <typename T, int D>
+struct Tile {
+  uint4 k[2][Shape<T, D>::KU];
+  uint4 v[Shape<T, D>::NB][Shape<T, D>::VU];
+};
+
+// Uniform facts of a tile.
+struct TileInfo {
+  const char *k;    // first K row of the tile, kv head applied (bytes)
+  const char *v;    // the tile's V^T panel, kv head applied
+  int nvalid;       // valid keys in the tile (0 or less: none)
+  int j0;           // key index of the tile's first key within its link
+  int tok;          // ... within the request's linked rows (document tiles)
+  int own;          // own-KV tile (causal mask)
+};
+
+// Link and request tables are read through the constant address space: the
+// cursor over the links lives in scalar registers.
+typedef __attribute__((address_space(4))) const LinkEntry *const_links;
+typedef __attribute__((address_space(4))) const ReqEntry *const_reqs;
+typedef __attribute__((address_space(4))) const int32_t *const_ints;
+
+struct Cursor {
+  const_links links;
+  int li;
+  const char *k, *v;
+  int len, lp, tile0, end, tok0;   // tile0, end: in 32-key tiles
+  int kvh, doc_tiles;              // doc_tiles: in 32-key tiles
+};
+
+__device__ __forceinline__ void cursor_load(Cursor &c) {
+  c.k = (const char *)c.links[c.li].k;
+  c.v = (const char *)c.links[c.li].v;
+  c.len = c.links[c.li].len;
+  c.lp = c.links[c.li].lp;
+  c.tile0 = c.links[c.li].tile0 * (kTile / kT);
+  c.tok0 = c.links[c.li].tok0;
+  c.end = c.tile0 + (c.len + kTile - 1) / kTile * (kTile / kT);
+}
+
+// Puts the cursor on the link that holds tile t: the lanes read the first
+// tiles of up to 64 links at once (one memory round trip, where a walk from
+// the first link takes one per link).
+__device__ __forceinline__ void cursor_seek(Cursor &c, int nlinks, int t, int lane) {
+  int li = 0;
+  for (int base = 0; base < nlinks; base += 64) {
+    const int i = base + lane;
+    const bool before = i < nlinks && c.links[min(i, nlinks - 1)].tile0 * (kTile / kT) <= t;
+    const int n = __popcll(__ballot(before));
+    if (n > 0) li = base + n - 1;
+    if (n < 64) break;
+  }
+  c.li = uni(li);
+  cursor_load(c);
+}
+
+// Tile t of the request (t only grows).
+template <typename T, int D>
+__device__ __forceinline__ TileInfo tile_info(Cursor &c, int t) {
+  while (t >= c.end) {
+    ++c.li;
+    cursor_load(c);
+  }
+  const int tt = t - c.tile0;
+  TileInfo r;
+  r.nvalid = min(kT, c.len - tt * kT);
+  r.j0 = tt * kT;
+  r.tok = c.tok0 + tt * kT;
+  r.own = t >= c.doc_tiles;
+  r.k = c.k + ((int64_t)c.kvh * c.lp + tt * kT) * (D * (int)sizeof(T));
+  r.v = c.v + ((int64_t)c.kvh * c.lp + tt * kT) * (D * (int)sizeof(T));   // a panel is kT x D too
+  return r;
+}
+
+// koff / voff: this lane's byte offsets within a tile's K rows and panel.
+template <typename T, int D>
+__device__ __forceinline__ void load_tile(const TileInfo &r, uint32_t koff, uint32_t voff,
+                                          Tile<T, D> &x) {
+  using S = Shape<T, D>;
+  constexpr int kRowBlock = (S::F32 ? 16 : 4) * D * (int)sizeof(T);   // key block 1 after block 0
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int j = 0; j < S::KU; ++j)
+      x.k[b][j] = *(const uint4 *)(r.k + koff + b * kRowBlock + j * 64);
+#pragma unroll
+  for (int b = 0; b < S::NB; ++b)
+#pragma unroll
+    for (int u = 0; u < S::VU; ++u)
+      x.v[b][u] = *(const uint4 *)(r.v + voff + b * 16 * kT * (int)sizeof(T) + u * 64);
+}
+
+// Own-KV tiles of a small call, read in place: keys j0 .. of the request's
+// token-major rows (k, v: its first own row, kv head applied; stride: bytes
+// per token). Keys past the last own one reread it; they are masked.
+struct OwnRows {
+  const char *k, *v;
+  int64_t stride;
+  int last;
+};
+template <typename T, int D>
+__device__ __forceinline__ void load_own(const OwnRows &o, int j0, int lr, int lg,
+                                         Tile<T, D> &x) {
+  using S = Shape<T, D>;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int key = S::F32 ? 16 * b + lr : 8 * (lr >> 2) + 4 * b + (lr & 3);
+    const char *row = o.k + min(j0 + key, o.last) * o.stride + 16 * lg;
+#pragma unroll
+    for (int j = 0; j < S::KU; ++j) x.k[b][j] = *(const uint4 *)(row + j * 64);
+  }
+#pragma unroll
+  for (int u = 0; u < S::VU; ++u) {
+    // the unit's keys: 16 u + 4 lg + 0..3 (fp32), 8 lg + 0..7 (bf16)
+    uint32_t w[S::NB][4];
+#pragma unroll
+    for (int b = 0; b < S::NB; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[b][i] = 0;
+#pragma unroll
+    for (int i = 0; i < S::E; ++i) {
+      const int key = S::F32 ? 16 * u + 4 * lg + i : 8 * lg + i;
+      const T *row = (const T *)(o.v + min(j0 + key, o.last) * o.stride) + lr;
+#pragma unroll
+      for (int b = 0; b < S::NB; ++b) {
+        if constexpr (S::F32)
+          w[b][i] = __float_as_uint(row[16 * b]);
+        else
+          w[b][i >> 1] |= (uint32_t)row[16 * b] << (16 * (i & 1));
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < S::NB; ++b) x.v[b][u] = make_uint4(w[b][0], w[b][1], w[b][2], w[b][3]);
+  }
+}
+
+__device__ __forceinline__ float unit(const uint4 &u, int i) {
+  return __uint_as_float(i == 0 ? u.x : i == 1 ? u.y : i == 2 ? u.z : u.w);
+}
+
+template <typename T, int D, int CB>
+struct State {
+  f32x4 o[CB][Shape<T, D>::NB];   // O^T: value dims 16 b + 4 (l / 16) + i, row l % 16
+  float m[CB], l[CB];             // running max (log2 domain), this lane's partial row sum
+};
+
+template <typename T, int D, int CB>
+__device__ __forceinline__ void compute_tile(const Tile<T, D> &x, const TileInfo &r,
+                                             const uint4 (&qf)[CB][Shape<T, D>::KU],
+                                             State<T, D, CB> &st, int lg, const int (&lim)[CB],
+                                             const int (&dl)[CB], int wmin, float sc) {
+  using S = Shape<T, D>;
+  f32x4 s[CB][2];
+#pragma unroll
+  for (int c = 0; c < CB; ++c)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) s[c][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < S::KU; ++j) {
+    if constexpr (S::F32) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int c = 0; c < CB; ++c)
+            s[c][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(unit(x.k[b][j], i), unit(qf[c][j], i),
+                                                           s[c][b], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int c = 0; c < CB; ++c)
+          s[c][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              as_bf16x8(x.k[b][j]), as_bf16x8(qf[c][j]), s[c][b], 0, 0, 0);
+    }
+  }
+  // key of score register i of block b, less the lane's own part of it
+  auto key = [](int b, int i) { return S::F32 ? 16 * b + i : 4 * b + i; };
+  const int kbase = (S::F32 ? 4 : 8) * lg;
+  if (r.own || r.nvalid < kT || r.tok + kT > wmin) {
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      const int kl = (r.own ? min(lim[c] - r.j0, r.nvalid - 1) : min(dl[c] - r.tok, r.nvalid) - 1) -
+                     kbase;
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (key(b, i) > kl) s[c][b][i] = -INFINITY;
+    }
+  }
+  // The running max moves only if some score of the wave passes it by
+  // 2^64 (or a row with a visible key has none yet).
+  float tmax[CB];
+  bool jump = false;
+#pragma unroll
+  for (int c = 0; c < CB; ++c) {
+    tmax[c] = fmaxf(fmaxf(fmaxf(s[c][0][0], s[c][0][1]), fmaxf(s[c][0][2], s[c][0][3])),
+                    fmaxf(fmaxf(s[c][1][0], s[c][1][1]), fmaxf(s[c][1][2], s[c][1][3])));
+    jump |= !(__builtin_fmaf(tmax[c], sc, -st.m[c]) <= kJump) && tmax[c] != -INFINITY;
+  }
+  if (__any(jump)) {
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      const float mnew = fmaxf(st.m[c], col_max(tmax[c]) * sc);
+      const float alpha = mnew == st.m[c] ? 1.f : __builtin_amdgcn_exp2f(st.m[c] - mnew);
+      st.m[c] = mnew;
+      st.l[c] *= alpha;
+#pragma unroll
+      for (int b = 0; b < S::NB; ++b) st.o[c][b] *= alpha;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < CB; ++c) {
+    const float neg_m = st.m[c] == -INFINITY ? 0.f : -st.m[c];
+    float p[2][4];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        p[b][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[c][b][i], sc, neg_m));
+    st.l[c] += ((p[0][0] + p[0][1]) + (p[0][2] + p[0][3])) +
+               ((p[1][0] + p[1][1]) + (p[1][2] + p[1][3]));
+    if constexpr (S::F32) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int b = 0; b < S::NB; ++b)
+            st.o[c][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(unit(x.v[b][u], i), p[u][i],
+                                                              st.o[c][b], 0, 0, 0);
+    } else {
+      bf16x8 hi, lo;
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const __bf16 h = (__bf16)p[b][i];
+          hi[4 * b + i] = h;
+          lo[4 * b + i] = (__bf16)(p[b][i] - (float)h);
+        }
+#pragma unroll
+      for (int b = 0; b < S::NB; ++b) {
+        st.o[c][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x.v[b][0]), hi, st.o[c][b],
+                                                             0, 0, 0);
+        st.o[c][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x.v[b][0]), lo, st.o[c][b],
+                                                             0, 0, 0);
+      }
+    }
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ void store4(T *out, float a, float b, float c, float d);
+template <>
+__device__ __forceinline__ void store4<float>(float *out, float a, float b, float c, float d) {
+  *(float4 *)out = make_float4(a, b, c, d);
+}
+template <>
+__device__ __forceinline__ void store4<uint16_t>(uint16_t *out, float a, float b, float c,
+                                                 float d) {
+  const __bf16 v[4] = {(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
+  *(uint2 *)out = __builtin_bit_cast(uint2, v);
+}
+
+// kSmall: a small call, whose tables are kernel arguments and whose own-KV
+// tiles are read in place (no prologue kernel before it).
+template <typename T, int D, int CB, bool kSmall>
+__device__ __forceinline__ void stream_body(const LinkParams &p, const_links links,
+                                            const_reqs reqs, const_ints order) {
+  using S = Shape<T, D>;
+  constexpr int kR = 16 * CB;              // rows per wave
+  constexpr int kOS = D + 4;               // merge buffer row stride (floats)
+  __shared__ __attribute__((aligned(16))) float so[kWaves][kR * kOS];
+  __shared__ float sm[kWaves][kR], sl[kWaves][kR];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = uni(threadIdx.x >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+
+  // XCD-aware mapping (consecutive workgroups go round-robin to the XCDs):
+  // the row blocks of one (request, kv head, key split) share an XCD.
+  const int xcd = blockIdx.x % p.n_xcd, j = blockIdx.x / p.n_xcd;
+  const int u = xcd + p.n_xcd * (j / p.nrb), rb = j % p.nrb;
+  const int n_grp = p.batch * p.n_kv_heads;
+  if (u >= n_grp * p.num_splits) return;
+  const int grp = u / p.num_splits, split = u % p.num_splits;
+  const int kvh = grp % p.n_kv_heads;
+  ReqEntry R;
+  {
+    const_reqs rq = reqs + order[grp / p.n_kv_heads];
+    R.link0 = rq->link0;
+    R.nlinks = rq->nlinks;
+    R.q0 = rq->q0;
+    R.lq = rq->lq;
+    R.s0 = rq->s0;
+    R.ls = rq->ls;
+    R.doc_tiles = rq->doc_tiles;
+    R.tiles = rq->tiles;
+  }
+  const int group = p.group, kpar = p.kpar;
+  const int nrows = R.lq * group;
+  const int wg_row0 = rb * (kWaves / kpar) * kR;
+  if (wg_row0 >= nrows) return;
+  const int row0 = wg_row0 + (wave / kpar) * kR;
+  const bool active = row0 < nrows;
+
+  // 32-key tiles up to the last own key the wave's last row sees, cut into
+  // num_splits x kpar parts
+  int t_begin = 0, t_end = 0;
+  if (active) {
+    const int own_last = min(nrows - 1, row0 + kR - 1) / group + R.ls - R.lq;
+    const int vis = own_last >= 0 ? min(2 * R.tiles, 2 * R.doc_tiles + own_last / kT + 1)
+                                  : 2 * R.doc_tiles;
+    const int part = split * kpar + wave % kpar, parts = p.num_splits * kpar;
+    t_begin = (int)((int64_t)vis * part / parts);
+    t_end = (int)((int64_t)vis * (part + 1) / parts);
+  }
+
+  int lim[CB], dl[CB], wmin = kNoLimit;
+  int64_t orow[CB];
+  bool rvalid[CB];
+#pragma unroll
+  for (int c = 0; c < CB; ++c) {
+    const int row = row0 + 16 * c + lr;
+    rvalid[c] = row < nrows;
+    const int qi = rvalid[c] ? row / group : 0;
+    const int qh = kvh * group + (rvalid[c] ? row % group : 0);
+    lim[c] = rvalid[c] ? qi + R.ls - R.lq : -1;
+    dl[c] = rvalid[c] && p.doc_lim ? p.doc_lim[R.q0 + qi] : kNoLimit;
+    orow[c] = (int64_t)(R.q0 + qi) * p.n_q_heads + qh;
+    wmin = min(wmin, dl[c]);
+  }
+  if (p.doc_lim) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) wmin = min(wmin, __shfl_xor(wmin, o));
+    wmin = uni(wmin);
+  } else {
+    wmin = kNoLimit;
+  }
+
+  Cursor cur;
+  cur.links = links + R.link0;
+  cur.kvh = kvh;
+  cur.doc_tiles = 2 * R.doc_tiles;
+  const uint32_t koff =
+      (uint32_t)((S::F32 ? lr : 8 * (lr >> 2) + (lr & 3)) * D * (int)sizeof(T) + 16 * lg);
+  const uint32_t voff = (uint32_t)(lr * kT * (int)sizeof(T) + 16 * lg);
+
+  OwnRows own{};
+  if (kSmall && R.ls > 0) {
+    const int64_t at = ((int64_t)R.s0 * p.n_kv_heads + kvh) * D * (int)sizeof(T);
+    own.k = (const char *)p.k_self + at;
+    own.v = (const char *)p.v_self + at;
+    own.stride = (int64_t)p.n_kv_heads * D * sizeof(T);
+    own.last = R.ls - 1;
+  }
+  Tile<T, D> ta, tb;
+  TileInfo ia{}, ib{};
+  auto load = [&](int t, TileInfo &i, Tile<T, D> &x) {
+    i = tile_info<T, D>(cur, t);
+    if (kSmall && i.own)
+      load_own<T, D>(own, i.j0, lr, lg, x);
+    else
+      load_tile<T, D>(i, koff, voff, x);
+  };
+  if (t_begin < t_end) {
+    cursor_seek(cur, R.nlinks, t_begin, lane);
+    load(t_begin, ia, ta);
+  }
+  uint4 qf[CB][S::KU];
+#pragma unroll
+  for (int c = 0; c < CB; ++c) {
+    const char *q = (const char *)p.q + orow[c] * (D * (int)sizeof(T)) + 16 * lg;
+#pragma unroll
+    for (int jj = 0; jj < S::KU; ++jj) {
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (rvalid[c]) v = *(const uint4 *)(q + 64 * jj);
+      qf[c][jj] = v;
+    }
+  }
+  State<T, D, CB> st;
+#pragma unroll
+  for (int c = 0; c < CB; ++c) {
+    st.m[c] = -INFINITY;
+    st.l[c] = 0.f;
+#pragma unroll
+    for (int b = 0; b < S::NB; ++b) st.o[c][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const float sc = p.scale_log2;
+
+  for (int t = t_begin; t < t_end; t += 2) {
+    if (t + 1 < t_end) load(t + 1, ib, tb);
+    compute_tile<T, D, CB>(ta, ia, qf, st, lg, lim, dl, wmin, sc);
+    if (t + 1 >= t_end) break;
+    if (t + 2 < t_end) load(t + 2, ia, ta);
+    compute_tile<T, D, CB>(tb, ib, qf, st, lg, lim, dl, wmin, sc);
+  }
+
+  const int64_t total_rows = (int64_t)p.total_q * p.n_q_heads;
+  float ltot[CB];
+#pragma unroll
+  for (int c = 0; c < CB; ++c) ltot[c] = col_sum(st.l[c]);
+  if (kpar == 1) {
+    // each lane holds 4 consecutive value dims of its rows
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      if (!rvalid[c]) continue;
+      if (p.num_splits == 1) {
+        const float inv = ltot[c] > 0.f ? 1.f / ltot[c] : 0.f;
+        T *out = (T *)p.out + orow[c] * D + 4 * lg;
+#pragma unroll
+        for (int b = 0; b < S::NB; ++b)
+          store4<T>(out + 16 * b, st.o[c][b][0] * inv, st.o[c][b][1] * inv, st.o[c][b][2] * inv,
+                    st.o[c][b][3] * inv);
+        if (p.lse && lg == 0)
+          p.lse[orow[c]] =
+              ltot[c] > 0.f ? (st.m[c] + log2f(ltot[c])) * 0.69314718055994531f : -INFINITY;
+      } else {
+        const int64_t prow = split * total_rows + orow[c];
+        float *po = p.part_o + prow * D + 4 * lg;
+#pragma unroll
+        for (int b = 0; b < S::NB; ++b)
+          store4<float>(po + 16 * b, st.o[c][b][0], st.o[c][b][1], st.o[c][b][2], st.o[c][b][3]);
+        if (lg == 0) {
+          p.part_m[prow] = ltot[c] > 0.f ? st.m[c] : -INFINITY;
+          p.part_l[prow] = ltot[c];
+        }
+      }
+    }
+    return;
+  }
+  // merge the kpar parts of every row block through LDS
+#pragma unroll
+  for (int c = 0; c < CB; ++c) {
+    float *o = &so[wave][(16 * c + lr) * kOS + 4 * lg];
+#pragma unroll
+    for (int b = 0; b < S::NB; ++b)
+      store4<float>(o + 16 * b, st.o[c][b][0], st.o[c][b][1], st.o[c][b][2], st.o[c][b][3]);
+    if (lg == 0) {
+      sm[wave][16 * c + lr] = ltot[c] > 0.f ? st.m[c] : -INFINITY;
+      sl[wave][16 * c + lr] = ltot[c];
+    }
+  }
+  __syncthreads();
+  constexpr int kQ = D / 4;                      // 4-wide units per row
+  const int rows = (kWaves / kpar) * kR;
+  for (int idx = threadIdx.x; idx < rows * kQ; idx += 64 * kWaves) {
+    const int rr = idx / kQ, e = idx % kQ * 4;
+    const int row = wg_row0 + rr;
+    if (row >= nrows) break;                     // later units are later rows
+    const int w0 = rr / kR * kpar, rl = rr % kR;
+    float M = -INFINITY;
+    for (int w = 0; w < kpar; ++w) M = fmaxf(M, sm[w0 + w][rl]);
+    float L = 0.f;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int w = 0; w < kpar; ++w) {
+      const float mw = sm[w0 + w][rl];
+      const float wt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
+      const float4 v = *(const float4 *)&so[w0 + w][rl * kOS + e];
+      L += wt * sl[w0 + w][rl];
+      a.x += wt * v.x;
+      a.y += wt * v.y;
+      a.z += wt * v.z;
+      a.w += wt * v.w;
+    }
+    const int64_t orw = (int64_t)(R.q0 + row / group) * p.n_q_heads + kvh * group + row % group;
+    if (p.num_splits == 1) {
+      const float inv = L > 0.f ? 1.f / L : 0.f;
+      store4<T>((T *)p.out + orw * D + e, a.x * inv, a.y * inv, a.z * inv, a.w * inv);
+      if (p.lse && e == 0)
+        p.lse[orw] = L > 0.f ? (M + log2f(L)) * 0.69314718055994531f : -INFINITY;
+    } else {
+      const int64_t prow = split * total_rows + orw;
+      store4<float>(p.part_o + prow * D + e, a.x, a.y, a.z, a.w);
+      if (e == 0) {
+        p.part_m[prow] = M;
+        p.part_l[prow] = L;
+      }
+    }
+  }
+}
+
+// Two waves per SIMD, one for the widest fp32 heads (two tiles in flight of
+// 64 registers each for K and V).
+template <typename T, int D>
+constexpr int kMinWaves = D * sizeof(T) > 256 ? 1 : 2;
+
+template <typename T, int D, int CB>
+__global__ __launch_bounds__(64 * kWaves, (kMinWaves<T, D>)) void link_stream_kernel(LinkParams p) {
+  stream_body<T, D, CB, false>(p, (const_links)p.links, (const_reqs)p.reqs, (const_ints)p.order);
+}
+
+// The tables are read where they are, in the kernel arguments.
+struct SmallArgs {
+  LinkParams p;
+  SmallTabs t;
+};
+template <typename T, int D, int CB>
+__global__ __launch_bounds__(64 * kWaves, (kMinWaves<T, D>)) void link_small_kernel(SmallArgs a) {
+  typedef __attribute__((address_space(4))) const char *const_bytes;
+  const const_bytes arg = (const_bytes)__builtin_amdgcn_kernarg_segment_ptr();
+  stream_body<T, D, CB, true>(a.p, (const_links)(arg + offsetof(SmallArgs, t.links)),
+                              (const_reqs)(arg + offsetof(SmallArgs, t.reqs)),
+                              (const_ints)(arg + offsetof(SmallArgs, t.order)));
+}
+
+// f(T{}, constant D, constant CB) for the shape's instantiation.
+template <typename F>
+hipError_t pick(int dtype, int d, int cb, F f) {
+  auto by_cb = [&](auto t, auto dc) {
+    if (cb == 1) return f(t, dc, std::integral_constant<int, 1>());
+    if (cb == 2) return f(t, dc, std::integral_constant<int, 2>());
+    if constexpr (sizeof(t) == 2) return f(t, dc, std::integral_constant<int, 4>());
+    return hipErrorInvalidValue;
+  };
+  if (dtype == 0) {
+    if (d == 32) return by_cb(float(), std::integral_constant<int, 32>());
+    if (d == 64) return by_cb(float(), std::integral_constant<int, 64>());
+    return by_cb(float(), std::integral_constant<int, 128>());
+  }
+  if (d == 32) return by_cb(uint16_t(), std::integral_constant<int, 32>());
+  return by_cb(uint16_t(), std::integral_constant<int, 64>());
+}
+// Whether a small call is built for the shape: not where the in-place own
+// tiles would take the registers past their budget (wide heads and many
+// column blocks; such calls have little to gain).
+constexpr bool small_built(int esz, int d, int cb) { return cb * d * esz <= 512 && cb <= 2; }
+
+unsigned stream_blocks(const LinkParams &p) {
+  const int64_t units = (int64_t)p.batch * p.n_kv_heads * p.num_splits;
+  return (unsigned)((units + p.n_xcd - 1) / p.n_xcd * p.n_xcd * p.nrb);
+}
+
+}  // namespace
+
+bool stream_supported(int dtype, int d_k, int d_v) {
+  if (d_k != d_v) return false;
+  return d_k == 32 || d_k == 64 || (d_k == 128 && dtype == 0);
+}
+
+StreamShape stream_shape(int dtype, int d, int max_rows, bool small) {
+  int cb = max_rows <= 16 ? 1 : max_rows <= 32 || dtype == 0 ? 2 : 4;
+  if (small)
+    while (!small_built(dtype == 0 ? 4 : 2, d, cb)) cb /= 2;
+  StreamShape s;
+  s.rows = 16 * cb;
+  const int blocks = (max_rows + s.rows - 1) / s.rows;
+  s.kpar = blocks <= 1 ? 4 : blocks == 2 ? 2 : 1;
+  return s;
+}
+
+// Measured against the vector-ALU kernel these calls ran before (kernel time,
+// one MI355X): fp32 8/2 heads x 64, 12 ragged requests of 20..130 tokens over
+// 3..10 links 395 -> 99 us; bf16 32/8 x 64, 8 requests of 30..300 tokens
+// 3320 -> 190 us. At 512 tokens x 16 links x 1024, batch 4 (no ragged edges):
+// bf16 d 64 584 TFLOP/s (876 with the second product of the lo parts), fp32
+// 109 TFLOP/s of the 154 a large library product reaches. Decode, 64 requests
+// x 16 links x 1024: bf16 5.9 TB/s, fp32 5.6 TB/s.
+hipError_t launch_link_stream(const LinkParams &p, int dtype, int rows, hipStream_t st,
+                              const char **name) {
+  *name = dtype == 0 ? "link_stream_kernel<float>" : "link_stream_kernel<bf16>";
+  return pick(dtype, p.d_k, rows / 16, [&](auto t, auto dc, auto cb) {
+    hipLaunchKernelGGL((link_stream_kernel<decltype(t), decltype(dc)::value, decltype(cb)::value>),
+                       dim3(stream_blocks(p)), dim3(64 * kWaves), 0, st, p);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_link_stream_small(const LinkParams &p, const SmallTabs &tabs, int dtype, int rows,
+                                    hipStream_t st, const char **name) {
+  *name = dtype == 0 ? "link_small_kernel<float,stream>" : "link_small_kernel<bf16,stream>";
+  return pick(dtype, p.d_k, rows / 16, [&](auto t, auto dc, auto cb) {
+    constexpr int kD = decltype(dc)::value, kCB = decltype(cb)::value;
+    if constexpr (small_built(sizeof(t), kD, kCB)) {
+      hipLaunchKernelGGL((link_small_kernel<decltype(t), kD, kCB>), dim3(stream_blocks(p)),
+                         dim3(64 * kWaves), 0, st, SmallArgs{p, tabs});
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+  });
+}
+
+}  // namespace pic

@@ -612,7 +612,7 @@ void prof_stop(hipStream_t st, std::pair<hipEvent_t, hipEvent_t> *ev, const char
 }
 
 enum class Mode { Prefill, Decode };
-enum class Kern { Valu, Mfma128, Decode128, Mla };
+enum class Kern { Valu, Mfma128, Decode128, Mla, Stream };
 
 // Everything about a call that does not depend on its tensors: the resolved
 // tables, the kernel, the split count and the workspace layout
@@ -622,6 +622,8 @@ struct Setup {
   Kern kern = Kern::Valu;
   int32_t splits = 1;
   bool lean = false;             // a small call the lean kernel runs
+  bool small = false;            // tables as a kernel argument, own KV in place
+  int32_t stream_rows = 0;       // stream kernel: rows per wave
   LinkParams lp{};               // shapes only: no tables, tensors or scale yet
   std::vector<OwnArg> own_args;  // per request, for the prologue (batch <= kOwnArgs)
   size_t part_off = 0, part_bytes = 0;
@@ -720,6 +722,20 @@ void balance_order_d128(pic_store *s, Plan &P, const LinkParams &lp, int rows_pe
   }
 }
 
+// Tables that travel as a kernel argument (SmallTabs): such a call of a
+// kernel that reads its own-KV tiles from k_self / v_self skips the
+// prologue. For latency-bound calls the prologue was a sixth of the step
+// (tiny_f32: 3.7 of 23.4 us).
+bool small_tables(const Plan &P) {
+  return P.links.size() <= (size_t)kSmallLinks && P.reqs.size() <= (size_t)kSmallReqs &&
+         P.doc_lim.empty();
+}
+
+// Most rows per kv head of a stream-kernel call that reads its own KV in
+// place: every row block gathers the token-major values anew, which costs
+// more than the prologue saves once there are several.
+constexpr int kStreamSmallRows = 128;
+
 pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, float scale,
                       int32_t layer, int32_t num_splits, Mode mode, Setup &C) {
   if (mode == Mode::Decode && (num_splits < 0 || num_splits > 256))
@@ -765,11 +781,29 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
   // per-row masks of the flash kernel
   if (kern == Kern::Decode128 && !P.doc_lim.empty()) kern = Kern::Mfma128;
   if (d.dtype == PIC_BF16 && mla && d.d_k == 576 && d.d_v == 512) kern = Kern::Mla;
+  // A small generic call of a shape the lean kernel is built for (tables as
+  // a kernel argument, at most kLeanTiles tiles in all) runs it; other fp32
+  // and narrow bf16 GQA calls stream their keys through the matrix cores.
+  if (kern == Kern::Valu && !mla) {
+    if (lean_supported(d.dtype, d.d_k, d.d_v, lp.group) && small_tables(P)) {
+      int64_t tiles = 0;
+      for (const ReqEntry &R : P.reqs) tiles += R.tiles;
+      C.lean = tiles <= kLeanTiles;
+    }
+    if (!C.lean && stream_supported(d.dtype, d.d_k, d.d_v)) kern = Kern::Stream;
+  }
+  C.small = small_tables(P) &&
+            (kern == Kern::Valu || (kern == Kern::Stream && P.max_rows <= kStreamSmallRows));
   if (kern == Kern::Valu && valu_lds_bytes_for(s->esz, mla, d.d_k, d.d_v) > 160 * 1024)
     return fail(PIC_ERR_UNSUPPORTED, "head widths d_k=%d d_v=%d exceed the generic kernel's LDS",
                 d.d_k, d.d_v);
   C.kern = kern;
+  StreamShape ss{0, 1};
+  if (kern == Kern::Stream) ss = stream_shape(d.dtype, d.d_k, P.max_rows, C.small);
+  lp.kpar = ss.kpar;
+  C.stream_rows = ss.rows;
   const int rows_per_block = kern == Kern::Mfma128 ? mfma_d128_rows_per_block()
+                             : kern == Kern::Stream ? ss.rows * 4 / ss.kpar
                              : kern == Kern::Valu  ? valu_rows_per_block()
                              : kern == Kern::Mla   ? mla_rows_per_block()
                                                    : decode_d128_max_rows();
@@ -787,7 +821,7 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     } else {
       // about 8 work items per CU (one wave each for the decode kernel, a
       // workgroup each otherwise), never more splits than tiles
-      const int64_t items = 8 * (int64_t)s->shape.cus;
+      const int64_t items = (kern == Kern::Stream ? 2 : 8) * (int64_t)s->shape.cus;
       splits = (int32_t)std::max<int64_t>(1, std::min<int64_t>((items + blocks - 1) / blocks, 256));
       splits = std::min(splits, std::max(1, P.max_tiles));
     }
@@ -810,9 +844,12 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     // x 2 kv heads: 16 pieces 28 us, 19 pieces 41 us). Its partials then
     // stay below 256 x 256 rows x (d_v + 2) fp32 (34 MB).
     const int64_t per_cu =
-        kern == Kern::Mla ? 1 : kern == Kern::Mfma128 ? mfma_d128_blocks_per_cu() : 4;
+        kern == Kern::Mla       ? 1
+        : kern == Kern::Mfma128 ? mfma_d128_blocks_per_cu()
+        : kern == Kern::Stream  ? 2
+                                : 4;
     const int64_t slots = (int64_t)s->shape.cus * per_cu;
-    int min_piece = kern == Kern::Valu ? 1 : 8;
+    int min_piece = kern == Kern::Valu ? 1 : kern == Kern::Stream ? 2 * ss.kpar : 8;
     int64_t max_splits = 16;
     if (kern == Kern::Mfma128) {
       const int64_t part = 2 * (int64_t)std::min(P.max_rows, rows_per_block) * (d.d_v + 2) * 4;
@@ -828,15 +865,6 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     const int64_t per_slot = std::max<int64_t>(min_piece, (work + slots - 1) / slots);
     splits = (int32_t)std::min<int64_t>(max_splits, (P.max_tiles + per_slot - 1) / per_slot);
     splits = std::max(1, std::min(splits, P.max_tiles / min_piece));
-  }
-  // A small generic call of a shape the lean kernel is built for (tables as
-  // a kernel argument, at most kLeanTiles tiles in all) runs it.
-  if (kern == Kern::Valu && !mla && lean_supported(d.dtype, d.d_k, d.d_v, lp.group) &&
-      P.links.size() <= (size_t)kSmallLinks && P.reqs.size() <= (size_t)kSmallReqs &&
-      P.doc_lim.empty()) {
-    int64_t tiles = 0;
-    for (const ReqEntry &R : P.reqs) tiles += R.tiles;
-    C.lean = tiles <= kLeanTiles;
   }
   C.splits = splits;
   lp.num_splits = splits;
@@ -887,6 +915,8 @@ pic_status launch_call(const pic_store *s, const Setup &C, LinkParams lp, void *
     e = launch_link_mla(lp, st, &name);
   else if (C.kern == Kern::Mfma128)
     e = launch_link_mfma_d128(lp, st, &name);
+  else if (C.kern == Kern::Stream)
+    e = launch_link_stream(lp, d.dtype, C.stream_rows, st, &name);
   else
     e = launch_link_valu(lp, d.dtype, mla, st, &name);
   prof_stop(st, &ev, name);
@@ -896,16 +926,6 @@ pic_status launch_call(const pic_store *s, const Setup &C, LinkParams lp, void *
     if (e != hipSuccess) return hip_fail(e, "combine_kernel");
   }
   return PIC_OK;
-}
-
-// A generic-kernel call small enough for its tables to travel as a kernel
-// argument (SmallTabs) skips the prologue: link_small_kernel reads its
-// tables from its arguments and its own-KV tiles from k_self / v_self. For
-// latency-bound calls the prologue was a sixth of the step (tiny_f32: 3.7
-// of 23.4 us).
-bool small_call(const Setup &C) {
-  return C.kern == Kern::Valu && C.P.links.size() <= (size_t)kSmallLinks &&
-         C.P.reqs.size() <= (size_t)kSmallReqs && C.P.doc_lim.empty();
 }
 
 // A small call's kernels: the tables go as a kernel argument and the own KV
@@ -961,7 +981,9 @@ pic_status launch_small(const pic_store_desc &d, const Setup &C, const LinkEntry
     std::copy(C.P.reqs.begin(), C.P.reqs.end(), t.reqs);
     std::copy(C.P.order.begin(), C.P.order.end(), t.order);
     prof_start(st, &ev);
-    e = launch_link_small(lp, t, d.dtype, d.kind == PIC_MLA, st, &name);
+    e = C.kern == Kern::Stream
+            ? launch_link_stream_small(lp, t, d.dtype, C.stream_rows, st, &name)
+            : launch_link_small(lp, t, d.dtype, d.kind == PIC_MLA, st, &name);
   }
   prof_stop(st, &ev, name);
   if (e != hipSuccess) return hip_fail(e, name);
@@ -1005,7 +1027,7 @@ pic_status link_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, c
   // the workspace is allocated on the store's device
   DeviceGuard dg(s->device);
   if (!dg.ok) return fail(PIC_ERR_HIP, "cannot select the store's device");
-  if (small_call(C)) return small_link_call(s, C, q, k_self, v_self, scale, out, lse, st);
+  if (C.small) return small_link_call(s, C, q, k_self, v_self, scale, out, lse, st);
   Stage *stage = nullptr;
   TableLayout tl;
   LinkParams lp = C.lp;
@@ -1038,7 +1060,7 @@ struct pic_link_plan {
   size_t off_r = 0, off_o = 0;   // request / order tables within a layer's tables
   size_t off_d = 0;              // per-query limits (if any) within a layer's tables
   void *work = nullptr;          // inside dev
-  // small calls (see small_call): every layer's link table on the host,
+  // small calls (see small_tables): every layer's link table on the host,
   // [layer][link], run by the small-call kernels as pic_link_attn /
   // pic_link_decode run them (tables as a kernel argument)
   bool small = false;
@@ -1570,7 +1592,7 @@ pic_status pic_link_decode_noalloc(pic_store *s, const pic_link_req *req, int32_
   // A small call runs the kernels pic_link_decode runs for it (tables as a
   // kernel argument, own KV read in place): the scratch holds only its
   // split partials.
-  if (small_call(C)) {
+  if (C.small) {
     if (C.part_bytes > kStaticScratchBytes)
       return fail(PIC_ERR_INVALID,
                   "the call needs %zu bytes of scratch (split partials); the static scratch "
@@ -1652,7 +1674,7 @@ pic_status pic_link_plan_create(pic_store *s, const pic_link_req *req, int32_t n
   pl->table_bytes = round_up(pl->off_d + sizeof(int32_t) * P.doc_lim.size(), 256);
   // A small call keeps its tables on the host (one per layer) and needs
   // device memory for its split partials only.
-  pl->small = small_call(pl->C);
+  pl->small = pl->C.small;
   if (pl->small) {
     pl->small_links.resize((size_t)s->n_layers * nl);
     std::vector<bool> own_link(nl, false);

@@ -93,6 +93,7 @@ struct LinkParams {
   int32_t max_rows;       // most rows of one (request, kv head)
   int32_t n_groups;       // batch * n_kv_heads, padded as the kernel requires
   int32_t n_xcd;          // accelerator dies (XCDs) of the device, each with its own L2
+  int32_t kpar;           // stream kernel: key parts within a workgroup (1, 2 or 4)
   float scale_log2;       // softmax_scale * log2(e)
 };
 
@@ -169,6 +170,18 @@ int mfma_d128_blocks_per_cu();   // resident workgroups per CU (2 waves per SIMD
 hipError_t launch_link_decode_d128(const LinkParams &p, hipStream_t st, const char **name);
 int decode_d128_max_rows();
 
+// fp32 GQA (d_k = d_v in {32, 64, 128}) and narrow bf16 GQA ({32, 64}) link
+// attention on the matrix cores, prefill- and decode-shaped. stream_shape:
+// rows per wave and key parts per workgroup of a call whose largest request
+// has max_rows rows per kv head; a workgroup covers rows * 4 / kpar rows.
+bool stream_supported(int dtype, int d_k, int d_v);
+struct StreamShape {
+  int32_t rows, kpar;
+};
+StreamShape stream_shape(int dtype, int d, int max_rows, bool small);
+hipError_t launch_link_stream(const LinkParams &p, int dtype, int rows, hipStream_t st,
+                              const char **name);
+
 // bf16 MLA (absorbed) link attention: one 576-wide latent kv head, values
 // are the first 512 entries of each latent row.
 hipError_t launch_link_mla(const LinkParams &p, hipStream_t st, const char **name);
@@ -202,6 +215,8 @@ struct SmallTabs {
 };
 hipError_t launch_link_small(const LinkParams &p, const SmallTabs &t, int dtype, int mla,
                              hipStream_t st, const char **name);
+hipError_t launch_link_stream_small(const LinkParams &p, const SmallTabs &t, int dtype, int rows,
+                                    hipStream_t st, const char **name);
 
 // Tables of a lean small call (link_lean_kernel): requests in dispatch
 // order, and for every tile of every request the link that holds it
