@@ -23,53 +23,6 @@ template <> __device__ __forceinline__ float from_f32<float>(float x) { return x
 template <> __device__ __forceinline__ uint16_t from_f32<uint16_t>(float x) { return bf16_rne(x); }
 
 // ---------------------------------------------------------------------------
-// Store layout transforms (the compile-side put; not on the link path).
-
-// src token-major [n][heads][width] -> dst [heads][lp][width], rows >= n zero.
-// width * esz is a multiple of 16, so every row is a whole number of uint4.
-__global__ void put_rows_kernel(const uint4 *__restrict__ src, uint4 *__restrict__ dst,
-                                int64_t n, int32_t lp, int32_t heads, int32_t vpr) {
-  const int64_t total = (int64_t)heads * lp * vpr;
-  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t h = idx / ((int64_t)lp * vpr);
-    const int64_t rem = idx - h * lp * vpr;
-    const int64_t t = rem / vpr;
-    const int64_t c = rem - t * vpr;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (t < n) v = src[(t * heads + h) * vpr + c];
-    dst[idx] = v;
-  }
-}
-
-// src token-major [n][heads][width] -> dst [heads][lp / 32][width][32]
-// (32-token panels, tokens contiguous), columns >= n zero. 64x64 tiles
-// through LDS so both the read and the write are coalesced.
-template <typename E>
-__global__ void put_transposed_kernel(const E *__restrict__ src, E *__restrict__ dst, int64_t n,
-                                      int32_t lp, int32_t heads, int32_t width) {
-  __shared__ E tile[64][65];
-  const int64_t t0 = (int64_t)blockIdx.x * 64;
-  const int e0 = blockIdx.y * 64;
-  const int h = blockIdx.z;
-  for (int i = threadIdx.x; i < 64 * 64; i += blockDim.x) {
-    const int tl = i >> 6, el = i & 63;
-    const int64_t t = t0 + tl;
-    const int e = e0 + el;
-    E v = E(0);
-    if (t < n && e < width) v = src[(t * heads + h) * width + e];
-    tile[tl][el] = v;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 64 * 64; i += blockDim.x) {
-    const int el = i >> 6, tl = i & 63;
-    const int64_t t = t0 + tl;
-    const int e = e0 + el;
-    if (e < width && t < lp) dst[vt_offset(h, e, t, lp, width)] = tile[tl][el];
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Address resolution shared by the gather hook and the attention kernels.
 
 // Link holding document token j of a request (links sorted by tok0).
@@ -120,24 +73,79 @@ __global__ void gather_kernel(const LinkEntry *__restrict__ links, int32_t n_lin
 }
 
 // Rows written into chunk slots (rows recomputed at link time): row i of the
-// token-major sources goes to dst[i], K into its head-major row, V into its
-// transposed column. Off the link path.
+// token-major sources goes to chunk token row[i], K into its head-major row,
+// V into its transposed column, one workgroup per row. The rows and the
+// chunk's views come as a kernel argument, so the call is one launch (a
+// table staged through the host-mapped buffer took a copy kernel before each
+// write: 2.5 us of GPU time and a launch per layer and document). 16-byte
+// units, every thread's loads before its stores: what a row costs is one
+// memory round trip (75 rows of 8 heads x 128: 6.7 us with 2-byte loads in
+// a loop of dependent divisions).
 template <typename E>
-__global__ void write_rows_kernel(const RowDst *__restrict__ dst, int32_t n,
-                                  const E *__restrict__ src_k, const E *__restrict__ src_v,
-                                  int32_t heads, int32_t d_k, int32_t d_v, int32_t mla) {
-  const int i = blockIdx.x;
-  if (i >= n) return;
-  const RowDst d = dst[i];
-  for (int x = threadIdx.x; x < heads * d_k; x += blockDim.x) {
-    const int h = x / d_k, c = x - h * d_k;
-    ((E *)d.k)[(int64_t)h * d.lp * d_k + c] = src_k[(int64_t)i * heads * d_k + x];
-  }
-  if (!mla)
-    for (int x = threadIdx.x; x < heads * d_v; x += blockDim.x) {
-      const int h = x / d_v, e = x - h * d_v;
-      ((E *)d.v)[(int64_t)h * d_v * d.lp + e * kPanel] = src_v[(int64_t)i * heads * d_v + x];
+__device__ __forceinline__ void write_row(char *dk, char *dv, int64_t lp, const E *src_k,
+                                          const E *src_v, int heads, int d_k, int d_v) {
+  constexpr int EPV = 16 / sizeof(E);
+  const int ku = heads * d_k / EPV, vu = dv ? heads * d_v / EPV : 0;
+  for (int x = threadIdx.x; x < ku + vu; x += blockDim.x) {
+    if (x < ku) {
+      const int h = x * EPV / d_k, c = x * EPV - h * d_k;
+      uint4 v;
+      __builtin_memcpy(&v, src_k + x * EPV, 16);
+      *(uint4 *)((E *)dk + (int64_t)h * lp * d_k + c) = v;
+    } else {
+      const int y = x - ku, h = y * EPV / d_v, e = y * EPV - h * d_v;
+      E v[EPV];
+      __builtin_memcpy(v, src_v + y * EPV, 16);
+      E *d = (E *)dv + (int64_t)h * d_v * lp + e * kPanel;
+#pragma unroll
+      for (int i = 0; i < EPV; ++i) d[i * kPanel] = v[i];
     }
+  }
+}
+template <typename E, int kRows>
+__global__ __launch_bounds__(256) void write_rows_kernel(WriteRows<kRows> w,
+                                                         const E *__restrict__ src_k,
+                                                         const E *__restrict__ src_v,
+                                                         int32_t heads, int32_t d_k, int32_t d_v) {
+  const int i = blockIdx.x;
+  const int t = w.row[i];
+  int u = 0;
+  while (u + 1 < w.n_views && w.view[u + 1].tok0 <= t) ++u;
+  const RowView V = w.view[u];
+  const int64_t at = t - V.tok0;
+  char *dk = (char *)V.k + at * d_k * (int)sizeof(E);
+  char *dv = V.v ? (char *)V.v + vt_offset(0, 0, at, V.lp, d_v) * (int)sizeof(E) : nullptr;
+  write_row<E>(dk, dv, V.lp, src_k + (int64_t)i * heads * d_k,
+               V.v ? src_v + (int64_t)i * heads * d_v : nullptr, heads, d_k, d_v);
+}
+
+// Whole 64-token pages copied between slots, every layer: page blockIdx.x / 2
+// (even: K, odd: V), kv head blockIdx.y, layer blockIdx.z. A page of one head is
+// 64 consecutive K rows and two consecutive V panels. One launch for up to
+// kCopyPages pages of a derived chunk (a 2D device copy per page, layer and
+// tensor was 660 launches of 2.6 us for 11 documents of 500 tokens in 4
+// layers).
+__global__ __launch_bounds__(256) void copy_pages_kernel(PageCopies c) {
+  const PageCopy P = c.page[blockIdx.x >> 1];
+  const int layer = blockIdx.z, h = blockIdx.y;
+  auto copy = [&](const char *src, char *dst, int64_t s_lp, int64_t d_lp, int width) {
+    const int64_t row = (int64_t)width * c.esz;
+    const uint4 *s = (const uint4 *)(src + layer * c.layer_bytes + h * s_lp * row);
+    uint4 *d = (uint4 *)(dst + layer * c.layer_bytes + h * d_lp * row);
+    const int n = (int)(kTile * row / 16);
+    for (int base = threadIdx.x; base < n; base += 4 * 256) {
+      uint4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = s[min(base + 256 * u, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (base + 256 * u < n) d[base + 256 * u] = make_uint4(v[u].x, v[u].y, v[u].z, v[u].w);
+    }
+  };
+  if ((blockIdx.x & 1) == 0)
+    copy(P.src_k, P.dst_k, P.src_lp, P.dst_lp, c.d_k);
+  else if (P.src_v)
+    copy(P.src_v, P.dst_v, P.src_lp, P.dst_lp, c.d_v);
 }
 
 // ---------------------------------------------------------------------------
@@ -164,7 +172,8 @@ struct PrepParams {
 // One 64-token x 64-value tile of own V, transposed into the slot's V block.
 // 16-byte global loads of 8 values of one token, an LDS tile with padded rows,
 // then 16-byte global stores of 8 tokens of one value dim.
-template <typename E>
+// kAligned: src is 16-byte aligned (else it is read element by element).
+template <typename E, bool kAligned = true>
 __device__ __forceinline__ void prep_transposed_tile(const ReqEntry &R, const LinkEntry &L,
                                                      const E *__restrict__ src, int heads,
                                                      int width, int tile) {
@@ -182,7 +191,17 @@ __device__ __forceinline__ void prep_transposed_tile(const ReqEntry &R, const Li
     const int64_t t = t0 + tl;
     const int e = e0 + ec * EPV;
     uint4 v = make_uint4(0, 0, 0, 0);
-    if (t < R.ls && e < width) v = *(const uint4 *)(src + ((R.s0 + t) * heads + h) * width + e);
+    if (t < R.ls && e < width) {
+      const E *p = src + ((R.s0 + t) * heads + h) * width + e;
+      if (kAligned) {
+        v = *(const uint4 *)p;
+      } else {
+        E x[EPV];
+#pragma unroll
+        for (int k = 0; k < EPV; ++k) x[k] = p[k];
+        __builtin_memcpy(&v, x, 16);
+      }
+    }
     *(uint4 *)(tile_s + tl * ROW + ec * EPV) = v;
   }
   __syncthreads();
@@ -199,6 +218,68 @@ __device__ __forceinline__ void prep_transposed_tile(const ReqEntry &R, const Li
     // EPV tokens (4 or 8) never straddle a 32-token panel
     *(uint4 *)(dst + vt_offset(h, e, t0 + tc * EPV, L.lp, width)) = vals.u;
   }
+}
+
+// K rows: dst [heads][lp][vpr] from src [token][heads][vpr] in 16-byte units
+// (zeros past the own rows), by workgroups 0 .. n_blocks - 1.
+__device__ __forceinline__ void prep_rows(const ReqEntry &R, const LinkEntry &L, const uint4 *src,
+                                          int heads, int vpr, int n_blocks) {
+  uint4 *dst = (uint4 *)L.k;
+  const int64_t total = (int64_t)heads * L.lp * vpr;
+  if (total < (int64_t)1 << 31) {
+    // 32-bit index math, and four units per thread loaded before any is
+    // stored, so their latencies overlap
+    const int per_h = L.lp * vpr, n = (int)total;
+    const int stride = n_blocks * blockDim.x;
+    for (int base = blockIdx.x * blockDim.x + threadIdx.x; base < n; base += 4 * stride) {
+      uint4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int idx = min(base + u * stride, n - 1);
+        const int h = idx / per_h, rem = idx - h * per_h, t = rem / vpr, c = rem - t * vpr;
+        v[u] = t < R.ls ? src[((int64_t)(R.s0 + t) * heads + h) * vpr + c]
+                        : make_uint4(0, 0, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (base + u * stride < n) dst[base + u * stride] = make_uint4(v[u].x, v[u].y, v[u].z, v[u].w);
+    }
+    return;
+  }
+  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
+       idx += (int64_t)n_blocks * blockDim.x) {
+    const int64_t h = idx / ((int64_t)L.lp * vpr);
+    const int64_t rem = idx - h * L.lp * vpr;
+    const int64_t t = rem / vpr;
+    const int64_t c = rem - t * vpr;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (t < R.ls) v = src[((R.s0 + t) * heads + h) * vpr + c];
+    dst[idx] = v;
+  }
+}
+
+// A chunk's rows laid out into one run of pages (the compile-side put), every
+// layer in one launch: layer blockIdx.y, the first rows_blocks workgroups K
+// rows, the others 64x64 tiles of V. A launch per layer and tensor, with
+// 2-byte reads and writes of the transposed values, took 3 + 9 us per layer
+// of 500 tokens (8 heads x 128).
+template <typename E, bool kAligned>
+__global__ __launch_bounds__(256) void put_kernel(PutParams pp) {
+  ReqEntry R;
+  R.s0 = 0;
+  R.ls = pp.n_tokens;
+  LinkEntry L;
+  L.k = pp.dst_k + blockIdx.y * pp.layer_bytes;
+  L.v = pp.dst_v + blockIdx.y * pp.layer_bytes;
+  L.lp = pp.lp;
+  if ((int)blockIdx.x < pp.rows_blocks) {
+    prep_rows(R, L, (const uint4 *)(pp.src_k + blockIdx.y * pp.src_k_layer), pp.heads,
+              pp.d_k * pp.esz / 16, pp.rows_blocks);
+    return;
+  }
+  const int tile = blockIdx.x - pp.rows_blocks;
+  const char *src = pp.src_v + blockIdx.y * pp.src_v_layer;
+  prep_transposed_tile<E, kAligned>(R, L, (const E *)src, pp.heads, pp.d_v, tile);
 }
 
 // The call's prologue. z slices 0 .. prep_z-1 lay out request z's own KV
@@ -230,42 +311,7 @@ __global__ void prep_own_kernel(PrepParams pp) {
   }
   if (R.ls == 0) return;
   if ((int)blockIdx.x < pp.rows_blocks) {
-    // K rows: dst [heads][lp][vpr] from src [token][heads][vpr] in 16-byte
-    // units (zeros past the own rows)
-    const int vpr = pp.d_k * pp.esz / 16;
-    const uint4 *src = (const uint4 *)pp.k_self;
-    uint4 *dst = (uint4 *)L.k;
-    const int64_t total = (int64_t)pp.heads * L.lp * vpr;
-    if (total < (int64_t)1 << 31) {
-      // 32-bit index math, and four units per thread loaded before any is
-      // stored, so their latencies overlap
-      const int per_h = L.lp * vpr, n = (int)total;
-      const int stride = pp.rows_blocks * blockDim.x;
-      for (int base = blockIdx.x * blockDim.x + threadIdx.x; base < n; base += 4 * stride) {
-        uint4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int idx = min(base + u * stride, n - 1);
-          const int h = idx / per_h, rem = idx - h * per_h, t = rem / vpr, c = rem - t * vpr;
-          v[u] = t < R.ls ? src[((int64_t)(R.s0 + t) * pp.heads + h) * vpr + c]
-                          : make_uint4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (base + u * stride < n) dst[base + u * stride] = make_uint4(v[u].x, v[u].y, v[u].z, v[u].w);
-      }
-      return;
-    }
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)pp.rows_blocks * blockDim.x) {
-      const int64_t h = idx / ((int64_t)L.lp * vpr);
-      const int64_t rem = idx - h * L.lp * vpr;
-      const int64_t t = rem / vpr;
-      const int64_t c = rem - t * vpr;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (t < R.ls) v = src[((R.s0 + t) * pp.heads + h) * vpr + c];
-      dst[idx] = v;
-    }
+    prep_rows(R, L, (const uint4 *)pp.k_self, pp.heads, pp.d_k * pp.esz / 16, pp.rows_blocks);
     return;
   }
   if (pp.mla) return;
@@ -1269,39 +1315,52 @@ hipError_t launch_table_copy(const void *src, void *dst, int64_t bytes, hipStrea
   return hipGetLastError();
 }
 
-hipError_t launch_put_rows(const void *src, void *dst, int64_t n_tokens, int32_t lp,
-                           int32_t heads, int32_t width, int32_t esz, hipStream_t st) {
-  const int32_t vpr = width * esz / 16;
-  const int64_t total = (int64_t)heads * lp * vpr;
-  const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 65536);
-  hipLaunchKernelGGL(put_rows_kernel, dim3(blocks), dim3(256), 0, st, (const uint4 *)src,
-                     (uint4 *)dst, n_tokens, lp, heads, vpr);
+hipError_t launch_put(PutParams pp, int32_t n_layers, hipStream_t st) {
+  const int64_t units = (int64_t)pp.heads * pp.lp * (pp.d_k * pp.esz / 16);
+  pp.rows_blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>((units + 1023) / 1024, 4096));
+  const bool aligned = (uintptr_t)pp.src_v % 16 == 0;
+  const int64_t tiles =
+      pp.src_v ? (int64_t)pp.heads * (pp.lp / 64) * ((pp.d_v + 63) / 64) : 0;
+  const dim3 grid((unsigned)(pp.rows_blocks + tiles), (unsigned)n_layers);
+  if (pp.esz == 2) {
+    if (aligned)
+      hipLaunchKernelGGL((put_kernel<uint16_t, true>), grid, dim3(256), 0, st, pp);
+    else
+      hipLaunchKernelGGL((put_kernel<uint16_t, false>), grid, dim3(256), 0, st, pp);
+  } else {
+    if (aligned)
+      hipLaunchKernelGGL((put_kernel<uint32_t, true>), grid, dim3(256), 0, st, pp);
+    else
+      hipLaunchKernelGGL((put_kernel<uint32_t, false>), grid, dim3(256), 0, st, pp);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_put_transposed(const void *src, void *dst, int64_t n_tokens, int32_t lp,
-                                 int32_t heads, int32_t width, int32_t esz, hipStream_t st) {
-  dim3 grid(lp / 64, (width + 63) / 64, heads);
-  if (esz == 2)
-    hipLaunchKernelGGL(put_transposed_kernel<uint16_t>, grid, dim3(256), 0, st,
-                       (const uint16_t *)src, (uint16_t *)dst, n_tokens, lp, heads, width);
-  else
-    hipLaunchKernelGGL(put_transposed_kernel<uint32_t>, grid, dim3(256), 0, st,
-                       (const uint32_t *)src, (uint32_t *)dst, n_tokens, lp, heads, width);
+hipError_t launch_copy_pages(const PageCopies &c, int32_t n, int32_t n_layers, hipStream_t st) {
+  hipLaunchKernelGGL(copy_pages_kernel, dim3(2 * n, c.heads, n_layers), dim3(256), 0, st, c);
   return hipGetLastError();
 }
 
-hipError_t launch_write_rows(const RowDst *dst, int32_t n, const void *src_k, const void *src_v,
-                             int32_t heads, int32_t d_k, int32_t d_v, int32_t mla, int32_t esz,
-                             hipStream_t st) {
+hipError_t launch_write_rows(const RowView *views, int32_t n_views, const int32_t *rows, int32_t n,
+                             const void *src_k, const void *src_v, int32_t heads, int32_t d_k,
+                             int32_t d_v, int32_t esz, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  if (esz == 2)
-    hipLaunchKernelGGL(write_rows_kernel<uint16_t>, dim3(n), dim3(256), 0, st, dst, n,
-                       (const uint16_t *)src_k, (const uint16_t *)src_v, heads, d_k, d_v, mla);
-  else
-    hipLaunchKernelGGL(write_rows_kernel<uint32_t>, dim3(n), dim3(256), 0, st, dst, n,
-                       (const uint32_t *)src_k, (const uint32_t *)src_v, heads, d_k, d_v, mla);
-  return hipGetLastError();
+  auto go = [&](auto kc) {
+    constexpr int kRows = decltype(kc)::value;
+    WriteRows<kRows> w;
+    w.n_views = n_views;
+    std::copy(views, views + n_views, w.view);
+    std::copy(rows, rows + n, w.row);
+    if (esz == 2)
+      hipLaunchKernelGGL((write_rows_kernel<uint16_t, kRows>), dim3(n), dim3(256), 0, st, w,
+                         (const uint16_t *)src_k, (const uint16_t *)src_v, heads, d_k, d_v);
+    else
+      hipLaunchKernelGGL((write_rows_kernel<uint32_t, kRows>), dim3(n), dim3(256), 0, st, w,
+                         (const uint32_t *)src_k, (const uint32_t *)src_v, heads, d_k, d_v);
+    return hipGetLastError();
+  };
+  if (n <= kWriteRowsFew) return go(std::integral_constant<int, kWriteRowsFew>());
+  return go(std::integral_constant<int, kWriteRowsMost>());
 }
 
 hipError_t launch_gather(const LinkEntry *links, int32_t n_links, int64_t total_tokens,

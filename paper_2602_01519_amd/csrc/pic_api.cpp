@@ -1173,19 +1173,24 @@ pic_status pic_store_put(pic_store *s, uint64_t chunk_id, int64_t n_tokens, cons
   const int64_t k_src_layer = n_tokens * s->k_tok_elems * s->esz;
   const int64_t v_src_layer = n_tokens * s->v_tok_elems * s->esz;
   hipError_t e = hipSuccess;
-  for (int32_t l = 0; l < s->n_layers && e == hipSuccess; ++l) {
-    for (const Run &r : runs) {
-      const LinkEntry E = run_entry(s, r, l);
-      const char *ksrc = (const char *)k + l * k_src_layer + (int64_t)r.tok0 * s->k_tok_elems * s->esz;
-      e = launch_put_rows(ksrc, (void *)E.k, r.ntok, E.lp, d.n_kv_heads, d.d_k, s->esz, st);
-      if (e != hipSuccess) break;
-      if (gqa) {
-        const char *vsrc =
-            (const char *)v + l * v_src_layer + (int64_t)r.tok0 * s->v_tok_elems * s->esz;
-        e = launch_put_transposed(vsrc, (void *)E.v, r.ntok, E.lp, d.n_kv_heads, d.d_v, s->esz, st);
-        if (e != hipSuccess) break;
-      }
-    }
+  for (const Run &r : runs) {
+    const LinkEntry E = run_entry(s, r, 0);
+    PutParams pp{};
+    pp.src_k = (const char *)k + (int64_t)r.tok0 * s->k_tok_elems * s->esz;
+    pp.src_v = gqa ? (const char *)v + (int64_t)r.tok0 * s->v_tok_elems * s->esz : nullptr;
+    pp.dst_k = (char *)E.k;
+    pp.dst_v = (char *)E.v;
+    pp.src_k_layer = k_src_layer;
+    pp.src_v_layer = v_src_layer;
+    pp.layer_bytes = s->layer_bytes;
+    pp.n_tokens = r.ntok;
+    pp.lp = E.lp;
+    pp.heads = d.n_kv_heads;
+    pp.d_k = d.d_k;
+    pp.d_v = d.d_v;
+    pp.esz = s->esz;
+    e = launch_put(pp, s->n_layers, st);
+    if (e != hipSuccess) break;
   }
   if (e != hipSuccess) {
     for (const Run &r : runs) free_run(s, r.page0, r.pages);
@@ -1262,21 +1267,22 @@ pic_status pic_store_derive(pic_store *s, uint64_t new_id, uint64_t base_id, int
   const hipStream_t st = (hipStream_t)stream;
   const pic_store_desc &d = s->desc;
   hipError_t e = hipSuccess;
-  for (int32_t l = 0; l < s->n_layers && e == hipSuccess; ++l)
-    for (const auto &c : copies) {
-      const LinkEntry S = run_entry(s, c.first, l), D = run_entry(s, c.second, l);
-      const size_t kw = (size_t)kTile * d.d_k * s->esz;
-      e = hipMemcpy2DAsync((void *)D.k, (size_t)D.lp * d.d_k * s->esz, S.k,
-                           (size_t)S.lp * d.d_k * s->esz, kw, (size_t)d.n_kv_heads,
-                           hipMemcpyDeviceToDevice, st);
-      if (e != hipSuccess) break;
-      if (d.kind == PIC_GQA) {   // a page is two whole V^T panels per head
-        e = hipMemcpy2DAsync((void *)D.v, (size_t)D.lp * d.d_v * s->esz, S.v,
-                             (size_t)S.lp * d.d_v * s->esz, (size_t)kTile * d.d_v * s->esz,
-                             (size_t)d.n_kv_heads, hipMemcpyDeviceToDevice, st);
-        if (e != hipSuccess) break;
-      }
+  for (size_t c0 = 0; c0 < copies.size() && e == hipSuccess; c0 += kCopyPages) {
+    const size_t n = std::min<size_t>(kCopyPages, copies.size() - c0);
+    PageCopies pc;
+    pc.layer_bytes = s->layer_bytes;
+    pc.heads = d.n_kv_heads;
+    pc.d_k = d.d_k;
+    pc.d_v = d.d_v;
+    pc.esz = s->esz;
+    for (size_t i = 0; i < n; ++i) {
+      const LinkEntry S = run_entry(s, copies[c0 + i].first, 0), D = run_entry(s, copies[c0 + i].second, 0);
+      const bool gqa = d.kind == PIC_GQA;
+      pc.page[i] = PageCopy{(const char *)S.k, gqa ? (const char *)S.v : nullptr, (char *)D.k,
+                            gqa ? (char *)D.v : nullptr, S.lp, D.lp};
     }
+    e = launch_copy_pages(pc, (int32_t)n, s->n_layers, st);
+  }
   if (e != hipSuccess) {
     for (const Run &r : fresh) free_run(s, r.page0, r.pages);
     return hip_fail(e, "derive page copies");
@@ -1317,34 +1323,42 @@ pic_status pic_store_write_rows(pic_store *s, uint64_t chunk_id, int32_t layer, 
   const bool gqa = s->desc.kind == PIC_GQA;
   if (!k || (gqa && !v)) return fail(PIC_ERR_INVALID, "k/v is NULL");
   if (!gqa && v) return fail(PIC_ERR_INVALID, "v must be NULL for MLA");
-  std::vector<RowDst> dst(n_rows);
   for (int32_t i = 0; i < n_rows; ++i) {
     const Run &r = view_of(sl, rows[i]);
     if (s->page_refs[r.page0 + r.skip + (rows[i] - r.tok0) / kTile] != 1)
       return fail(PIC_ERR_INVALID, "row %d of chunk 0x%llx is on a page shared with another chunk",
                   rows[i], (unsigned long long)chunk_id);
-    const LinkEntry E = run_entry(s, r, layer);
-    const int64_t t = rows[i] - r.tok0;
-    dst[i].k = (char *)E.k + t * s->desc.d_k * s->esz;
-    dst[i].v = gqa ? (char *)E.v + vt_offset(0, 0, t, E.lp, s->desc.d_v) * s->esz : nullptr;
-    dst[i].lp = E.lp;
   }
   DeviceGuard dg(s->device);
   if (!dg.ok) return fail(PIC_ERR_HIP, "cannot select the store's device");
-  const hipStream_t st = (hipStream_t)stream;
-  const size_t bytes = sizeof(RowDst) * (size_t)n_rows;
-  Stage *stage = nullptr;
-  pic_status rc = stage_acquire(s, bytes, &stage);
-  if (rc != PIC_OK) return rc;
-  memcpy(stage->host, dst.data(), bytes);
-  HIP_TRY(launch_table_copy(stage->host_dev, stage->dev, (int64_t)round_up(bytes, 16), st),
-          "table_copy_kernel");
   const pic_store_desc &d = s->desc;
-  HIP_TRY(launch_write_rows((const RowDst *)stage->dev, n_rows, k, v, d.n_kv_heads, d.d_k, d.d_v,
-                            !gqa, s->esz, st),
-          "write_rows_kernel");
-  HIP_TRY(hipEventRecord(stage->done, st), "hipEventRecord(stage)");
-  stage->pending = true;
+  // one launch per kWriteRowsMost rows or kWriteViews of the views they lie in
+  RowView views[kWriteViews];
+  size_t v0 = 0;                     // the view after the last one listed
+  int32_t n_views = 0, first = 0;    // views listed, first row not yet written
+  auto flush = [&](int32_t end) {
+    const int64_t done = first;
+    const hipError_t e = launch_write_rows(
+        views, n_views, rows + first, end - first,
+        (const char *)k + done * s->k_tok_elems * s->esz,
+        gqa ? (const char *)v + done * s->v_tok_elems * s->esz : nullptr, d.n_kv_heads, d.d_k,
+        d.d_v, s->esz, (hipStream_t)stream);
+    first = end;
+    n_views = 0;
+    return e;
+  };
+  for (int32_t i = 0; i < n_rows; ++i) {
+    const bool listed = n_views > 0 && rows[i] < sl.runs[v0 - 1].tok0 + sl.runs[v0 - 1].ntok;
+    if (i - first == kWriteRowsMost || (!listed && n_views == kWriteViews))
+      HIP_TRY(flush(i), "write_rows_kernel");
+    if (listed && n_views > 0) continue;
+    v0 = 0;
+    while (rows[i] >= sl.runs[v0].tok0 + sl.runs[v0].ntok) ++v0;
+    const LinkEntry E = run_entry(s, sl.runs[v0], layer);
+    views[n_views++] = RowView{(void *)E.k, gqa ? (void *)E.v : nullptr, E.lp, sl.runs[v0].tok0};
+    ++v0;
+  }
+  HIP_TRY(flush(n_rows), "write_rows_kernel");
   return PIC_OK;
 }
 

@@ -107,27 +107,58 @@ struct DevShape {
 DevShape device_shape();
 
 // Launchers (each returns the launch status).
-hipError_t launch_put_rows(const void *src, void *dst, int64_t n_tokens, int32_t lp,
-                           int32_t heads, int32_t width, int32_t esz, hipStream_t st);
-hipError_t launch_put_transposed(const void *src, void *dst, int64_t n_tokens, int32_t lp,
-                                 int32_t heads, int32_t width, int32_t esz, hipStream_t st);
+
+// One run of a put chunk: token-major sources [layer][n_tokens..][heads][d]
+// into the run's K block and V block of every layer (src_v NULL for MLA).
+struct PutParams {
+  const char *src_k, *src_v;      // the run's first token, layer 0
+  char *dst_k, *dst_v;            // the run's blocks in layer 0
+  int64_t src_k_layer, src_v_layer, layer_bytes;   // bytes from layer to layer
+  int32_t n_tokens, lp, heads, d_k, d_v, esz;
+  int32_t rows_blocks;            // set by launch_put
+};
+hipError_t launch_put(PutParams pp, int32_t n_layers, hipStream_t st);
 hipError_t launch_gather(const LinkEntry *links, int32_t n_links, int64_t total_tokens,
                          int32_t heads, int32_t d_k, int32_t d_v, int32_t mla, int32_t esz,
                          void *k_out, void *v_out, hipStream_t st);
 
-// Destination of one row written into a chunk slot: its K row of head 0
-// (head h at + h * lp * d_k elements) and its V^T entry of head 0, dim 0
-// (head h, dim e at + h * d_v * lp + e * kPanel; unused for MLA).
-struct RowDst {
-  void *k;
-  void *v;
-  int64_t lp;
+// Page copies of a derived chunk (kernel argument): pages of 64 tokens, kv
+// head 0 of layer 0 (head h at + h * lp * width elements); v NULL for MLA.
+struct PageCopy {
+  const char *src_k, *src_v;
+  char *dst_k, *dst_v;
+  int32_t src_lp, dst_lp;
+};
+constexpr int kCopyPages = 64;
+struct PageCopies {
+  PageCopy page[kCopyPages];
+  int64_t layer_bytes;
+  int32_t heads, d_k, d_v, esz;
+};
+hipError_t launch_copy_pages(const PageCopies &c, int32_t n, int32_t n_layers, hipStream_t st);
+
+// A view of a chunk in one layer, for rows written into it: its K rows and V
+// panels of head 0 (head h at + h * lp * width elements; v NULL for MLA)
+// from chunk token tok0 on.
+struct RowView {
+  void *k, *v;
+  int32_t lp, tok0;
+};
+// Kernel argument of a row write: up to kRows rows in up to kWriteViews
+// views (ascending tokens).
+constexpr int kWriteViews = 16, kWriteRowsFew = 128, kWriteRowsMost = 768;
+template <int kRows>
+struct WriteRows {
+  RowView view[kWriteViews];
+  int32_t n_views;
+  int32_t row[kRows];
 };
 // Scatters token-major rows src_k [n][heads][d_k] (and src_v [n][heads][d_v]
-// unless mla) to the slot rows dst[0 .. n).
-hipError_t launch_write_rows(const RowDst *dst, int32_t n, const void *src_k, const void *src_v,
-                             int32_t heads, int32_t d_k, int32_t d_v, int32_t mla, int32_t esz,
-                             hipStream_t st);
+// unless the views' v are NULL) to chunk tokens rows[0 .. n), n <=
+// kWriteRowsMost, n_views <= kWriteViews.
+hipError_t launch_write_rows(const RowView *views, int32_t n_views, const int32_t *rows, int32_t n,
+                             const void *src_k, const void *src_v, int32_t heads, int32_t d_k,
+                             int32_t d_v, int32_t esz, hipStream_t st);
 
 // Copies bytes (a multiple of 16) from a host-mapped buffer to the device.
 hipError_t launch_table_copy(const void *src, void *dst, int64_t bytes, hipStream_t st);
