@@ -3,7 +3,7 @@
 // Decode reads every linked key once per query token (a generated token is a
 // query token, Sec. 4), so the work is a stream over the request's
 // concatenated chunk KV (Sec. 4.2) bounded by HBM bandwidth, not by math.
-// Each wave owns one work item (request, kv head, key split) and streams its
+// Each wave owns one kv head of a work item (a piece of a request's keys) and streams its
 // key range in 32-key tiles straight from HBM into registers, already in the
 // operand layout of v_mfma_f32_16x16x32_bf16:
 //   S^T[32 keys][16 cols] = K . Q^T    2 key blocks x 4 d steps  (8 MFMAs)
@@ -37,13 +37,6 @@ constexpr int kCols = 16;         // MFMA N: rows of a work item
 constexpr int kWaves = 4;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
-__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ const char *uni(const void *p) {
-  const uint64_t u = (uint64_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-  return (const char *)(((uint64_t)hi << 32) | lo);
-}
 
 // Reduction over the 4 lane groups (l, l^16, l^32, l^48) of a column.
 __device__ __forceinline__ float col_max(float x) {
@@ -70,37 +63,45 @@ struct Tile {
 struct TileInfo {
   const char *k;    // first K row of the tile, kv head applied (bytes)
   const char *v;    // the tile's V^T panel, kv head applied
-  int lp;           // padded tokens of the link
   int nvalid;       // valid keys in the tile
   int j0;           // key index of the tile's first key within its link
   int own;          // own-KV tile (causal mask)
 };
 
 struct Cursor {
-  const LinkEntry *links;  // the request's links
+  const_links links;       // the request's links, from the item's first on
   int li;                  // current link
+  const char *k, *v;       // its K / V^T blocks
+  int len, lp, tile0, end; // its tokens, padded tokens, first tile, tile after its last (32-key)
   int kvh;
   int doc_tiles32;         // 32-key tiles over the documents
 };
 
+__device__ __forceinline__ void cursor_set(Cursor &c, const void *k, const void *v, int len, int lp,
+                                           int tile0) {
+  c.k = (const char *)k;
+  c.v = (const char *)v;
+  c.len = len;
+  c.lp = lp;
+  c.tile0 = tile0 * (kTile / kT);
+  c.end = c.tile0 + (len + kTile - 1) / kTile * (kTile / kT);
+}
+
 // Tile t (32-key units, t only grows) of the request.
 __device__ __forceinline__ TileInfo tile_info(Cursor &c, int t) {
-  for (;;) {
-    const LinkEntry &e = c.links[c.li];
-    const int tile0 = uni(e.tile0) * (kTile / kT), lp = uni(e.lp);
-    if (t < tile0 + (uni(e.len) + kTile - 1) / kTile * (kTile / kT)) {
-      const int tt = t - tile0;
-      TileInfo r;
-      r.lp = lp;
-      r.nvalid = min(kT, uni(e.len) - tt * kT);
-      r.j0 = tt * kT;
-      r.own = t >= c.doc_tiles32;
-      r.k = uni(e.k) + ((int64_t)c.kvh * lp + tt * kT) * kD * 2;
-      r.v = uni(e.v) + ((int64_t)c.kvh * kD * lp + tt * kT * kD) * 2;   // the tile's V^T panel
-      return r;
-    }
+  while (t >= c.end) {
     ++c.li;
+    cursor_set(c, c.links[c.li].k, c.links[c.li].v, c.links[c.li].len, c.links[c.li].lp,
+               c.links[c.li].tile0);
   }
+  const int tt = t - c.tile0;
+  TileInfo r;
+  r.nvalid = min(kT, c.len - tt * kT);
+  r.j0 = tt * kT;
+  r.own = t >= c.doc_tiles32;
+  r.k = c.k + ((int64_t)c.kvh * c.lp + tt * kT) * kD * 2;
+  r.v = c.v + ((int64_t)c.kvh * kD * c.lp + tt * kT * kD) * 2;   // the tile's V^T panel
+  return r;
 }
 
 // Per-lane byte offsets of the tile's loads: K block b, step s: key row
@@ -116,17 +117,48 @@ __device__ __forceinline__ uint4 load_nt(const char *p) {
   return make_uint4(w.x, w.y, w.z, w.w);
 }
 
-__device__ __forceinline__ void load_tile(const TileInfo &r, int lane, Tile &x) {
+// Not live: the lanes of a load all read the same 16 bytes (one line), for
+// the load that past the last tile only keeps the number of loads in flight
+// fixed.
+__device__ __forceinline__ void load_tile(const TileInfo &r, int lane, bool live, Tile &x) {
+  const int grp = lane >> 4, m = lane & 15;
+  const uint32_t mask = live ? ~0u : 0u;
+  const uint32_t koff = (uint32_t)(((8 * (m >> 2) + (m & 3)) * kD + 8 * grp) * 2) & mask;
+  const uint32_t voff = (uint32_t)(m * kT * 2 + 16 * grp) & mask;
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      x.k[b * 4 + s] = load_nt(r.k + koff + (4 * b * kD + 32 * s) * 2);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) x.v[b] = load_nt(r.v + voff + 16 * b * kT * 2);
+}
+
+// Own-KV tile read in place: keys j0 .. of the request's token-major own rows
+// (k, v: its first own row, kv head applied; stride: bytes per token). Keys
+// past the last own one reread it; they are masked.
+__device__ __forceinline__ void load_own(const char *k, const char *v, int64_t stride, int j0,
+                                         int last, int lane, Tile &x) {
   const int grp = lane >> 4, m = lane & 15;
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
-    const int krow = 8 * (m >> 2) + 4 * b + (m & 3);
+    const char *row = k + min(j0 + 8 * (m >> 2) + 4 * b + (m & 3), last) * stride + 16 * grp;
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-      x.k[b * 4 + s] = load_nt(r.k + (uint32_t)((krow * kD + 32 * s + 8 * grp) * 2));
+    for (int s = 0; s < 4; ++s) x.k[b * 4 + s] = *(const uint4 *)(row + 64 * s);
+  }
+  uint32_t w[8][4];
+#pragma unroll
+  for (int b = 0; b < 8; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[b][i] = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const uint16_t *row = (const uint16_t *)(v + min(j0 + 8 * grp + i, last) * stride) + m;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) w[b][i >> 1] |= (uint32_t)row[16 * b] << (16 * (i & 1));
   }
 #pragma unroll
-  for (int b = 0; b < 8; ++b) x.v[b] = load_nt(r.v + (uint32_t)((16 * b + m) * kT * 2 + 16 * grp));
+  for (int b = 0; b < 8; ++b) x.v[b] = make_uint4(w[b][0], w[b][1], w[b][2], w[b][3]);
 }
 
 struct State {
@@ -185,26 +217,22 @@ __device__ __forceinline__ void compute_tile(const Tile &x, const TileInfo &r,
 __global__ __launch_bounds__(256, 2) void link_decode_d128_kernel(LinkParams p) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // work item: (group = request x kv head, split); waves of a block take
-  // consecutive splits of one group
-  const int item = blockIdx.x * kWaves + wave;
-  const int S = p.num_splits;
-  const int grp = item / S, split = item % S;
-  if (grp >= p.batch * p.n_kv_heads) return;
-  const int req_i = p.order[grp / p.n_kv_heads];
-  const int kvh = grp % p.n_kv_heads;
-  const ReqEntry R = p.reqs[req_i];
+  // one (item, kv head) per wave
+  const int u = blockIdx.x * kWaves + wave;
+  if (u >= p.n_items * p.n_kv_heads) return;
+  const int kvh = u % p.n_kv_heads;
+  const WorkItem it = load_item(p.items, u / p.n_kv_heads);
+  const ReqEntry R = item_request(it);
   const int group = p.group;
   const int nrows = R.lq * group;                 // <= kCols (checked by the planner)
-  const int tiles = R.tiles * (kTile / kT);
-  const int t_begin = (int)((int64_t)tiles * split / S);
-  const int t_end = (int)((int64_t)tiles * (split + 1) / S);
+  const int t_begin = it.t_begin, t_end = it.t_end;
 
   Cursor cur;
-  cur.links = p.links + R.link0;
+  cur.links = (const_links)p.links + it.link;
   cur.li = 0;
   cur.kvh = kvh;
   cur.doc_tiles32 = R.doc_tiles * (kTile / kT);
+  cursor_set(cur, it.k, it.v, it.len, it.lp, it.tile0);
 
   // This lane's column (row of the work item).
   const int col = lane & 15;
@@ -214,11 +242,14 @@ __global__ __launch_bounds__(256, 2) void link_decode_d128_kernel(LinkParams p) 
   const int lim = cvalid ? qi + R.ls - R.lq : -1;
   const int64_t orow = (int64_t)(R.q0 + qi) * p.n_q_heads + qh;
 
+  // Own KV in place: the own tiles come first (the order of the keys does not
+  // matter to the sums), while the first document tile is in flight.
+  const int doc_end = p.own_in_place ? min(t_end, cur.doc_tiles32) : t_end;
   Tile ta, tb;
   TileInfo ia{}, ib{};
-  if (t_begin < t_end) {
+  if (t_begin < doc_end) {
     ia = tile_info(cur, t_begin);
-    load_tile(ia, lane, ta);
+    load_tile(ia, lane, true, ta);
   }
   // Q operand: Q^T[d = 32 s + 8 (l/16) + 0..7][col]
   bf16x8 qf[4];
@@ -238,17 +269,30 @@ __global__ __launch_bounds__(256, 2) void link_decode_d128_kernel(LinkParams p) 
   st.l = 0.f;
   const float sc = p.scale_log2;
 
-  for (int t = t_begin; t < t_end; t += 2) {
-    if (t + 1 < t_end) {
-      ib = tile_info(cur, t + 1);
-      load_tile(ib, lane, tb);
+  if (p.own_in_place) {
+    const int64_t at = ((int64_t)it.tok0 * p.n_kv_heads + kvh) * kD * 2;
+    const int64_t stride = (int64_t)p.n_kv_heads * kD * 2;
+    const int own_end = min(t_end, cur.doc_tiles32 + (R.ls + kT - 1) / kT);
+    for (int t = max(t_begin, cur.doc_tiles32); t < own_end; ++t) {
+      ib.own = 1;
+      ib.j0 = (t - cur.doc_tiles32) * kT;
+      ib.nvalid = min(kT, R.ls - ib.j0);
+      load_own((const char *)p.k_self + at, (const char *)p.v_self + at, stride, ib.j0, R.ls - 1,
+               lane, tb);
+      compute_tile(tb, ib, qf, st, lane, lim, sc);
     }
+  }
+  // The loads past the last tile read next to nothing of it: a branch around
+  // them makes the compiler wait for every load in flight where the paths
+  // meet, so that no load ran under the arithmetic of its own wave (64
+  // requests x 16 links of 1024: 670 -> 660 us).
+  for (int t = t_begin; t < doc_end; t += 2) {
+    ib = tile_info(cur, min(t + 1, doc_end - 1));
+    load_tile(ib, lane, t + 1 < doc_end, tb);
     compute_tile(ta, ia, qf, st, lane, lim, sc);
-    if (t + 1 >= t_end) break;
-    if (t + 2 < t_end) {
-      ia = tile_info(cur, t + 2);
-      load_tile(ia, lane, ta);
-    }
+    if (t + 1 >= doc_end) break;
+    ia = tile_info(cur, min(t + 2, doc_end - 1));
+    load_tile(ia, lane, t + 2 < doc_end, ta);
     compute_tile(tb, ib, qf, st, lane, lim, sc);
   }
 
@@ -256,8 +300,7 @@ __global__ __launch_bounds__(256, 2) void link_decode_d128_kernel(LinkParams p) 
   if (!cvalid) return;
   // lane l holds value rows 16 b + 4 (l/16) + i of column l%16
   const int r4 = 4 * (lane >> 4);
-  const int total_rows = p.total_q * p.n_q_heads;
-  if (S == 1) {
+  if (it.part < 0) {
     const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
     uint16_t *out = (uint16_t *)p.out + orow * kD;
 #pragma unroll
@@ -270,7 +313,7 @@ __global__ __launch_bounds__(256, 2) void link_decode_d128_kernel(LinkParams p) 
     if (p.lse && lane < 16)
       p.lse[orow] = ltot > 0.f ? (st.m + log2f(ltot)) * 0.69314718055994531f : -INFINITY;
   } else {
-    const int64_t prow = (int64_t)split * total_rows + orow;
+    const int64_t prow = it.part + (orow - (int64_t)R.q0 * p.n_q_heads);
     float *po = p.part_o + prow * kD;
 #pragma unroll
     for (int b = 0; b < 8; ++b)
@@ -288,7 +331,7 @@ int decode_d128_max_rows() { return kCols; }
 
 hipError_t launch_link_decode_d128(const LinkParams &p, hipStream_t st, const char **name) {
   *name = "link_decode_d128_kernel";
-  const int64_t items = (int64_t)p.batch * p.n_kv_heads * p.num_splits;
+  const int64_t items = (int64_t)p.n_items * p.n_kv_heads;
   dim3 grid((unsigned)((items + kWaves - 1) / kWaves));
   hipLaunchKernelGGL(link_decode_d128_kernel, grid, dim3(64 * kWaves), 0, st, p);
   return hipGetLastError();

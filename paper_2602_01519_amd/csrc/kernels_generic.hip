@@ -798,9 +798,9 @@ __global__ __launch_bounds__(256) void link_small_kernel(LinkParams p, SmallTabs
 // round trip and no cross-lane reduction; the row's waves then merge through
 // LDS. With one wave per row the passes are a serial chain of round trips:
 // 32 splits of 1184 rows took 7.4 us (now 5.6), 43 of 192 rows 8.9 us (4.0),
-// 43 of 512 rows 512 wide 20.2 us (12.1). Every (split,
-// row) partial below the request's split count is written by the attention
-// kernels (zeros with m = -inf for an empty split).
+// 43 of 512 rows 512 wide 20.2 us (12.1). Every (split, row) partial below
+// the request's split count is written by the attention kernels (zeros with
+// m = -inf for an empty split).
 template <typename T>
 __device__ __forceinline__ void store_pair(T *out, int e, float x, float y);
 template <>
@@ -823,13 +823,28 @@ __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
   // scalar loads
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int sub = wave % kWpr;
-  const int64_t rows = (int64_t)p.total_q * p.n_q_heads;
-  const int64_t orow = (int64_t)blockIdx.x * kRowsPerBlock + wave / kWpr;
-  const bool valid = orow < rows;
-  const int S = valid ? p.num_splits : 0, dv = p.d_v;
+  int64_t rows, row0 = 0, part0 = 0;
+  int splits;
+  if (p.comb) {            // request blockIdx.y
+    typedef __attribute__((address_space(4))) const CombineEntry *const_comb;
+    const const_comb e = (const_comb)p.comb + blockIdx.y;
+    rows = e->rows;
+    row0 = e->row0;
+    part0 = e->part0;
+    splits = e->splits;
+    // not split (its rows are in out already), or fewer rows than the grid
+    if (splits <= 1 || (int64_t)blockIdx.x * kRowsPerBlock >= rows) return;
+  } else {
+    rows = (int64_t)p.total_q * p.n_q_heads;
+    splits = p.num_splits;
+  }
+  const int64_t lrow = (int64_t)blockIdx.x * kRowsPerBlock + wave / kWpr;
+  const int64_t orow = row0 + lrow, prow = part0 + lrow;
+  const bool valid = lrow < rows;
+  const int S = valid ? splits : 0, dv = p.d_v;
   const int e0 = 2 * lane;
-  const const_floats pm = (const_floats)p.part_m + orow;
-  const const_floats pl = (const_floats)p.part_l + orow;
+  const const_floats pm = (const_floats)p.part_m + prow;
+  const const_floats pl = (const_floats)p.part_l + prow;
   float M = -INFINITY, L = 0.f;
   float2 acc[kChunks];
 #pragma unroll
@@ -863,7 +878,7 @@ __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
       const int si = s0 + i * kWpr, sc = min(si, S - 1);   // past the last: reread it, weight 0
       mb[i] = pm[(int64_t)sc * rows];
       lb[i] = pl[(int64_t)sc * rows];
-      const float *po = p.part_o + ((int64_t)sc * rows + orow) * dv;
+      const float *po = p.part_o + ((int64_t)sc * rows + prow) * dv;
 #pragma unroll
       for (int c = 0; c < kChunks; ++c) {
         const int e = 128 * c + e0;
@@ -1314,12 +1329,12 @@ hipError_t launch_link_valu(const LinkParams &p, int dtype, int mla, hipStream_t
   return mla ? launch_valu_t<uint16_t, true>(p, st) : launch_valu_t<uint16_t, false>(p, st);
 }
 
-hipError_t launch_combine(const LinkParams &p, int dtype, hipStream_t st) {
-  const int64_t rows = (int64_t)p.total_q * p.n_q_heads;
+hipError_t launch_combine(const LinkParams &p, int dtype, int32_t max_rows, hipStream_t st) {
+  const int64_t rows = p.comb ? max_rows : (int64_t)p.total_q * p.n_q_heads;
   if (rows == 0) return hipSuccess;
   // as many waves per row as leave each at most one pass, up to four
   const int wpr = p.num_splits <= 4 ? 1 : p.num_splits <= 8 ? 2 : 4;
-  const dim3 grid((unsigned)((rows * wpr + 3) / 4));
+  const dim3 grid((unsigned)((rows * wpr + 3) / 4), p.comb ? (unsigned)p.batch : 1u);
   auto go = [&](auto kc, auto kw) {
     constexpr int kC = decltype(kc)::value, kW = decltype(kw)::value;
     if (dtype == 0)

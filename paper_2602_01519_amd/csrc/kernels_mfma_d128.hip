@@ -111,17 +111,10 @@ struct TileRef {
   int own;           // the tile belongs to the request's own KV (causal mask)
 };
 
-// The link and request tables are read through the constant address space:
-// every lookup is a scalar load and the link cursor lives in scalar
-// registers (no LDS, no barrier).
-typedef __attribute__((address_space(4))) const LinkEntry *const_links;
-typedef __attribute__((address_space(4))) const ReqEntry *const_reqs;
-typedef __attribute__((address_space(4))) const int32_t *const_ints;
-
 struct Ctx {
   ReqEntry R;
   int kvh, wave, lane, n, g;
-  const_links links;           // the request's links
+  const_links links;           // the request's links, from the item's first on
   int li;                      // cursor: current link
   const char *lk, *lv;         // its K / V^T blocks
   int llen, llp, ltile0, lend; // its tokens, padded tokens, first tile, tile after its last
@@ -308,7 +301,7 @@ __device__ __forceinline__ void compute_tile(const Ctx &c, const uint4 *kt, cons
     return ts;
   };
   float ts = probs();
-  if (__any(!(ts <= kJumpSum) || (a.m_used == -INFINITY && ts > 0.f))) {
+  if (__builtin_expect(__any(!(ts <= kJumpSum) || (a.m_used == -INFINITY && ts > 0.f)), 0)) {
     float tmax = -INFINITY;
 #pragma unroll
     for (int x = 0; x < 16; x += 2) {
@@ -358,27 +351,14 @@ __global__ __launch_bounds__(kWaves * 64, 8 / kWaves) void link_mfma_d128_kernel
   c.n = c.lane & 31;
   c.g = c.lane >> 5;
 
-  // XCD-aware work mapping: consecutive blocks go round-robin to the XCDs;
-  // all row blocks of one (request, kv head) land on the same XCD (same L2)
-  // and are dispatched back to back. Heaviest requests first.
-  const int lin = blockIdx.x;
-  const int xcd = lin % p.n_xcd, j = lin / p.n_xcd;
-  const int grp = xcd + p.n_xcd * (j / p.nrb);
-  const int rb = j % p.nrb;
-  const int split = blockIdx.y;
-  if (grp >= p.batch * p.n_kv_heads) return;
-  const int req_i = ((const_ints)p.order)[grp / p.n_kv_heads];
-  c.kvh = grp % p.n_kv_heads;
-  {
-    const_reqs rq = (const_reqs)p.reqs + req_i;
-    c.R.link0 = rq->link0;
-    c.R.nlinks = rq->nlinks;
-    c.R.q0 = rq->q0;
-    c.R.lq = rq->lq;
-    c.R.ls = rq->ls;
-    c.R.doc_tiles = rq->doc_tiles;
-    c.R.tiles = rq->tiles;
-  }
+  // Items with the most work first; see unit_of_block.
+  const int units = p.n_items * p.n_kv_heads;
+  const UnitBlock ub = unit_of_block(blockIdx.x, p.nrb, p.n_xcd, p.spread, units);
+  const int rb = ub.rb;
+  if (ub.u >= units) return;
+  const WorkItem it = load_item(p.items, ub.u / p.n_kv_heads);
+  c.kvh = ub.u % p.n_kv_heads;
+  c.R = item_request(it);
   const ReqEntry &R = c.R;
   const int group = p.group;
   const int nrows = R.lq * group;
@@ -387,8 +367,7 @@ __global__ __launch_bounds__(kWaves * 64, 8 / kWaves) void link_mfma_d128_kernel
   // Own tiles past the causal limit of the block's last row hold no key any
   // of its rows sees: the block's key range ends at the last visible one.
   const int vis = visible_tiles(R, min(nrows - 1, row0 + kRows - 1) / group);
-  const int t_begin = (int)((int64_t)vis * split / p.num_splits);
-  const int t_end = (int)((int64_t)vis * (split + 1) / p.num_splits);
+  const int t_begin = it.t_begin, t_end = min(it.t_end, vis);
 
   // This lane's row. A wave whose 32 rows are all past the request's rows
   // (short questions: a 16-token question fills 64 of the 256 rows) only
@@ -422,11 +401,15 @@ __global__ __launch_bounds__(kWaves * 64, 8 / kWaves) void link_mfma_d128_kernel
     c.voff[u] = (uint32_t)((cc >> 2) * kD * kPanel * 2 + dv * kPanel * 2 + (cc & 3) * 16);
   }
 
-  c.links = (const_links)p.links + c.R.link0;
+  c.links = (const_links)p.links + it.link;
   c.li = 0;
-  c.lk = c.lv = nullptr;
-  c.llen = c.llp = c.ltile0 = c.lend = 0;
-  if (c.R.nlinks > 0) cursor_load(c);
+  c.lk = (const char *)it.k;
+  c.lv = (const char *)it.v;
+  c.llen = it.len;
+  c.llp = it.lp;
+  c.ltile0 = it.tile0;
+  c.ltok0 = it.tok0;
+  c.lend = it.tile0 + (it.len + kTile - 1) / kTile;
 
   // masking facts of the tile held in each buffer pair
   TileRef ref0{}, ref1{}, ref2{};
@@ -534,8 +517,7 @@ __global__ __launch_bounds__(kWaves * 64, 8 / kWaves) void link_mfma_d128_kernel
   // ---- epilogue: O^T[dv][row] with dv = d*32 + (x>>2)*8 + g*4 + (x&3)
   const float ltot = half_swap_sum(a.lsum);
   if (!rvalid) return;
-  const int total_rows = p.total_q * p.n_q_heads;
-  if (p.num_splits == 1) {
+  if (it.part < 0) {
     const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
     uint16_t *out = (uint16_t *)p.out + orow * kD;
 #pragma unroll
@@ -551,7 +533,7 @@ __global__ __launch_bounds__(kWaves * 64, 8 / kWaves) void link_mfma_d128_kernel
     if (p.lse && c.g == 0)
       p.lse[orow] = ltot > 0.f ? (a.m_used + log2f(ltot)) * 0.69314718055994531f : -INFINITY;
   } else {
-    const int64_t prow = (int64_t)split * total_rows + orow;
+    const int64_t prow = it.part + (orow - (int64_t)R.q0 * p.n_q_heads);
     float *po = p.part_o + prow * kD;
 #pragma unroll
     for (int d = 0; d < 4; ++d)
@@ -575,7 +557,8 @@ int mfma_d128_blocks_per_cu() { return 8 / kWaves; }
 
 hipError_t launch_link_mfma_d128(const LinkParams &p, hipStream_t st, const char **name) {
   *name = "link_mfma_d128_kernel";
-  dim3 grid(p.n_groups * p.nrb, p.num_splits);
+  const int64_t units = (int64_t)p.n_items * p.n_kv_heads;
+  const dim3 grid((unsigned)unit_blocks(units, p.nrb, p.n_xcd, p.spread));
   // Calls in which no (request, kv head) fills a workgroup's rows (short
   // questions: few busy waves, short tiles) are bound by the latency of the
   // tile copies and get the three-stage loop; the others the two-stage one.

@@ -108,15 +108,9 @@ struct TileRef {
   int tok;          // first key's row within the request's linked rows (document tiles)
 };
 
-// Walks a request's links in order. The tables are read through the
-// constant address space, so every lookup is a scalar load and the cursor
-// lives in scalar registers (no LDS, no barrier).
-typedef __attribute__((address_space(4))) const LinkEntry *const_links;
-typedef __attribute__((address_space(4))) const ReqEntry *const_reqs;
-typedef __attribute__((address_space(4))) const int32_t *const_ints;
-
+// Walks a request's links in order, from an item's first one on.
 struct Cursor {
-  const_links links;     // this request's links
+  const_links links;     // the request's links
   int li;                // current link
   const char *k;         // its first latent row
   int len, tile0, end;   // its tokens, first tile and the tile after its last
@@ -188,35 +182,23 @@ __global__ __launch_bounds__(256, 1) void link_mla_kernel(LinkParams p) {
   const int n = lane & 31, g = lane >> 5;
   const int rb_s = wave >> 1, kb_s = wave & 1;      // this wave's score tile
 
-  // Blocks are dealt to the XCDs round-robin; give each XCD a contiguous
-  // run of row blocks so the row blocks of one request share an L2.
-  int b = blockIdx.x;
-  if (gridDim.x % p.n_xcd == 0)
-    b = (b % p.n_xcd) * (gridDim.x / p.n_xcd) + b / p.n_xcd;
+  // Workgroups go round-robin to the XCDs. Runs of p.gang consecutive (item,
+  // row block) pairs share an XCD, so that the row blocks of one request walk
+  // the same rows at the same time through one L2 (see launch_link_mla).
   const int nrb = p.nrb;
-  const int grp = b / nrb, rblk = b % nrb;
-  const int split = blockIdx.y;
-  if (grp >= p.batch) return;
-  ReqEntry R;
-  {
-    const int ri = ((const_ints)p.order)[grp];
-    const_reqs rq = (const_reqs)p.reqs + ri;
-    R.link0 = rq->link0;
-    R.nlinks = rq->nlinks;
-    R.q0 = rq->q0;
-    R.lq = rq->lq;
-    R.ls = rq->ls;
-    R.doc_tiles = rq->doc_tiles;
-    R.tiles = rq->tiles;
-  }
+  const int xcd = blockIdx.x % p.n_xcd, j = blockIdx.x / p.n_xcd;
+  const int b = ((j / p.gang) * p.n_xcd + xcd) * p.gang + j % p.gang;
+  const int rblk = b % nrb;
+  if (b / nrb >= p.n_items) return;
+  const WorkItem it = load_item(p.items, b / nrb);
+  const ReqEntry R = item_request(it);
   const int group = p.group;           // query heads (one latent kv head)
   const int nrows = R.lq * group;
   const int row0 = rblk * kRowsMla;
   if (row0 >= nrows) return;
   // the block's key range ends at the last own key its last row sees
   const int vis = visible_tiles(R, min(nrows - 1, row0 + kRowsMla - 1) / group);
-  const int t_begin = (int)((int64_t)vis * split / p.num_splits);
-  const int t_end = (int)((int64_t)vis * (split + 1) / p.num_splits);
+  const int t_begin = it.t_begin, t_end = min(it.t_end, vis);
 
   // Rows: this lane's row in block rb is row0 + 32 rb + n.
   int lim[2];
@@ -248,11 +230,13 @@ __global__ __launch_bounds__(256, 1) void link_mla_kernel(LinkParams p) {
                                        16 * ((tid & 7) ^ ((tid >> 4) & 7)));
 
   Cursor cur;
-  cur.links = (const_links)p.links + R.link0;
+  cur.links = (const_links)p.links + it.link;
   cur.li = 0;
-  cur.k = nullptr;
-  cur.len = cur.tile0 = cur.end = 0;
-  if (R.nlinks > 0) cursor_load(cur);
+  cur.k = (const char *)it.k;
+  cur.len = it.len;
+  cur.tile0 = it.tile0;
+  cur.tok0 = it.tok0;
+  cur.end = it.tile0 + (it.len + kTile - 1) / kTile;
 
   // The first tile is copied up front; every later one during its
   // predecessor's score loop (the last tile re-copies itself into the idle
@@ -485,11 +469,10 @@ __global__ __launch_bounds__(256, 1) void link_mla_kernel(LinkParams p) {
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) ltot[rb] = sm.xm[2 * rb][n] + sm.xm[2 * rb + 1][n];
 
-  const int total_rows = p.total_q * p.n_q_heads;
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
     if (!rvalid[rb]) continue;
-    if (p.num_splits == 1) {
+    if (it.part < 0) {
       const float inv = ltot[rb] > 0.f ? 1.f / ltot[rb] : 0.f;
       uint16_t *out = (uint16_t *)p.out + orow[rb] * kDV;
 #pragma unroll
@@ -506,7 +489,7 @@ __global__ __launch_bounds__(256, 1) void link_mla_kernel(LinkParams p) {
         p.lse[orow[rb]] =
             ltot[rb] > 0.f ? (m_used[rb] + log2f(ltot[rb])) * 0.69314718055994531f : -INFINITY;
     } else {
-      const int64_t prow = (int64_t)split * total_rows + orow[rb];
+      const int64_t prow = it.part + (orow[rb] - (int64_t)R.q0 * p.n_q_heads);
       float *po = p.part_o + prow * kDV;
 #pragma unroll
       for (int db = 0; db < 4; ++db)
@@ -528,9 +511,18 @@ __global__ __launch_bounds__(256, 1) void link_mla_kernel(LinkParams p) {
 
 int mla_rows_per_block() { return kRowsMla; }
 
-hipError_t launch_link_mla(const LinkParams &p, hipStream_t st, const char **name) {
+hipError_t launch_link_mla(LinkParams p, hipStream_t st, const char **name) {
   *name = "link_mla_kernel";
-  dim3 grid(p.batch * p.nrb, p.num_splits);
+  // A batch of like requests (p.even) gives each XCD one contiguous eighth of
+  // all row blocks, whole requests where it can. With uneven requests the
+  // heaviest ones would fall to one XCD; runs of 32 row blocks, what an
+  // XCD's CUs hold at once, are dealt round-robin instead (20 ragged requests
+  // of 2..51 tokens over 3..16 links: 142 -> 130 us; 8 like requests of 256
+  // tokens over 12 links of 512: 409 us contiguous, 413 in runs).
+  const int64_t blocks = (int64_t)p.n_items * p.nrb;
+  p.gang = p.even && blocks % p.n_xcd == 0 ? (int32_t)(blocks / p.n_xcd) : 32;
+  const int64_t per_round = (int64_t)p.gang * p.n_xcd;
+  const dim3 grid((unsigned)((blocks + per_round - 1) / per_round * per_round));
   if (p.doc_lim)
     hipLaunchKernelGGL(link_mla_kernel<true>, grid, dim3(256), 0, st, p);
   else

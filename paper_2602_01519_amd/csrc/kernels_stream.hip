@@ -33,9 +33,7 @@
 // parts of one key range. Calls with many rows take kpar = 1: the four waves
 // walk the same tiles, which one of them brings into the CU's cache. Calls
 // with few rows split the keys over the waves too and merge the (m, l, O) of
-// the parts through LDS at the end. Workgroups that share keys (the row
-// blocks of one request, kv head and key split) run on one XCD, whose L2
-// then serves the repeated reads.
+// the parts through LDS at the end.
 //
 // What bounds it: fp32, the matrix cores (157 TFLOP/s; the exponentials are
 // a fiftieth of the matrix cycles); bf16 at D = 64, the vector ALU (about 36
@@ -104,7 +102,6 @@ struct TileInfo {
 
 // Link and request tables are read through the constant address space: the
 // cursor over the links lives in scalar registers.
-typedef __attribute__((address_space(4))) const LinkEntry *const_links;
 typedef __attribute__((address_space(4))) const ReqEntry *const_reqs;
 typedef __attribute__((address_space(4))) const int32_t *const_ints;
 
@@ -116,30 +113,26 @@ struct Cursor {
   int kvh, doc_tiles;              // doc_tiles: in 32-key tiles
 };
 
+__device__ __forceinline__ void cursor_set(Cursor &c, const void *k, const void *v, int len, int lp,
+                                           int tile0, int tok0) {
+  c.k = (const char *)k;
+  c.v = (const char *)v;
+  c.len = len;
+  c.lp = lp;
+  c.tile0 = tile0 * (kTile / kT);
+  c.tok0 = tok0;
+  c.end = c.tile0 + (len + kTile - 1) / kTile * (kTile / kT);
+}
 __device__ __forceinline__ void cursor_load(Cursor &c) {
-  c.k = (const char *)c.links[c.li].k;
-  c.v = (const char *)c.links[c.li].v;
-  c.len = c.links[c.li].len;
-  c.lp = c.links[c.li].lp;
-  c.tile0 = c.links[c.li].tile0 * (kTile / kT);
-  c.tok0 = c.links[c.li].tok0;
-  c.end = c.tile0 + (c.len + kTile - 1) / kTile * (kTile / kT);
+  cursor_set(c, c.links[c.li].k, c.links[c.li].v, c.links[c.li].len, c.links[c.li].lp,
+             c.links[c.li].tile0, c.links[c.li].tok0);
 }
 
-// Puts the cursor on the link that holds tile t: the lanes read the first
-// tiles of up to 64 links at once (one memory round trip, where a walk from
-// the first link takes one per link).
-__device__ __forceinline__ void cursor_seek(Cursor &c, int nlinks, int t, int lane) {
-  int li = 0;
-  for (int base = 0; base < nlinks; base += 64) {
-    const int i = base + lane;
-    const bool before = i < nlinks && c.links[min(i, nlinks - 1)].tile0 * (kTile / kT) <= t;
-    const int n = __popcll(__ballot(before));
-    if (n > 0) li = base + n - 1;
-    if (n < 64) break;
-  }
-  c.li = uni(li);
-  cursor_load(c);
+// The link of a small call's request that holds its 64-key tile t: the lanes
+// read the first tiles of all its links at once (kSmallLinks <= 64).
+__device__ __forceinline__ int seek_link(const_links links, int nlinks, int t, int lane) {
+  const bool before = lane < nlinks && links[min(lane, nlinks - 1)].tile0 <= t;
+  return uni(max(0, __popcll(__ballot(before)) - 1));
 }
 
 // Tile t of the request (t only grows).
@@ -288,7 +281,7 @@ __device__ __forceinline__ void compute_tile(const Tile<T, D> &x, const TileInfo
                     fmaxf(fmaxf(s[c][1][0], s[c][1][1]), fmaxf(s[c][1][2], s[c][1][3])));
     jump |= !(__builtin_fmaf(tmax[c], sc, -st.m[c]) <= kJump) && tmax[c] != -INFINITY;
   }
-  if (__any(jump)) {
+  if (__builtin_expect(__any(jump), 0)) {
 #pragma unroll
     for (int c = 0; c < CB; ++c) {
       const float mnew = fmaxf(st.m[c], col_max(tmax[c]) * sc);
@@ -320,14 +313,27 @@ __device__ __forceinline__ void compute_tile(const Tile<T, D> &x, const TileInfo
             st.o[c][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(unit(x.v[b][u], i), p[u][i],
                                                               st.o[c][b], 0, 0, 0);
     } else {
+      // hi: p rounded to bf16; lo: the rest, p - hi (one dot product each:
+      // bf16 products are exact), rounded to bf16
       bf16x8 hi, lo;
+      // (-1, 0) and (0, -1), kept in scalar registers: the compiler writes
+      // (-1, 0) as the inline constant -1.0, which the instruction reads as
+      // the fp32 pattern, that is (0, -1)
+      uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;
+      asm("" : "+s"(c0), "+s"(c1));
+      const bf16x2 first = __builtin_bit_cast(bf16x2, c0), second = __builtin_bit_cast(bf16x2, c1);
 #pragma unroll
       for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const __bf16 h = (__bf16)p[b][i];
-          hi[4 * b + i] = h;
-          lo[4 * b + i] = (__bf16)(p[b][i] - (float)h);
+        for (int i = 0; i < 4; i += 2) {
+          const bf16x2 h = __builtin_convertvector((f32x2){p[b][i], p[b][i + 1]}, bf16x2);
+          const f32x2 rest = {__builtin_amdgcn_fdot2_f32_bf16(h, first, p[b][i], false),
+                              __builtin_amdgcn_fdot2_f32_bf16(h, second, p[b][i + 1], false)};
+          const bf16x2 l = __builtin_convertvector(rest, bf16x2);
+          hi[4 * b + i] = h[0];
+          hi[4 * b + i + 1] = h[1];
+          lo[4 * b + i] = l[0];
+          lo[4 * b + i + 1] = l[1];
         }
 #pragma unroll
       for (int b = 0; b < S::NB; ++b) {
@@ -368,16 +374,16 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
   const int wave = uni(threadIdx.x >> 6);
   const int lr = lane & 15, lg = lane >> 4;
 
-  // XCD-aware mapping (consecutive workgroups go round-robin to the XCDs):
-  // the row blocks of one (request, kv head, key split) share an XCD.
-  const int xcd = blockIdx.x % p.n_xcd, j = blockIdx.x / p.n_xcd;
-  const int u = xcd + p.n_xcd * (j / p.nrb), rb = j % p.nrb;
-  const int n_grp = p.batch * p.n_kv_heads;
-  if (u >= n_grp * p.num_splits) return;
-  const int grp = u / p.num_splits, split = u % p.num_splits;
-  const int kvh = grp % p.n_kv_heads;
-  ReqEntry R;
-  {
+  const int units = p.n_kv_heads * (kSmall ? p.batch * p.num_splits : p.n_items);
+  const UnitBlock ub = unit_of_block(blockIdx.x, p.nrb, p.n_xcd, p.spread, units);
+  const int rb = ub.rb;
+  if (ub.u >= units) return;
+  int kvh, part_row = -1, p_begin = 0, p_end = 0;   // the piece, in 32-key tiles
+  ReqEntry R{};
+  Cursor cur;
+  if constexpr (kSmall) {
+    const int grp = ub.u / p.num_splits, split = ub.u % p.num_splits;
+    kvh = grp % p.n_kv_heads;
     const_reqs rq = reqs + order[grp / p.n_kv_heads];
     R.link0 = rq->link0;
     R.nlinks = rq->nlinks;
@@ -387,6 +393,20 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
     R.ls = rq->ls;
     R.doc_tiles = rq->doc_tiles;
     R.tiles = rq->tiles;
+    p_begin = (int)((int64_t)2 * R.tiles * split / p.num_splits);
+    p_end = (int)((int64_t)2 * R.tiles * (split + 1) / p.num_splits);
+    if (p.num_splits > 1) part_row = (split * p.total_q + R.q0) * p.n_q_heads;
+    cur.links = links + R.link0;
+  } else {
+    const WorkItem it = load_item(p.items, ub.u / p.n_kv_heads);
+    kvh = ub.u % p.n_kv_heads;
+    R = item_request(it);
+    p_begin = it.t_begin;
+    p_end = it.t_end;
+    part_row = it.part;
+    cur.links = links + it.link;
+    cur.li = 0;
+    cursor_set(cur, it.k, it.v, it.len, it.lp, it.tile0, it.tok0);
   }
   const int group = p.group, kpar = p.kpar;
   const int nrows = R.lq * group;
@@ -395,16 +415,16 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
   const int row0 = wg_row0 + (wave / kpar) * kR;
   const bool active = row0 < nrows;
 
-  // 32-key tiles up to the last own key the wave's last row sees, cut into
-  // num_splits x kpar parts
+  // the piece's tiles up to the last own key the wave's last row sees, cut
+  // into kpar parts
   int t_begin = 0, t_end = 0;
   if (active) {
     const int own_last = min(nrows - 1, row0 + kR - 1) / group + R.ls - R.lq;
     const int vis = own_last >= 0 ? min(2 * R.tiles, 2 * R.doc_tiles + own_last / kT + 1)
                                   : 2 * R.doc_tiles;
-    const int part = split * kpar + wave % kpar, parts = p.num_splits * kpar;
-    t_begin = (int)((int64_t)vis * part / parts);
-    t_end = (int)((int64_t)vis * (part + 1) / parts);
+    const int n = max(0, min(p_end, vis) - p_begin), part = wave % kpar;
+    t_begin = p_begin + n * part / kpar;
+    t_end = p_begin + n * (part + 1) / kpar;
   }
 
   int lim[CB], dl[CB], wmin = kNoLimit;
@@ -429,8 +449,6 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
     wmin = kNoLimit;
   }
 
-  Cursor cur;
-  cur.links = links + R.link0;
   cur.kvh = kvh;
   cur.doc_tiles = 2 * R.doc_tiles;
   const uint32_t koff =
@@ -447,16 +465,19 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
   }
   Tile<T, D> ta, tb;
   TileInfo ia{}, ib{};
-  auto load = [&](int t, TileInfo &i, Tile<T, D> &x) {
+  auto load = [&](int t, bool live, TileInfo &i, Tile<T, D> &x) {
     i = tile_info<T, D>(cur, t);
     if (kSmall && i.own)
       load_own<T, D>(own, i.j0, lr, lg, x);
     else
-      load_tile<T, D>(i, koff, voff, x);
+      load_tile<T, D>(i, kSmall || live ? koff : 0, kSmall || live ? voff : 0, x);
   };
   if (t_begin < t_end) {
-    cursor_seek(cur, R.nlinks, t_begin, lane);
-    load(t_begin, ia, ta);
+    if constexpr (kSmall) {
+      cur.li = seek_link(cur.links, R.nlinks, t_begin / (kTile / kT), lane);
+      cursor_load(cur);
+    }
+    load(t_begin, true, ia, ta);
   }
   uint4 qf[CB][S::KU];
 #pragma unroll
@@ -479,15 +500,18 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
   }
   const float sc = p.scale_log2;
 
+  // The loads past the last tile read one line each of it: a branch around
+  // them makes the compiler wait for every load in flight where the paths
+  // meet (the small form branches anyway, on own tiles).
   for (int t = t_begin; t < t_end; t += 2) {
-    if (t + 1 < t_end) load(t + 1, ib, tb);
+    if (!kSmall || t + 1 < t_end) load(min(t + 1, t_end - 1), t + 1 < t_end, ib, tb);
     compute_tile<T, D, CB>(ta, ia, qf, st, lg, lim, dl, wmin, sc);
     if (t + 1 >= t_end) break;
-    if (t + 2 < t_end) load(t + 2, ia, ta);
+    if (!kSmall || t + 2 < t_end) load(min(t + 2, t_end - 1), t + 2 < t_end, ia, ta);
     compute_tile<T, D, CB>(tb, ib, qf, st, lg, lim, dl, wmin, sc);
   }
 
-  const int64_t total_rows = (int64_t)p.total_q * p.n_q_heads;
+  const int64_t part0 = part_row - (int64_t)R.q0 * p.n_q_heads;   // partial row of output row 0
   float ltot[CB];
 #pragma unroll
   for (int c = 0; c < CB; ++c) ltot[c] = col_sum(st.l[c]);
@@ -496,7 +520,7 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
 #pragma unroll
     for (int c = 0; c < CB; ++c) {
       if (!rvalid[c]) continue;
-      if (p.num_splits == 1) {
+      if (part_row < 0) {
         const float inv = ltot[c] > 0.f ? 1.f / ltot[c] : 0.f;
         T *out = (T *)p.out + orow[c] * D + 4 * lg;
 #pragma unroll
@@ -507,7 +531,7 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
           p.lse[orow[c]] =
               ltot[c] > 0.f ? (st.m[c] + log2f(ltot[c])) * 0.69314718055994531f : -INFINITY;
       } else {
-        const int64_t prow = split * total_rows + orow[c];
+        const int64_t prow = part0 + orow[c];
         float *po = p.part_o + prow * D + 4 * lg;
 #pragma unroll
         for (int b = 0; b < S::NB; ++b)
@@ -555,13 +579,13 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
       a.w += wt * v.w;
     }
     const int64_t orw = (int64_t)(R.q0 + row / group) * p.n_q_heads + kvh * group + row % group;
-    if (p.num_splits == 1) {
+    if (part_row < 0) {
       const float inv = L > 0.f ? 1.f / L : 0.f;
       store4<T>((T *)p.out + orw * D + e, a.x * inv, a.y * inv, a.z * inv, a.w * inv);
       if (p.lse && e == 0)
         p.lse[orw] = L > 0.f ? (M + log2f(L)) * 0.69314718055994531f : -INFINITY;
     } else {
-      const int64_t prow = split * total_rows + orw;
+      const int64_t prow = part0 + orw;
       store4<float>(p.part_o + prow * D + e, a.x, a.y, a.z, a.w);
       if (e == 0) {
         p.part_m[prow] = M;
@@ -578,7 +602,7 @@ constexpr int kMinWaves = D * sizeof(T) > 256 ? 1 : 2;
 
 template <typename T, int D, int CB>
 __global__ __launch_bounds__(64 * kWaves, (kMinWaves<T, D>)) void link_stream_kernel(LinkParams p) {
-  stream_body<T, D, CB, false>(p, (const_links)p.links, (const_reqs)p.reqs, (const_ints)p.order);
+  stream_body<T, D, CB, false>(p, (const_links)p.links, nullptr, nullptr);
 }
 
 // The tables are read where they are, in the kernel arguments.
@@ -617,9 +641,8 @@ hipError_t pick(int dtype, int d, int cb, F f) {
 // column blocks; such calls have little to gain).
 constexpr bool small_built(int esz, int d, int cb) { return cb * d * esz <= 512 && cb <= 2; }
 
-unsigned stream_blocks(const LinkParams &p) {
-  const int64_t units = (int64_t)p.batch * p.n_kv_heads * p.num_splits;
-  return (unsigned)((units + p.n_xcd - 1) / p.n_xcd * p.n_xcd * p.nrb);
+unsigned stream_blocks(const LinkParams &p, int64_t units) {
+  return (unsigned)unit_blocks(units, p.nrb, p.n_xcd, p.spread);
 }
 
 }  // namespace
@@ -652,7 +675,8 @@ hipError_t launch_link_stream(const LinkParams &p, int dtype, int rows, hipStrea
   *name = dtype == 0 ? "link_stream_kernel<float>" : "link_stream_kernel<bf16>";
   return pick(dtype, p.d_k, rows / 16, [&](auto t, auto dc, auto cb) {
     hipLaunchKernelGGL((link_stream_kernel<decltype(t), decltype(dc)::value, decltype(cb)::value>),
-                       dim3(stream_blocks(p)), dim3(64 * kWaves), 0, st, p);
+                       dim3(stream_blocks(p, (int64_t)p.n_items * p.n_kv_heads)),
+                       dim3(64 * kWaves), 0, st, p);
     return hipGetLastError();
   });
 }
@@ -663,7 +687,8 @@ hipError_t launch_link_stream_small(const LinkParams &p, const SmallTabs &tabs, 
   return pick(dtype, p.d_k, rows / 16, [&](auto t, auto dc, auto cb) {
     constexpr int kD = decltype(dc)::value, kCB = decltype(cb)::value;
     if constexpr (small_built(sizeof(t), kD, kCB)) {
-      hipLaunchKernelGGL((link_small_kernel<decltype(t), kD, kCB>), dim3(stream_blocks(p)),
+      hipLaunchKernelGGL((link_small_kernel<decltype(t), kD, kCB>),
+                         dim3(stream_blocks(p, (int64_t)p.batch * p.n_kv_heads * p.num_splits)),
                          dim3(64 * kWaves), 0, st, SmallArgs{p, tabs});
       return hipGetLastError();
     }

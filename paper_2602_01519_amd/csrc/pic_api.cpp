@@ -539,13 +539,6 @@ void place_own(const pic_store *s, const Plan &P, void *work, LinkEntry *links) 
   }
 }
 
-// Writes the plan's tables into a staging slot (host-mapped pinned memory)
-// and points lp's tables at the slot's device copy; the call's prologue
-// kernel moves them there.
-struct TableLayout {
-  size_t off_r, off_o, off_d, bytes;
-};
-
 // Where the prologue reads the tables, and what it copies first.
 struct Prologue {
   const LinkEntry *links = nullptr;
@@ -554,36 +547,6 @@ struct Prologue {
   void *copy_dst = nullptr;
   int64_t copy_bytes = 0;
 };
-
-// The slot also holds the call's workspace (work_bytes), where the own-KV
-// links are pointed.
-pic_status upload(pic_store *s, Plan &P, size_t work_bytes, Stage **stage, LinkParams &lp,
-                  TableLayout &tl) {
-  const size_t nl = P.links.size(), nr = P.reqs.size();
-  tl.off_r = round_up(sizeof(LinkEntry) * nl, 256);
-  tl.off_o = tl.off_r + round_up(sizeof(ReqEntry) * nr, 256);
-  tl.off_d = tl.off_o + round_up(sizeof(int32_t) * nr, 256);
-  tl.bytes = tl.off_d + round_up(sizeof(int32_t) * P.doc_lim.size(), 256);
-  const size_t off_r = tl.off_r, off_o = tl.off_o, bytes = tl.bytes;
-  pic_status rc = stage_acquire(s, bytes, stage);
-  if (rc != PIC_OK) return rc;
-  if (work_bytes > 0) {
-    rc = ensure_work(*stage, work_bytes);
-    if (rc != PIC_OK) return rc;
-  }
-  place_own(s, P, (*stage)->work, P.links.data());
-  char *h = (char *)(*stage)->host;
-  if (nl) memcpy(h, P.links.data(), sizeof(LinkEntry) * nl);
-  memcpy(h + off_r, P.reqs.data(), sizeof(ReqEntry) * nr);
-  memcpy(h + off_o, P.order.data(), sizeof(int32_t) * nr);
-  if (!P.doc_lim.empty()) memcpy(h + tl.off_d, P.doc_lim.data(), sizeof(int32_t) * P.doc_lim.size());
-  char *dv = (char *)(*stage)->dev;
-  lp.links = (const LinkEntry *)dv;
-  lp.reqs = (const ReqEntry *)(dv + off_r);
-  lp.order = (const int32_t *)(dv + off_o);
-  lp.doc_lim = P.doc_lim.empty() ? nullptr : (const int32_t *)(dv + tl.off_d);
-  return PIC_OK;
-}
 
 void prof_start(hipStream_t st, std::pair<hipEvent_t, hipEvent_t> *ev) {
   ev->first = ev->second = nullptr;
@@ -620,15 +583,197 @@ enum class Kern { Valu, Mfma128, Decode128, Mla, Stream };
 struct Setup {
   Plan P;
   Kern kern = Kern::Valu;
-  int32_t splits = 1;
+  int32_t splits = 1;            // most pieces of a request
+  std::vector<int32_t> req_splits;   // pieces per request (kernels that take work items)
+  std::vector<CombineEntry> comb;    // their partial rows (when some request is split)
+  int32_t tile_keys = kTile;     // keys per tile of the kernel's work items
+  int32_t n_items = 0;
   bool lean = false;             // a small call the lean kernel runs
   bool small = false;            // tables as a kernel argument, own KV in place
+  bool own_in_place = false;     // the kernel reads own KV from k_self / v_self
+  int32_t rows_per_block = 0;    // rows of a workgroup (decode kernel: wave)
   int32_t stream_rows = 0;       // stream kernel: rows per wave
   LinkParams lp{};               // shapes only: no tables, tensors or scale yet
   std::vector<OwnArg> own_args;  // per request, for the prologue (batch <= kOwnArgs)
+  int64_t part_rows = 0;         // partial rows of the call
   size_t part_off = 0, part_bytes = 0;
   size_t work_bytes() const { return part_off + part_bytes; }
 };
+
+// Layout of a call's tables: links, requests, request order, per-query
+// limits, work items, combine entries.
+struct TableLayout {
+  size_t off_r, off_o, off_d, off_i, off_c, bytes;
+};
+TableLayout table_layout(const Setup &C) {
+  const size_t nl = C.P.links.size(), nr = C.P.reqs.size();
+  TableLayout t;
+  t.off_r = round_up(sizeof(LinkEntry) * nl, 256);
+  t.off_o = t.off_r + round_up(sizeof(ReqEntry) * nr, 256);
+  t.off_d = t.off_o + round_up(sizeof(int32_t) * nr, 256);
+  t.off_i = t.off_d + round_up(sizeof(int32_t) * C.P.doc_lim.size(), 256);
+  t.off_c = t.off_i + round_up(sizeof(WorkItem) * C.n_items, 256);
+  t.bytes = t.off_c + round_up(sizeof(CombineEntry) * C.comb.size(), 256);
+  return t;
+}
+
+// The call's work items in dispatch order: C.P.order's requests, each one's
+// pieces in key order. links: the call's link table (own-KV links placed).
+void write_items(const Setup &C, const LinkEntry *links, WorkItem *out) {
+  const int per = kTile / C.tile_keys;     // kernel tiles per 64-key tile
+  for (int32_t r : C.P.order) {
+    const ReqEntry &R = C.P.reqs[r];
+    const int64_t S = C.req_splits[r], tiles = (int64_t)R.tiles * per;
+    int32_t li = R.link0;
+    for (int64_t i = 0; i < S; ++i) {
+      WorkItem w{};
+      w.t_begin = (int32_t)(tiles * i / S);
+      w.t_end = (int32_t)(tiles * (i + 1) / S);
+      if (w.t_begin < w.t_end) {
+        while (li + 1 < R.link0 + R.nlinks && links[li + 1].tile0 * per <= w.t_begin) ++li;
+        const LinkEntry &L = links[li];
+        w.k = L.k;
+        w.v = L.v;
+        w.len = L.len;
+        w.lp = L.lp;
+        w.tile0 = L.tile0;
+        w.tok0 = L.tok0;
+      }
+      if (C.own_in_place) w.tok0 = R.s0;   // the decode kernel masks no linked rows
+      w.link = li;
+      w.q0 = R.q0;
+      w.lq = R.lq;
+      w.ls = R.ls;
+      w.doc_tiles = R.doc_tiles;
+      w.part = S > 1 ? (int32_t)(C.comb[r].part0 + i * C.comb[r].rows) : -1;
+      *out++ = w;
+    }
+  }
+}
+
+// Writes the call's tables (host memory, laid out by t) for one layer's
+// links.
+void write_tables(const Setup &C, const TableLayout &t, const LinkEntry *links, char *h) {
+  const Plan &P = C.P;
+  if (!P.links.empty()) memcpy(h, links, sizeof(LinkEntry) * P.links.size());
+  if (!P.reqs.empty()) {
+    memcpy(h + t.off_r, P.reqs.data(), sizeof(ReqEntry) * P.reqs.size());
+    memcpy(h + t.off_o, P.order.data(), sizeof(int32_t) * P.reqs.size());
+  }
+  if (!P.doc_lim.empty())
+    memcpy(h + t.off_d, P.doc_lim.data(), sizeof(int32_t) * P.doc_lim.size());
+  if (C.n_items > 0) write_items(C, links, (WorkItem *)(h + t.off_i));
+  if (!C.comb.empty())
+    memcpy(h + t.off_c, C.comb.data(), sizeof(CombineEntry) * C.comb.size());
+}
+
+// Points lp's tables at their device copy.
+void point_tables(const Setup &C, const TableLayout &t, const char *dev, LinkParams &lp) {
+  lp.links = (const LinkEntry *)dev;
+  lp.reqs = (const ReqEntry *)(dev + t.off_r);
+  lp.order = (const int32_t *)(dev + t.off_o);
+  lp.doc_lim = C.P.doc_lim.empty() ? nullptr : (const int32_t *)(dev + t.off_d);
+  lp.items = C.n_items > 0 ? (const WorkItem *)(dev + t.off_i) : nullptr;
+  lp.comb = C.comb.empty() ? nullptr : (const CombineEntry *)(dev + t.off_c);
+}
+
+// Writes the call's tables into a staging slot (host-mapped pinned memory)
+// and points lp's tables at the slot's device copy; the call's prologue
+// kernel moves them there. The slot also holds the call's workspace, where
+// the own-KV links are pointed.
+pic_status upload(pic_store *s, Setup &C, Stage **stage, LinkParams &lp, TableLayout &tl) {
+  tl = table_layout(C);
+  pic_status rc = stage_acquire(s, tl.bytes, stage);
+  if (rc != PIC_OK) return rc;
+  if (C.work_bytes() > 0) {
+    rc = ensure_work(*stage, C.work_bytes());
+    if (rc != PIC_OK) return rc;
+  }
+  place_own(s, C.P, (*stage)->work, C.P.links.data());
+  write_tables(C, tl, C.P.links.data(), (char *)(*stage)->host);
+  point_tables(C, tl, (const char *)(*stage)->dev, lp);
+  return PIC_OK;
+}
+
+// What a kernel's pieces cost, in its tiles.
+struct SplitCost {
+  int64_t slots;       // workgroups (decode kernel: waves) the GPU holds at once
+  int64_t fit;         // ... that a round is planned with
+  double over;         // a piece's fixed time: start, first loads, epilogue
+  double part;         // writing and merging one partial row
+  double fixed;        // the combine launch
+  int32_t min_piece;   // fewest tiles of a piece
+  int32_t max_splits;
+};
+
+// Pieces per request, so that the call finishes early: candidate piece
+// lengths L are the shortest for which the call's workgroups still fit half,
+// one, two, three or four rounds of the GPU, and the whole request; each
+// costs its longest piece if the workgroups all run at once, else the
+// average work per slot plus 0.3 of the longest piece (in-order dispatch
+// leaves the last pieces uneven), and in both cases the partials its splits
+// write and merge. Requests are cut into equal pieces of at most L tiles, so
+// a ragged batch gets pieces of like length (with one split count for all
+// requests the longest request's pieces set the time: an MLA decode step of
+// 32 requests over 4..14 links took 58 us in 8 pieces each).
+// tiles, blocks, rows: per request its key tiles, its workgroups per piece
+// and its output rows.
+std::vector<int32_t> choose_splits(const std::vector<int32_t> &tiles,
+                                   const std::vector<int32_t> &blocks,
+                                   const std::vector<int64_t> &rows, const SplitCost &c) {
+  const size_t n = tiles.size();
+  // ceil(tiles / L); + 0.5 keeps the product off the integers it is cut at
+  auto pieces = [&](size_t r, int32_t L, double inv) {
+    const int32_t s = (int32_t)((tiles[r] + L - 1 + 0.5) * inv);
+    return std::min(c.max_splits, std::max(1, s));
+  };
+  auto total = [&](int32_t L) {
+    const double inv = 1.0 / L;
+    int64_t t = 0;
+    for (size_t r = 0; r < n; ++r) t += (int64_t)blocks[r] * pieces(r, L, inv);
+    return t;
+  };
+  auto cost = [&](int32_t L) {
+    const double inv = 1.0 / L;
+    double work = 0, longest = 0, part = 0;
+    int64_t wgs = 0;
+    for (size_t r = 0; r < n; ++r) {
+      if (blocks[r] == 0) continue;
+      const int32_t S = pieces(r, L, inv);
+      wgs += (int64_t)blocks[r] * S;
+      work += blocks[r] * (tiles[r] + c.over * S);
+      longest = std::max(longest, (double)((tiles[r] + S - 1) / S) + c.over);
+      if (S > 1) part += c.part * (double)rows[r] * S;
+    }
+    const double run = wgs <= c.slots ? longest
+                                      : std::max(longest, work / (double)c.slots + 0.3 * longest);
+    return run + part + (part > 0 ? c.fixed : 0.0);
+  };
+  int32_t most = 1;
+  for (size_t r = 0; r < n; ++r) most = std::max(most, tiles[r]);
+  int32_t best_L = most;
+  double best = cost(most);
+  for (int k : {1, 2, 4, 6, 8}) {          // half rounds
+    const int64_t limit = c.fit * k / 2;
+    if (total(most) > limit) continue;
+    int32_t lo = std::min(c.min_piece, most), hi = most;   // shortest L that fits
+    while (lo < hi) {
+      const int32_t mid = (lo + hi) / 2;
+      if (total(mid) <= limit)
+        hi = mid;
+      else
+        lo = mid + 1;
+    }
+    const double t = cost(lo);
+    if (t < best) {
+      best = t;
+      best_L = lo;
+    }
+  }
+  std::vector<int32_t> S(n);
+  for (size_t r = 0; r < n; ++r) S[r] = pieces(r, best_L, 1.0 / best_L);
+  return S;
+}
 
 // Request order for the d128 prefill kernel. Workgroup j of XCD x runs row
 // block j % nrb of group x + n_xcd (j / nrb) (see the kernel's work
@@ -736,6 +881,135 @@ bool small_tables(const Plan &P) {
 // more than the prologue saves once there are several.
 constexpr int kStreamSmallRows = 128;
 
+// Most own tokens of a request whose own KV the decode kernel reads in place
+// (2-byte gathers of the token-major values, once per kv head) instead of
+// having the prologue lay it out; a plan's runs then need no prologue.
+constexpr int32_t kOwnInPlace = 128;
+
+// Costs of a kernel's pieces in its tiles (see choose_splits). Tile times on
+// a full GPU: d128 1.75 us per workgroup (64 keys), MLA 2.0 us (64 keys),
+// decode 5 us per wave (32 keys, eight waves per CU on the HBM stream),
+// stream kernel below. Partials move at about 4 TB/s, written and read; a
+// combine launch is about 4.5 us.
+SplitCost split_cost(Kern kern, int32_t cus, const pic_store_desc &d, int32_t max_rows,
+                     const StreamShape &ss) {
+  const double part_us = (d.d_v + 2) * 8.0 / 4e6;
+  SplitCost c{};
+  c.max_splits = 256;
+  double us = 1;
+  if (kern == Kern::Mfma128) {
+    us = 1.75;
+    c.slots = (int64_t)cus * mfma_d128_blocks_per_cu();
+    c.over = 3;
+    // a piece reads more keys and values than the partials it writes and the
+    // combine reads back
+    const int64_t part = 2 * (int64_t)std::min(max_rows, mfma_d128_rows_per_block()) * (d.d_v + 2) * 4;
+    const int64_t tile = (int64_t)kTile * (d.d_k + d.d_v) * 2;
+    c.min_piece = (int32_t)std::max<int64_t>(1, std::min<int64_t>(8, part / tile));
+  } else if (kern == Kern::Mla) {
+    us = 2.0;
+    c.slots = cus;
+    c.over = 4;
+    c.min_piece = 2;
+  } else if (kern == Kern::Decode128) {
+    us = 5.0;
+    c.slots = 8 * (int64_t)cus;
+    c.over = 2;
+    c.min_piece = 1;
+  } else {
+    // two workgroups per CU; fp32: a 32-key tile is D/16 x 16 matrix
+    // instructions of 32 cycles per 16 rows and wave; bf16: 36 cycles per
+    // score and lane; the waves of a workgroup share a tile kpar ways
+    const double cyc = d.dtype == PIC_F32 ? 32.0 * d.d_k * ss.rows / 16 : 22.0 * ss.rows;
+    us = 2 * cyc / 2200.0 / ss.kpar;
+    c.slots = 2 * (int64_t)cus;
+    // a round planned full to the last place runs over on some XCD, as row
+    // blocks of ragged requests stay empty (8 requests of 30..300 tokens,
+    // 32/8 heads x 64: 176 us full, 148 us with a twentieth left free)
+    c.fit = c.slots * 19 / 20;
+    c.over = 6.0 / us;
+    c.min_piece = 2 * ss.kpar;
+  }
+  if (c.fit == 0) c.fit = c.slots;
+  c.part = part_us / us;
+  c.fixed = 4.5 / us;
+  return c;
+}
+
+// Completes a call of work items from its pieces per request (C.req_splits):
+// item counts, partial rows, request order, workspace layout.
+void apply_splits(pic_store *s, int32_t n_q_heads, int rows_per_block, Setup &C) {
+  Plan &P = C.P;
+  LinkParams &lp = C.lp;
+  const int B = (int)P.reqs.size();
+  C.n_items = 0;
+  C.splits = 1;
+  lp.even = 1;
+  for (int r = 0; r < B; ++r) {
+    if (P.reqs[r].lq == 0) C.req_splits[r] = 1;
+    C.n_items += C.req_splits[r];
+    C.splits = std::max(C.splits, C.req_splits[r]);
+    if (P.reqs[r].tiles != P.reqs[0].tiles || P.reqs[r].lq != P.reqs[0].lq) lp.even = 0;
+  }
+  lp.n_items = C.n_items;
+  lp.num_splits = C.splits;
+  lp.spread = C.kern == Kern::Stream ||
+              spread_units((int64_t)C.n_items * lp.n_kv_heads, lp.nrb, lp.n_xcd);
+  C.part_rows = 0;
+  C.comb.clear();
+  if (C.splits > 1) {
+    C.comb.resize(B);
+    for (int r = 0; r < B; ++r) {
+      const int32_t S = C.req_splits[r], rows = P.reqs[r].lq * n_q_heads;
+      C.comb[r] = CombineEntry{P.reqs[r].q0 * n_q_heads, rows, (int32_t)C.part_rows, S};
+      if (S > 1) C.part_rows += (int64_t)rows * S;
+    }
+    // longest pieces first
+    std::stable_sort(P.order.begin(), P.order.end(), [&](int32_t a, int32_t b) {
+      return (int64_t)P.reqs[a].tiles * C.req_splits[b] > (int64_t)P.reqs[b].tiles * C.req_splits[a];
+    });
+  } else if (C.kern == Kern::Mfma128 && !lp.spread) {
+    balance_order_d128(s, P, lp, rows_per_block,
+                       s->shape.cus / s->shape.xcds * mfma_d128_blocks_per_cu());
+  }
+  if (C.kern == Kern::Decode128) {
+    int32_t own = 0;
+    for (const ReqEntry &R : P.reqs) own = std::max(own, R.ls);
+    C.own_in_place = own > 0 && own <= kOwnInPlace;
+    lp.own_in_place = C.own_in_place;
+    if (C.own_in_place) P.max_own_lp = 0;      // nothing to lay out
+  }
+  C.part_off = C.own_in_place ? 0 : round_up(P.own_bytes, 256);
+  C.part_bytes = (size_t)C.part_rows * (s->desc.d_v + 2) * sizeof(float);
+}
+
+// Bytes of static scratch a pic_link_decode_noalloc call is charged for (its
+// limit, stated in pic.h): tables, the own KV laid out, and partials of one
+// split count for all requests, num_splits or, for 0, the one that gives
+// about eight workgroups (decode kernel: waves) per CU, of 256 rows (d128),
+// 64 (MLA) or 16 (others).
+size_t noalloc_charge(const pic_store *s, const Setup &C, int32_t num_splits) {
+  const Plan &P = C.P;
+  const pic_store_desc &d = s->desc;
+  const int block = C.kern == Kern::Mfma128 ? mfma_d128_rows_per_block()
+                    : C.kern == Kern::Mla   ? mla_rows_per_block()
+                                            : 16;
+  int64_t splits = num_splits;
+  if (splits == 0) {
+    const int64_t blocks = (int64_t)P.reqs.size() * d.n_kv_heads *
+                           std::max(1, (P.max_rows + block - 1) / block);
+    splits = std::max<int64_t>(
+        1, std::min<int64_t>((8 * (int64_t)s->shape.cus + blocks - 1) / blocks, 256));
+    splits = std::min<int64_t>(splits, std::max(1, P.max_tiles));
+  }
+  const size_t part = splits > 1 ? (size_t)P.total_q * C.lp.n_q_heads * splits * (d.d_v + 2) * 4 : 0;
+  if ((C.kern == Kern::Valu || C.kern == Kern::Stream) && small_tables(P)) return part;
+  return round_up(sizeof(LinkEntry) * P.links.size(), 256) +
+         round_up(sizeof(ReqEntry) * P.reqs.size(), 256) +
+         round_up(sizeof(int32_t) * P.reqs.size(), 256) +
+         round_up(sizeof(int32_t) * P.doc_lim.size(), 256) + round_up(P.own_bytes, 256) + part;
+}
+
 pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, float scale,
                       int32_t layer, int32_t num_splits, Mode mode, Setup &C) {
   if (mode == Mode::Decode && (num_splits < 0 || num_splits > 256))
@@ -793,7 +1067,8 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     if (!C.lean && stream_supported(d.dtype, d.d_k, d.d_v)) kern = Kern::Stream;
   }
   C.small = small_tables(P) &&
-            (kern == Kern::Valu || (kern == Kern::Stream && P.max_rows <= kStreamSmallRows));
+            (kern == Kern::Valu || (kern == Kern::Stream && (mode == Mode::Decode ||
+                                                             P.max_rows <= kStreamSmallRows)));
   if (kern == Kern::Valu && valu_lds_bytes_for(s->esz, mla, d.d_k, d.d_v) > 160 * 1024)
     return fail(PIC_ERR_UNSUPPORTED, "head widths d_k=%d d_v=%d exceed the generic kernel's LDS",
                 d.d_k, d.d_v);
@@ -807,11 +1082,32 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
                              : kern == Kern::Valu  ? valu_rows_per_block()
                              : kern == Kern::Mla   ? mla_rows_per_block()
                                                    : decode_d128_max_rows();
+  C.rows_per_block = rows_per_block;
   lp.nrb = std::max(1, (P.max_rows + rows_per_block - 1) / rows_per_block);
   lp.max_rows = P.max_rows;
   lp.n_groups = req->batch * d.n_kv_heads;
   lp.n_xcd = s->shape.xcds;
-  if (kern == Kern::Mfma128) lp.n_groups = (int32_t)round_up(lp.n_groups, lp.n_xcd);
+
+  const bool by_items = kern != Kern::Valu && !C.small;
+  if (by_items) {
+    C.tile_keys = kern == Kern::Decode128 || kern == Kern::Stream ? 32 : kTile;
+    const int B = req->batch;
+    std::vector<int32_t> tiles(B), blocks(B);
+    std::vector<int64_t> rows(B);
+    for (int r = 0; r < B; ++r) {
+      const ReqEntry &R = P.reqs[r];
+      tiles[r] = R.tiles * (kTile / C.tile_keys);
+      blocks[r] = d.n_kv_heads * ((R.lq * lp.group + rows_per_block - 1) / rows_per_block);
+      rows[r] = (int64_t)R.lq * n_q_heads;
+    }
+    if (mode == Mode::Decode && num_splits > 0)
+      C.req_splits.assign(B, num_splits);
+    else
+      C.req_splits = choose_splits(tiles, blocks, rows,
+                                   split_cost(kern, s->shape.cus, d, P.max_rows, ss));
+    apply_splits(s, n_q_heads, rows_per_block, C);
+    return PIC_OK;
+  }
 
   int32_t splits = 1;
   const int64_t blocks = (int64_t)req->batch * d.n_kv_heads * lp.nrb;
@@ -819,61 +1115,34 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     if (num_splits > 0) {
       splits = num_splits;
     } else {
-      // about 8 work items per CU (one wave each for the decode kernel, a
-      // workgroup each otherwise), never more splits than tiles
+      // workgroups for eight rounds of the CUs (stream kernel: two per CU),
+      // never more splits than tiles
       const int64_t items = (kern == Kern::Stream ? 2 : 8) * (int64_t)s->shape.cus;
       splits = (int32_t)std::max<int64_t>(1, std::min<int64_t>((items + blocks - 1) / blocks, 256));
       splits = std::min(splits, std::max(1, P.max_tiles));
     }
   } else {
-    // Few row blocks per call -- short queries over long documents (the
-    // regime the paper targets: a few dozen dynamic tokens after thousands
-    // of cached ones), or a single small request -- leave most CUs idle and
-    // let the longest request set the kernel time. Split every request's
-    // key range so that its longest piece is no longer than the average work
-    // per resident workgroup of the GPU (its CUs times the kernel's
-    // workgroups per CU), with a minimum piece (8 tiles for the MLA kernel,
-    // 1 for the vector-ALU kernel, whose tiles are slow) and at most 16
-    // pieces. A piece of the d=128 matrix-core kernel only has to read more
-    // keys and values than the partial results it writes and the merge
-    // reads back (2 x rows x (d_v + 2) fp32), at most 8 tiles; and a d=128
-    // call whose row blocks fill at most half the GPU takes as many pieces
-    // as one round of workgroups holds, up to 32 (a single short request,
-    // 4 links of 512 tokens and 16 questions: 15 -> 10 us), but no more: the
-    // pieces of a second round cost more than they save (8 ragged requests
-    // x 2 kv heads: 16 pieces 28 us, 19 pieces 41 us). Its partials then
-    // stay below 256 x 256 rows x (d_v + 2) fp32 (34 MB).
-    const int64_t per_cu =
-        kern == Kern::Mla       ? 1
-        : kern == Kern::Mfma128 ? mfma_d128_blocks_per_cu()
-        : kern == Kern::Stream  ? 2
-                                : 4;
-    const int64_t slots = (int64_t)s->shape.cus * per_cu;
-    int min_piece = kern == Kern::Valu ? 1 : kern == Kern::Stream ? 2 * ss.kpar : 8;
-    int64_t max_splits = 16;
-    if (kern == Kern::Mfma128) {
-      const int64_t part = 2 * (int64_t)std::min(P.max_rows, rows_per_block) * (d.d_v + 2) * 4;
-      const int64_t tile = (int64_t)kTile * (d.d_k + d.d_v) * s->esz;
-      min_piece = (int)std::max<int64_t>(1, std::min<int64_t>(8, part / tile));
-      if (2 * blocks <= slots) max_splits = std::min<int64_t>(32, slots / blocks);
-    }
+    // Vector-ALU and small calls, one split count for all requests: the
+    // longest request's pieces no longer than the average work per resident
+    // workgroup, at least min_piece tiles (1 for the vector-ALU kernel, whose
+    // tiles are slow), at most 16 pieces.
+    const int64_t slots = (int64_t)s->shape.cus * (kern == Kern::Stream ? 2 : 4);
+    const int min_piece = kern == Kern::Stream ? 2 * ss.kpar : 1;
     int64_t work = 0;   // tiles summed over all non-empty workgroups
     for (const ReqEntry &R : P.reqs) {
       const int64_t rows = (int64_t)R.lq * lp.group;
       work += (int64_t)d.n_kv_heads * ((rows + rows_per_block - 1) / rows_per_block) * R.tiles;
     }
     const int64_t per_slot = std::max<int64_t>(min_piece, (work + slots - 1) / slots);
-    splits = (int32_t)std::min<int64_t>(max_splits, (P.max_tiles + per_slot - 1) / per_slot);
+    splits = (int32_t)std::min<int64_t>(16, (P.max_tiles + per_slot - 1) / per_slot);
     splits = std::max(1, std::min(splits, P.max_tiles / min_piece));
   }
   C.splits = splits;
   lp.num_splits = splits;
-  if (kern == Kern::Mfma128 && splits == 1)
-    balance_order_d128(s, P, lp, rows_per_block,
-                       s->shape.cus / s->shape.xcds * mfma_d128_blocks_per_cu());
-  const size_t rows = (size_t)P.total_q * n_q_heads;
+  lp.spread = kern == Kern::Stream;
+  C.part_rows = splits > 1 ? (int64_t)P.total_q * n_q_heads * splits : 0;
   C.part_off = round_up(P.own_bytes, 256);
-  C.part_bytes = splits > 1 ? rows * splits * (d.d_v + 2) * sizeof(float) : 0;
+  C.part_bytes = (size_t)C.part_rows * (d.d_v + 2) * sizeof(float);
   return PIC_OK;
 }
 
@@ -894,10 +1163,9 @@ pic_status launch_call(const pic_store *s, const Setup &C, LinkParams lp, void *
   lp.lse = lse;
   lp.scale_log2 = scale * 1.4426950408889634f;
   if (C.splits > 1) {
-    const size_t rows = (size_t)C.P.total_q * lp.n_q_heads;
     lp.part_o = (float *)((char *)work + C.part_off);
-    lp.part_m = lp.part_o + rows * C.splits * d.d_v;
-    lp.part_l = lp.part_m + rows * C.splits;
+    lp.part_m = lp.part_o + C.part_rows * d.d_v;
+    lp.part_l = lp.part_m + C.part_rows;
   }
   if (C.P.max_own_lp > 0 || pro.copy_bytes > 0) {
     hipError_t e = launch_prologue(lp, pro.links, pro.reqs, mla, s->esz, C.P.max_own_lp,
@@ -922,7 +1190,7 @@ pic_status launch_call(const pic_store *s, const Setup &C, LinkParams lp, void *
   prof_stop(st, &ev, name);
   if (e != hipSuccess) return hip_fail(e, name);
   if (C.splits > 1) {
-    e = launch_combine(lp, d.dtype, st);
+    e = launch_combine(lp, d.dtype, lp.max_rows * d.n_kv_heads, st);
     if (e != hipSuccess) return hip_fail(e, "combine_kernel");
   }
   return PIC_OK;
@@ -938,14 +1206,15 @@ pic_status launch_small(const pic_store_desc &d, const Setup &C, const LinkEntry
                         float scale, void *out, float *lse, hipStream_t st) {
   LinkParams lp = C.lp;
   if (C.splits > 1) {
-    const size_t rows = (size_t)C.P.total_q * lp.n_q_heads;
     lp.part_o = (float *)work;
-    lp.part_m = lp.part_o + rows * C.splits * d.d_v;
-    lp.part_l = lp.part_m + rows * C.splits;
+    lp.part_m = lp.part_o + C.part_rows * d.d_v;
+    lp.part_l = lp.part_m + C.part_rows;
   }
   lp.links = nullptr;
+  lp.items = nullptr;
   lp.reqs = nullptr;
   lp.order = nullptr;
+  lp.comb = nullptr;
   lp.doc_lim = nullptr;
   lp.q = q;
   lp.k_self = k_self;
@@ -988,7 +1257,7 @@ pic_status launch_small(const pic_store_desc &d, const Setup &C, const LinkEntry
   prof_stop(st, &ev, name);
   if (e != hipSuccess) return hip_fail(e, name);
   if (C.splits > 1) {
-    e = launch_combine(lp, d.dtype, st);
+    e = launch_combine(lp, d.dtype, lp.max_rows * d.n_kv_heads, st);
     if (e != hipSuccess) return hip_fail(e, "combine_kernel");
   }
   return PIC_OK;
@@ -1031,7 +1300,7 @@ pic_status link_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, c
   Stage *stage = nullptr;
   TableLayout tl;
   LinkParams lp = C.lp;
-  rc = upload(s, C.P, C.work_bytes(), &stage, lp, tl);
+  rc = upload(s, C, &stage, lp, tl);
   if (rc != PIC_OK) return rc;
   Prologue pro;
   const char *hd = (const char *)stage->host_dev;
@@ -1057,8 +1326,7 @@ struct pic_link_plan {
   int32_t batch = 0;
   void *dev = nullptr;           // [layer tables][workspace]
   size_t table_bytes = 0;        // one layer's tables, 256-byte aligned
-  size_t off_r = 0, off_o = 0;   // request / order tables within a layer's tables
-  size_t off_d = 0;              // per-query limits (if any) within a layer's tables
+  TableLayout layout{};          // within a layer's tables
   void *work = nullptr;          // inside dev
   // small calls (see small_tables): every layer's link table on the host,
   // [layer][link], run by the small-call kernels as pic_link_attn /
@@ -1603,14 +1871,15 @@ pic_status pic_link_decode_noalloc(pic_store *s, const pic_link_req *req, int32_
   rc = check_tensors(s, C.P, q, k_self, v_self, out);
   if (rc != PIC_OK) return rc;
   if (C.P.total_q == 0) return PIC_OK;
-  // A small call runs the kernels pic_link_decode runs for it (tables as a
-  // kernel argument, own KV read in place): the scratch holds only its
-  // split partials.
+  // (A small call runs the kernels pic_link_decode runs for it, tables as a
+  // kernel argument and own KV read in place: the scratch holds only its
+  // split partials.)
+  const size_t charge = noalloc_charge(s, C, num_splits);
+  if (charge > kStaticScratchBytes)
+    return fail(PIC_ERR_INVALID,
+                "the call needs %zu bytes of scratch (tables, own KV, split partials); the static "
+                "scratch holds %zu", charge, kStaticScratchBytes);
   if (C.small) {
-    if (C.part_bytes > kStaticScratchBytes)
-      return fail(PIC_ERR_INVALID,
-                  "the call needs %zu bytes of scratch (split partials); the static scratch "
-                  "holds %zu", C.part_bytes, kStaticScratchBytes);
     DeviceGuard dg(s->device);
     if (!dg.ok) return fail(PIC_ERR_HIP, "cannot select the store's device");
     void *base = nullptr;
@@ -1618,44 +1887,36 @@ pic_status pic_link_decode_noalloc(pic_store *s, const pic_link_req *req, int32_
     return launch_small(s->desc, C, C.P.links.data(), base, q, k_self, v_self, softmax_scale,
                         out, lse, (hipStream_t)stream);
   }
-  // scratch layout: [link table][request table][order][per-query limits][workspace]
-  Plan &P = C.P;
-  const size_t nl = P.links.size(), nr = P.reqs.size();
-  const size_t off_r = round_up(sizeof(LinkEntry) * nl, 256);
-  const size_t off_o = off_r + round_up(sizeof(ReqEntry) * nr, 256);
-  const size_t off_d = off_o + round_up(sizeof(int32_t) * nr, 256);
-  const size_t tables = off_d + round_up(sizeof(int32_t) * P.doc_lim.size(), 256);
-  const size_t need = tables + C.work_bytes();
-  if (need > kStaticScratchBytes)
-    return fail(PIC_ERR_INVALID,
-                "the call needs %zu bytes of scratch (tables, own KV, split partials); the static "
-                "scratch holds %zu", need, kStaticScratchBytes);
+  // scratch layout: [tables][workspace]. Uneven requests may be cut into more
+  // pieces than the call is charged for: then into fewer, until it fits.
+  TableLayout t = table_layout(C);
+  while (t.bytes + C.work_bytes() > kStaticScratchBytes + kStaticScratchSlack && C.splits > 1) {
+    const int32_t most = C.splits / 2;
+    for (int32_t &S : C.req_splits) S = std::min(S, most);
+    apply_splits(s, n_q_heads, C.rows_per_block, C);
+    t = table_layout(C);
+  }
+  if (t.bytes + C.work_bytes() > kStaticScratchBytes + kStaticScratchSlack)
+    return fail(PIC_ERR_INVALID, "the call's tables exceed the static scratch");
   DeviceGuard dg(s->device);
   if (!dg.ok) return fail(PIC_ERR_HIP, "cannot select the store's device");
   void *base = nullptr;
   HIP_TRY(static_scratch(&base), "hipGetSymbolAddress(scratch)");
   char *dev = (char *)base;
-  place_own(s, P, dev + tables, P.links.data());
-  std::vector<char> host(tables, 0);
-  if (nl) memcpy(host.data(), P.links.data(), sizeof(LinkEntry) * nl);
-  memcpy(host.data() + off_r, P.reqs.data(), sizeof(ReqEntry) * nr);
-  memcpy(host.data() + off_o, P.order.data(), sizeof(int32_t) * nr);
-  if (!P.doc_lim.empty())
-    memcpy(host.data() + off_d, P.doc_lim.data(), sizeof(int32_t) * P.doc_lim.size());
+  place_own(s, C.P, dev + t.bytes, C.P.links.data());
+  std::vector<char> host(t.bytes, 0);
+  write_tables(C, t, C.P.links.data(), host.data());
   const hipStream_t st = (hipStream_t)stream;
   // pageable source: the runtime copies it before returning (no staging
   // buffer of ours, no allocation)
-  HIP_TRY(hipMemcpyAsync(dev, host.data(), tables, hipMemcpyHostToDevice, st),
+  HIP_TRY(hipMemcpyAsync(dev, host.data(), t.bytes, hipMemcpyHostToDevice, st),
           "hipMemcpyAsync(tables to scratch)");
   LinkParams lp = C.lp;
-  lp.links = (const LinkEntry *)dev;
-  lp.reqs = (const ReqEntry *)(dev + off_r);
-  lp.order = (const int32_t *)(dev + off_o);
-  lp.doc_lim = P.doc_lim.empty() ? nullptr : (const int32_t *)(dev + off_d);
+  point_tables(C, t, dev, lp);
   Prologue pro;
   pro.links = lp.links;
   pro.reqs = lp.reqs;
-  return launch_call(s, C, lp, dev + tables, pro, q, k_self, v_self, softmax_scale, out, lse, st,
+  return launch_call(s, C, lp, dev + t.bytes, pro, q, k_self, v_self, softmax_scale, out, lse, st,
                      false);
 }
 
@@ -1681,11 +1942,9 @@ pic_status pic_link_plan_create(pic_store *s, const pic_link_req *req, int32_t n
   pl->store = s;
   pl->batch = req->batch;
   const Plan &P = pl->C.P;
-  const size_t nl = P.links.size(), nr = P.reqs.size();
-  pl->off_r = round_up(sizeof(LinkEntry) * nl, 256);
-  pl->off_o = pl->off_r + round_up(sizeof(ReqEntry) * nr, 256);
-  pl->off_d = pl->off_o + round_up(sizeof(int32_t) * nr, 256);
-  pl->table_bytes = round_up(pl->off_d + sizeof(int32_t) * P.doc_lim.size(), 256);
+  const size_t nl = P.links.size();
+  pl->layout = table_layout(pl->C);
+  pl->table_bytes = pl->layout.bytes;
   // A small call keeps its tables on the host (one per layer) and needs
   // device memory for its split partials only.
   pl->small = pl->C.small;
@@ -1734,19 +1993,13 @@ pic_status pic_link_plan_create(pic_store *s, const pic_link_req *req, int32_t n
     std::vector<bool> own(nl, false);
     for (auto &o : P.own) own[o.first] = true;
     for (int32_t l = 0; l < s->n_layers; ++l) {
-      char *h = host.data() + (size_t)l * pl->table_bytes;
-      LinkEntry *L = (LinkEntry *)h;
-      for (size_t i = 0; i < nl; ++i) {
-        L[i] = links[i];
+      std::vector<LinkEntry> at(links);
+      for (size_t i = 0; i < nl; ++i)
         if (!own[i]) {
-          L[i].k = (const char *)links[i].k + (int64_t)l * s->layer_bytes;
-          L[i].v = (const char *)links[i].v + (int64_t)l * s->layer_bytes;
+          at[i].k = (const char *)at[i].k + (int64_t)l * s->layer_bytes;
+          at[i].v = (const char *)at[i].v + (int64_t)l * s->layer_bytes;
         }
-      }
-      if (nr) memcpy(h + pl->off_r, P.reqs.data(), sizeof(ReqEntry) * nr);
-      if (nr) memcpy(h + pl->off_o, P.order.data(), sizeof(int32_t) * nr);
-      if (!P.doc_lim.empty())
-        memcpy(h + pl->off_d, P.doc_lim.data(), sizeof(int32_t) * P.doc_lim.size());
+      write_tables(pl->C, pl->layout, at.data(), host.data() + (size_t)l * pl->table_bytes);
     }
     hipError_t e = hipMemcpy(pl->dev, host.data(), tables, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
@@ -1783,10 +2036,7 @@ pic_status pic_link_plan_run(pic_link_plan *pl, int32_t layer, const void *q, co
                         (hipStream_t)stream);
   LinkParams lp = pl->C.lp;
   const char *t = (const char *)pl->dev + (size_t)layer * pl->table_bytes;
-  lp.links = (const LinkEntry *)t;
-  lp.reqs = (const ReqEntry *)(t + pl->off_r);
-  lp.order = (const int32_t *)(t + pl->off_o);
-  lp.doc_lim = pl->C.P.doc_lim.empty() ? nullptr : (const int32_t *)(t + pl->off_d);
+  point_tables(pl->C, pl->layout, t, lp);
   Prologue pro;
   pro.links = lp.links;
   pro.reqs = lp.reqs;

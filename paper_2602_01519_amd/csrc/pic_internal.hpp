@@ -68,31 +68,62 @@ __host__ __device__ __forceinline__ int visible_tiles(const ReqEntry &r, int q_l
                        : r.doc_tiles;
 }
 
+// One piece of a request's keys: a kernel's unit of work for one kv head (and
+// row block). Holds all that a workgroup needs before its first key load, so
+// that load waits for one table read (the request order, the request and a
+// walk over its links were three and more dependent ones). The link fields
+// are those of the entry that holds tile t_begin; later links follow at
+// links[link + 1] ...
+struct WorkItem {
+  const void *k, *v;
+  int32_t len, lp, tile0, tok0;
+  int32_t link;
+  int32_t t_begin, t_end; // tiles of the piece, in the kernel's tile size
+  int32_t q0, lq, ls, doc_tiles;
+  int32_t part;           // first partial row of the piece (row i of the request
+                          // at part + i); -1: the request is not split
+};
+static_assert(sizeof(WorkItem) == 64, "one 64-byte line per item");
+
+// A request's split partials for the combine: rows row0 .. row0 + rows of
+// out, piece s of row i at partial row part0 + s * rows + i.
+struct CombineEntry {
+  int32_t row0, rows, part0, splits;
+};
+
 struct LinkParams {
   const LinkEntry *links;
+  const WorkItem *items;  // NULL for the vector-ALU and small-call kernels
   const ReqEntry *reqs;
   const int32_t *order;   // requests, heaviest first
+  const CombineEntry *comb;   // per request (NULL: num_splits pieces of every row)
   const void *q;
   const void *k_self;
   const void *v_self;
   void *out;
   float *lse;
-  float *part_o;          // split partials: [split][Tq*H_q][d_v] unnormalised
-  float *part_m;          // [split][Tq*H_q] running max (log2 domain)
-  float *part_l;          // [split][Tq*H_q] running sum
+  float *part_o;          // split partials: [partial row][d_v] unnormalised
+  float *part_m;          // [partial row] running max (log2 domain)
+  float *part_l;          // [partial row] running sum
   const int32_t *doc_lim; // per query token: linked rows it sees (NULL: all of them)
   int32_t batch;
+  int32_t n_items;
   int32_t n_q_heads;
   int32_t n_kv_heads;
   int32_t group;          // n_q_heads / n_kv_heads
   int32_t d_k;
   int32_t d_v;
   int32_t total_q;        // Tq
-  int32_t num_splits;     // 1: write out/lse directly; >1: write partials
+  int32_t num_splits;     // most pieces of a request (1: nothing to combine)
   int32_t nrb;            // row blocks per (request, kv head)
   int32_t max_rows;       // most rows of one (request, kv head)
-  int32_t n_groups;       // batch * n_kv_heads, padded as the kernel requires
+  int32_t n_groups;       // batch * n_kv_heads
+  int32_t spread;         // matrix-core kernels: row blocks of one unit on all XCDs
   int32_t n_xcd;          // accelerator dies (XCDs) of the device, each with its own L2
+  int32_t own_in_place;   // decode kernel: own KV read from k_self / v_self, an
+                          // item's tok0 holds the request's first own row
+  int32_t even;           // all requests have as many tiles, rows and pieces
+  int32_t gang;           // MLA kernel: consecutive row blocks on one XCD
   int32_t kpar;           // stream kernel: key parts within a workgroup (1, 2 or 4)
   float scale_log2;       // softmax_scale * log2(e)
 };
@@ -105,6 +136,62 @@ struct DevShape {
   int32_t xcds;
 };
 DevShape device_shape();
+
+// Work mapping of the matrix-core kernels: workgroup b of the grid takes row
+// block rb of unit u (item x kv head). Consecutive workgroups go round-robin
+// to the XCDs; the row blocks of one unit read the same keys, so they share
+// an XCD and its L2 and are dispatched back to back. Where that would leave
+// XCDs idle (few units, or a last round of them that fills few XCDs: more
+// than a quarter of the places empty), the row blocks of every unit spread
+// over all XCDs instead.
+inline bool spread_units(int64_t units, int32_t nrb, int32_t n_xcd) {
+  return nrb > 1 && 4 * ((units + n_xcd - 1) / n_xcd * n_xcd) > 5 * units;
+}
+inline int64_t unit_blocks(int64_t units, int32_t nrb, int32_t n_xcd, bool spread) {
+  return spread ? units * nrb : (units + n_xcd - 1) / n_xcd * n_xcd * nrb;
+}
+struct UnitBlock {
+  int32_t u, rb;
+};
+__device__ __forceinline__ UnitBlock unit_of_block(int32_t b, int32_t nrb, int32_t n_xcd,
+                                                   int32_t spread, int32_t units) {
+  if (spread) return UnitBlock{b % units, b / units};
+  const int32_t xcd = b % n_xcd, j = b / n_xcd;
+  return UnitBlock{xcd + n_xcd * (j / nrb), j % nrb};
+}
+
+// Items and tables are read through the constant address space: every lookup
+// is a scalar load.
+typedef __attribute__((address_space(4))) const LinkEntry *const_links;
+typedef __attribute__((address_space(4))) const WorkItem *const_items;
+__device__ __forceinline__ WorkItem load_item(const WorkItem *items, int32_t i) {
+  const_items p = (const_items)items + i;
+  WorkItem w;
+  w.k = p->k;
+  w.v = p->v;
+  w.len = p->len;
+  w.lp = p->lp;
+  w.tile0 = p->tile0;
+  w.tok0 = p->tok0;
+  w.link = p->link;
+  w.t_begin = p->t_begin;
+  w.t_end = p->t_end;
+  w.q0 = p->q0;
+  w.lq = p->lq;
+  w.ls = p->ls;
+  w.doc_tiles = p->doc_tiles;
+  w.part = p->part;
+  return w;
+}
+__device__ __forceinline__ ReqEntry item_request(const WorkItem &w) {
+  ReqEntry R{};
+  R.q0 = w.q0;
+  R.lq = w.lq;
+  R.ls = w.ls;
+  R.doc_tiles = w.doc_tiles;
+  R.tiles = w.doc_tiles + (w.ls + kTile - 1) / kTile;
+  return R;
+}
 
 // Launchers (each returns the launch status).
 
@@ -215,7 +302,7 @@ hipError_t launch_link_stream(const LinkParams &p, int dtype, int rows, hipStrea
 
 // bf16 MLA (absorbed) link attention: one 576-wide latent kv head, values
 // are the first 512 entries of each latent row.
-hipError_t launch_link_mla(const LinkParams &p, hipStream_t st, const char **name);
+hipError_t launch_link_mla(LinkParams p, hipStream_t st, const char **name);
 int mla_rows_per_block();
 
 // Achievable-peak microbenchmarks (out: peak_out_floats() floats of scratch).
@@ -228,12 +315,16 @@ hipError_t launch_peak_write(void *dst, int64_t bytes, hipStream_t st);
 // The library's static device scratch (a file-scope array, no allocation):
 // its size, and its address on the current device (resolved once per
 // device). Used by the entry points that must not allocate.
+// kStaticScratchSlack: room beyond what a call is charged for, for its work
+// items (64 B each).
 constexpr size_t kStaticScratchBytes = size_t(64) << 20;
+constexpr size_t kStaticScratchSlack = size_t(8) << 20;
 constexpr int kMaxDevices = 64;
 hipError_t static_scratch(void **out);
 
 // Log-sum-exp merge of split partials into out / lse.
-hipError_t launch_combine(const LinkParams &p, int dtype, hipStream_t st);
+// max_rows: most rows of one p.comb entry (unused when p.comb is NULL).
+hipError_t launch_combine(const LinkParams &p, int dtype, int32_t max_rows, hipStream_t st);
 
 // Tables of a small generic-kernel call, passed by value as a kernel
 // argument: the call then needs neither the table copy nor the own-KV

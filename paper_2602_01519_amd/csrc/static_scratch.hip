@@ -8,7 +8,7 @@
 
 #include "pic_internal.hpp"
 
-__device__ __align__(256) unsigned char scratch[pic::kStaticScratchBytes];
+__device__ __align__(256) unsigned char scratch[pic::kStaticScratchBytes + pic::kStaticScratchSlack];
 
 namespace pic {
 namespace {
