@@ -788,41 +788,42 @@ __global__ __launch_bounds__(256) void link_small_kernel(LinkParams p, SmallTabs
 }
 
 // ---------------------------------------------------------------------------
-// Split-K combine: kWpr waves per output row, lane j covering value dims
-// 2j, 2j+1 of each of the row's kChunks 128-wide chunks (8-byte loads: a
-// row's partial of one split is one coalesced 512-byte read per chunk).
-// A wave passes over every kWpr-th split, kB at a time: their maxima and
-// sums (wave-uniform, read through the scalar cache) and partial outputs are
-// loaded together, and the running merge is rescaled when the maximum grows,
-// as in the online softmax -- a wave with up to kB splits costs one memory
-// round trip and no cross-lane reduction; the row's waves then merge through
-// LDS. With one wave per row the passes are a serial chain of round trips:
-// 32 splits of 1184 rows took 7.4 us (now 5.6), 43 of 192 rows 8.9 us (4.0),
-// 43 of 512 rows 512 wide 20.2 us (12.1). Every (split, row) partial below
-// the request's split count is written by the attention kernels (zeros with
-// m = -inf for an empty split).
+// Split-K combine. A group of kLanes lanes (16, 32 or 64: d_v up to 64, 128,
+// more) takes a row, a lane 4 value dims of each of its kChunks chunks (16-byte
+// loads); kGpr groups of the workgroup share a row, each with every kGpr-th
+// split. A group takes its splits kB at a time: their maxima, sums and
+// partial outputs are loaded together, and the running merge is rescaled
+// when the maximum grows, as in the online softmax; the groups of a row then
+// merge through LDS. Bound by memory latency for few rows (a chain of kB
+// splits per round trip: hence several groups per row) and by memory
+// bandwidth for many (hence whole 16-byte lanes: one wave per row with 8-byte
+// loads left half of it idle for 64-wide heads). Measured, before -> now:
+// 32,800 rows x 2..3 splits x 128 15.9 -> 11.2 us, 36,000 x 2..4 x 64 15.4 ->
+// 7.6, 7,900 x 6..17 x 64 (fp32) 10.9 -> 7.3 (8.3 with eight groups per row),
+// 192 x 15..53 x 128 8.9 -> 4.1 (5.3 with four groups).
+// Every (split, row) partial below the request's split count is written by
+// the attention kernels (zeros with m = -inf for an empty split).
 template <typename T>
-__device__ __forceinline__ void store_pair(T *out, int e, float x, float y);
+__device__ __forceinline__ void store_quad(T *out, float4 v);
 template <>
-__device__ __forceinline__ void store_pair<float>(float *out, int e, float x, float y) {
-  *(float2 *)(out + e) = make_float2(x, y);
+__device__ __forceinline__ void store_quad<float>(float *out, float4 v) {
+  *(float4 *)out = v;
 }
 template <>
-__device__ __forceinline__ void store_pair<uint16_t>(uint16_t *out, int e, float x, float y) {
-  *(uint32_t *)(out + e) = (uint32_t)bf16_rne(x) | ((uint32_t)bf16_rne(y) << 16);
+__device__ __forceinline__ void store_quad<uint16_t>(uint16_t *out, float4 v) {
+  *(uint2 *)out = make_uint2((uint32_t)bf16_rne(v.x) | ((uint32_t)bf16_rne(v.y) << 16),
+                             (uint32_t)bf16_rne(v.z) | ((uint32_t)bf16_rne(v.w) << 16));
 }
 
-template <typename T, int kChunks, int kWpr>
+template <typename T, int kLanes, int kChunks, int kGpr>
 __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
-  typedef __attribute__((address_space(4))) const float *const_floats;
   constexpr int kB = 4;
-  constexpr int kRowsPerBlock = 4 / kWpr;
-  __shared__ float2 so[kWpr > 1 ? 4 : 1][kWpr > 1 ? kChunks * 64 : 1];
-  __shared__ float sm[4], sl[4];
-  // the wave index read as a uniform value, so the row's split loads are
-  // scalar loads
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int sub = wave % kWpr;
+  constexpr int kGroups = 256 / kLanes;
+  constexpr int kRowsPerBlock = kGroups / kGpr;
+  __shared__ float4 so[kGpr > 1 ? kGroups : 1][kGpr > 1 ? kChunks * kLanes : 1];
+  __shared__ float sm[kGroups], sl[kGroups];
+  const int grp = threadIdx.x / kLanes, lane = threadIdx.x % kLanes;
+  const int sub = grp % kGpr;
   int64_t rows, row0 = 0, part0 = 0;
   int splits;
   if (p.comb) {            // request blockIdx.y
@@ -838,17 +839,14 @@ __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
     rows = (int64_t)p.total_q * p.n_q_heads;
     splits = p.num_splits;
   }
-  const int64_t lrow = (int64_t)blockIdx.x * kRowsPerBlock + wave / kWpr;
+  const int64_t lrow = (int64_t)blockIdx.x * kRowsPerBlock + grp / kGpr;
   const int64_t orow = row0 + lrow, prow = part0 + lrow;
   const bool valid = lrow < rows;
   const int S = valid ? splits : 0, dv = p.d_v;
-  const int e0 = 2 * lane;
-  const const_floats pm = (const_floats)p.part_m + prow;
-  const const_floats pl = (const_floats)p.part_l + prow;
   float M = -INFINITY, L = 0.f;
-  float2 acc[kChunks];
+  float4 acc[kChunks];
 #pragma unroll
-  for (int c = 0; c < kChunks; ++c) acc[c] = make_float2(0.f, 0.f);
+  for (int c = 0; c < kChunks; ++c) acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
   auto merge = [&](float bm, auto &mb, auto &lb, auto &vb, int n) {
     if (bm == -INFINITY) return;
     const float r = M == -INFINITY ? 0.f : exp2f(M - bm);
@@ -857,6 +855,8 @@ __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
     for (int c = 0; c < kChunks; ++c) {
       acc[c].x *= r;
       acc[c].y *= r;
+      acc[c].z *= r;
+      acc[c].w *= r;
     }
 #pragma unroll
     for (int i = 0; i < n; ++i) {
@@ -866,23 +866,26 @@ __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
       for (int c = 0; c < kChunks; ++c) {
         acc[c].x += w * vb[i][c].x;
         acc[c].y += w * vb[i][c].y;
+        acc[c].z += w * vb[i][c].z;
+        acc[c].w += w * vb[i][c].w;
       }
     }
     M = bm;
   };
-  for (int s0 = sub; s0 < S; s0 += kB * kWpr) {
+  for (int s0 = sub; s0 < S; s0 += kB * kGpr) {
     float mb[kB], lb[kB];
-    float2 vb[kB][kChunks];
+    float4 vb[kB][kChunks];
 #pragma unroll
     for (int i = 0; i < kB; ++i) {
-      const int si = s0 + i * kWpr, sc = min(si, S - 1);   // past the last: reread it, weight 0
-      mb[i] = pm[(int64_t)sc * rows];
-      lb[i] = pl[(int64_t)sc * rows];
-      const float *po = p.part_o + ((int64_t)sc * rows + prow) * dv;
+      const int si = s0 + i * kGpr;
+      const int64_t pr = (int64_t)min(si, S - 1) * rows + prow;   // past the last: reread it, weight 0
+      mb[i] = p.part_m[pr];
+      lb[i] = p.part_l[pr];
+      const float *po = p.part_o + pr * dv;
 #pragma unroll
       for (int c = 0; c < kChunks; ++c) {
-        const int e = 128 * c + e0;
-        vb[i][c] = e < dv ? *(const float2 *)(po + e) : make_float2(0.f, 0.f);
+        const int e = 4 * (kLanes * c + lane);
+        vb[i][c] = e < dv ? *(const float4 *)(po + e) : make_float4(0.f, 0.f, 0.f, 0.f);
       }
       if (si >= S) mb[i] = -INFINITY;
     }
@@ -891,29 +894,29 @@ __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
     for (int i = 0; i < kB; ++i) bm = fmaxf(bm, mb[i]);
     merge(bm, mb, lb, vb, kB);
   }
-  if constexpr (kWpr > 1) {
-    // the row's first wave takes in what the others hold
+  if constexpr (kGpr > 1) {
+    // the row's first group takes in what the others hold
     if (sub > 0) {
 #pragma unroll
-      for (int c = 0; c < kChunks; ++c) so[wave][64 * c + lane] = acc[c];
+      for (int c = 0; c < kChunks; ++c) so[grp][kLanes * c + lane] = acc[c];
       if (lane == 0) {
-        sm[wave] = M;
-        sl[wave] = L;
+        sm[grp] = M;
+        sl[grp] = L;
       }
     }
     __syncthreads();
     if (sub > 0) return;
-    constexpr int kN = kWpr - 1;
+    constexpr int kN = kGpr - 1;
     float mb[kN], lb[kN];
-    float2 vb[kN][kChunks];
+    float4 vb[kN][kChunks];
     float bm = M;
 #pragma unroll
     for (int i = 0; i < kN; ++i) {
-      mb[i] = sm[wave + 1 + i];
-      lb[i] = sl[wave + 1 + i];
+      mb[i] = sm[grp + 1 + i];
+      lb[i] = sl[grp + 1 + i];
       bm = fmaxf(bm, mb[i]);
 #pragma unroll
-      for (int c = 0; c < kChunks; ++c) vb[i][c] = so[wave + 1 + i][64 * c + lane];
+      for (int c = 0; c < kChunks; ++c) vb[i][c] = so[grp + 1 + i][kLanes * c + lane];
     }
     merge(bm, mb, lb, vb, kN);
   }
@@ -922,8 +925,9 @@ __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
   const float inv = M == -INFINITY ? 0.f : 1.f / L;
 #pragma unroll
   for (int c = 0; c < kChunks; ++c) {
-    const int e = 128 * c + e0;
-    if (e < dv) store_pair<T>(out, e, acc[c].x * inv, acc[c].y * inv);
+    const int e = 4 * (kLanes * c + lane);
+    if (e < dv)
+      store_quad<T>(out + e, make_float4(acc[c].x * inv, acc[c].y * inv, acc[c].z * inv, acc[c].w * inv));
   }
   if (p.lse && lane == 0)
     p.lse[orow] = M == -INFINITY ? -INFINITY : (M + log2f(L)) * 0.69314718055994531f;
@@ -1332,31 +1336,41 @@ hipError_t launch_link_valu(const LinkParams &p, int dtype, int mla, hipStream_t
 hipError_t launch_combine(const LinkParams &p, int dtype, int32_t max_rows, hipStream_t st) {
   const int64_t rows = p.comb ? max_rows : (int64_t)p.total_q * p.n_q_heads;
   if (rows == 0) return hipSuccess;
-  // as many waves per row as leave each at most one pass, up to four
-  const int wpr = p.num_splits <= 4 ? 1 : p.num_splits <= 8 ? 2 : 4;
-  const dim3 grid((unsigned)((rows * wpr + 3) / 4), p.comb ? (unsigned)p.batch : 1u);
-  auto go = [&](auto kc, auto kw) {
-    constexpr int kC = decltype(kc)::value, kW = decltype(kw)::value;
+  // as many groups per row as leave each at most one pass, as far as a
+  // workgroup has them (eight of 16 or 32 lanes, four of 64)
+  const int lanes = p.d_v <= 64 ? 16 : p.d_v <= 128 ? 32 : 64;
+  const int gpr = p.num_splits <= 4    ? 1
+                  : p.num_splits <= 8  ? 2
+                  : p.num_splits <= 20 ? 4
+                  : lanes == 64        ? 4
+                                       : 8;
+  const int64_t per_block = 256 / lanes / gpr;
+  const dim3 grid((unsigned)((rows + per_block - 1) / per_block), p.comb ? (unsigned)p.batch : 1u);
+  auto go = [&](auto kl, auto kc, auto kg) {
+    constexpr int kL = decltype(kl)::value, kC = decltype(kc)::value, kG = decltype(kg)::value;
     if (dtype == 0)
-      hipLaunchKernelGGL((combine_kernel<float, kC, kW>), grid, dim3(256), 0, st, p);
+      hipLaunchKernelGGL((combine_kernel<float, kL, kC, kG>), grid, dim3(256), 0, st, p);
     else
-      hipLaunchKernelGGL((combine_kernel<uint16_t, kC, kW>), grid, dim3(256), 0, st, p);
+      hipLaunchKernelGGL((combine_kernel<uint16_t, kL, kC, kG>), grid, dim3(256), 0, st, p);
   };
-  auto by_wpr = [&](auto kc) {
-    if (wpr == 1)
-      go(kc, std::integral_constant<int, 1>());
-    else if (wpr == 2)
-      go(kc, std::integral_constant<int, 2>());
-    else
-      go(kc, std::integral_constant<int, 4>());
+  auto by_gpr = [&](auto kl, auto kc) {
+    if (gpr == 1)
+      go(kl, kc, std::integral_constant<int, 1>());
+    else if (gpr == 2)
+      go(kl, kc, std::integral_constant<int, 2>());
+    else if (gpr == 4)
+      go(kl, kc, std::integral_constant<int, 4>());
+    else if constexpr (decltype(kl)::value < 64)
+      go(kl, kc, std::integral_constant<int, 8>());
   };
-  const int chunks = (p.d_v + 127) / 128;     // 1 .. 8 (d_v <= 1024)
-  if (chunks == 1)
-    by_wpr(std::integral_constant<int, 1>());
-  else if (chunks <= 4)
-    by_wpr(std::integral_constant<int, 4>());
-  else
-    by_wpr(std::integral_constant<int, 8>());
+  if (lanes == 16)
+    by_gpr(std::integral_constant<int, 16>(), std::integral_constant<int, 1>());
+  else if (lanes == 32)
+    by_gpr(std::integral_constant<int, 32>(), std::integral_constant<int, 1>());
+  else if (p.d_v <= 512)
+    by_gpr(std::integral_constant<int, 64>(), std::integral_constant<int, 2>());
+  else            // d_v <= 1024
+    by_gpr(std::integral_constant<int, 64>(), std::integral_constant<int, 4>());
   return hipGetLastError();
 }
 
