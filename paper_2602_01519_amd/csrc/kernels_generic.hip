@@ -802,7 +802,10 @@ __global__ __launch_bounds__(256) void link_small_kernel(LinkParams p, SmallTabs
 // 7.6, 7,900 x 6..17 x 64 (fp32) 10.9 -> 7.3 (8.3 with eight groups per row),
 // 192 x 15..53 x 128 8.9 -> 4.1 (5.3 with four groups).
 // Every (split, row) partial below the request's split count is written by
-// the attention kernels (zeros with m = -inf for an empty split).
+// the attention kernels (zeros with m = -inf for an empty split). kSkip: but
+// for the values of those with m = -inf, which are neither written nor read
+// (calls with per-query limits, where about half the pieces of a row block
+// hold nothing for it); their loads then wait for the maxima.
 template <typename T>
 __device__ __forceinline__ void store_quad(T *out, float4 v);
 template <>
@@ -815,7 +818,7 @@ __device__ __forceinline__ void store_quad<uint16_t>(uint16_t *out, float4 v) {
                              (uint32_t)bf16_rne(v.z) | ((uint32_t)bf16_rne(v.w) << 16));
 }
 
-template <typename T, int kLanes, int kChunks, int kGpr>
+template <typename T, int kLanes, int kChunks, int kGpr, bool kSkip>
 __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
   constexpr int kB = 4;
   constexpr int kGroups = 256 / kLanes;
@@ -885,7 +888,8 @@ __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
 #pragma unroll
       for (int c = 0; c < kChunks; ++c) {
         const int e = 4 * (kLanes * c + lane);
-        vb[i][c] = e < dv ? *(const float4 *)(po + e) : make_float4(0.f, 0.f, 0.f, 0.f);
+        vb[i][c] = e < dv && (!kSkip || mb[i] != -INFINITY) ? *(const float4 *)(po + e)
+                                                            : make_float4(0.f, 0.f, 0.f, 0.f);
       }
       if (si >= S) mb[i] = -INFINITY;
     }
@@ -1349,9 +1353,11 @@ hipError_t launch_combine(const LinkParams &p, int dtype, int32_t max_rows, hipS
   auto go = [&](auto kl, auto kc, auto kg) {
     constexpr int kL = decltype(kl)::value, kC = decltype(kc)::value, kG = decltype(kg)::value;
     if (dtype == 0)
-      hipLaunchKernelGGL((combine_kernel<float, kL, kC, kG>), grid, dim3(256), 0, st, p);
+      hipLaunchKernelGGL((combine_kernel<float, kL, kC, kG, false>), grid, dim3(256), 0, st, p);
+    else if (kL == 32 && p.skip_empty)
+      hipLaunchKernelGGL((combine_kernel<uint16_t, kL, kC, kG, kL == 32>), grid, dim3(256), 0, st, p);
     else
-      hipLaunchKernelGGL((combine_kernel<uint16_t, kL, kC, kG>), grid, dim3(256), 0, st, p);
+      hipLaunchKernelGGL((combine_kernel<uint16_t, kL, kC, kG, false>), grid, dim3(256), 0, st, p);
   };
   auto by_gpr = [&](auto kl, auto kc) {
     if (gpr == 1)

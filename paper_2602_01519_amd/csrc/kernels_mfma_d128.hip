@@ -337,6 +337,26 @@ __device__ __forceinline__ void compute_tile(const Ctx &c, const uint4 *kt, cons
   }
 }
 
+// The tile after the last one of the item that holds a linked row below the
+// farthest limit of query tokens tok_lo .. tok_hi, at most t_end.
+__device__ __forceinline__ int limit_end(const LinkParams &p, const WorkItem &it, int tok_lo,
+                                         int tok_hi, int lane, int t_end) {
+  int far = 0;
+  for (int t = tok_lo + lane; t <= tok_hi; t += 64) far = max(far, p.doc_lim[t]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) far = max(far, __shfl_xor(far, o));
+  far = uni(far);
+  const const_links links = (const_links)p.links + it.link;
+  int li = 0, tok0 = it.tok0, len = it.len, tile0 = it.tile0;
+  while (far > tok0 + len && tile0 + (len + kTile - 1) / kTile < t_end) {
+    ++li;
+    tok0 = links[li].tok0;
+    len = links[li].len;
+    tile0 = links[li].tile0;
+  }
+  return min(t_end, tile0 + (max(0, min(far - tok0, len)) + kTile - 1) / kTile);
+}
+
 // kStages: tile buffer pairs, 2 or 3 (see the tile loops).
 template <bool kLim, int kStages>
 __global__ __launch_bounds__(kWaves * 64, 8 / kWaves) void link_mfma_d128_kernel(LinkParams p) {
@@ -367,7 +387,14 @@ __global__ __launch_bounds__(kWaves * 64, 8 / kWaves) void link_mfma_d128_kernel
   // Own tiles past the causal limit of the block's last row hold no key any
   // of its rows sees: the block's key range ends at the last visible one.
   const int vis = visible_tiles(R, min(nrows - 1, row0 + kRows - 1) / group);
-  const int t_begin = it.t_begin, t_end = min(it.t_end, vis);
+  const int t_begin = it.t_begin;
+  int t_end = min(it.t_end, vis);
+  // Per-query limits, documents only: nor does a tile past the farthest limit
+  // of the block's rows (recomputed tokens see the rows up to their own
+  // position, so the row blocks of early tokens need few tiles).
+  if (kLim && R.ls == 0) t_end = limit_end(p, it, R.q0 + row0 / group,
+                                           R.q0 + min(nrows - 1, row0 + kRows - 1) / group,
+                                           c.lane, t_end);
 
   // This lane's row. A wave whose 32 rows are all past the request's rows
   // (short questions: a 16-token question fills 64 of the 256 rows) only
@@ -514,36 +541,28 @@ __global__ __launch_bounds__(kWaves * 64, 8 / kWaves) void link_mfma_d128_kernel
     }
   }
 
-  // ---- epilogue: O^T[dv][row] with dv = d*32 + (x>>2)*8 + g*4 + (x&3)
+  // ---- epilogue: O^T[dv][row] with dv = d*32 + (x>>2)*8 + g*4 + (x&3).
+  // Every copy has landed and every wave is past its last tile: the tile
+  // buffers are free, 8 KB of them for each wave.
+  if (kStages == 3) __syncthreads();
   const float ltot = half_swap_sum(a.lsum);
-  if (!rvalid) return;
+  const int bi = c.wave & 3;
+  const lds_ptr buf = bi == 0 ? (lds_ptr)sk0 : bi == 1 ? (lds_ptr)sk1 : bi == 2 ? (lds_ptr)sv0 : (lds_ptr)sv1;
+  const lds_units sb = (lds_units)(uintptr_t)((uint32_t)(uintptr_t)buf + (c.wave >> 2) * kStoreBytes);
+  const int nvalid = min(kRowsPerWave, nrows - (row0 + c.wave * kRowsPerWave));
+  if (nvalid <= 0) return;
   if (it.part < 0) {
     const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
-    uint16_t *out = (uint16_t *)p.out + orow * kD;
-#pragma unroll
-    for (int d = 0; d < 4; ++d)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int dv = d * 32 + jj * 8 + c.g * 4;
-        __bf16 v4[4];
-#pragma unroll
-        for (int x = 0; x < 4; ++x) v4[x] = (__bf16)(a.o[d][jj * 4 + x] * inv);
-        *(uint2 *)(out + dv) = __builtin_bit_cast(uint2, v4);
-      }
-    if (p.lse && c.g == 0)
+    store_block_bf16(a.o[0], a.o[1], a.o[2], a.o[3], inv, sb, c.lane, nvalid, (int)orow,
+                     (uint16_t *)p.out, kD);
+    if (p.lse && rvalid && c.g == 0)
       p.lse[orow] = ltot > 0.f ? (a.m_used + log2f(ltot)) * 0.69314718055994531f : -INFINITY;
   } else {
     const int64_t prow = it.part + (orow - (int64_t)R.q0 * p.n_q_heads);
-    float *po = p.part_o + prow * kD;
-#pragma unroll
-    for (int d = 0; d < 4; ++d)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int dv = d * 32 + jj * 8 + c.g * 4;
-        *(float4 *)(po + dv) = make_float4(a.o[d][jj * 4], a.o[d][jj * 4 + 1],
-                                           a.o[d][jj * 4 + 2], a.o[d][jj * 4 + 3]);
-      }
-    if (c.g == 0) {
+    // (with limits, the combine reads no values where m is -inf)
+    if (!kLim || __any(ltot > 0.f))
+      store_block_f32(a.o[0], a.o[1], a.o[2], a.o[3], sb, c.lane, nvalid, (int)prow, p.part_o, kD);
+    if (rvalid && c.g == 0) {
       p.part_m[prow] = ltot > 0.f ? a.m_used : -INFINITY;
       p.part_l[prow] = ltot;
     }

@@ -469,37 +469,24 @@ __global__ __launch_bounds__(256, 1) void link_mla_kernel(LinkParams p) {
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) ltot[rb] = sm.xm[2 * rb][n] + sm.xm[2 * rb + 1][n];
 
+  // the tile buffers are free: 8 KB of the first for each wave
+  const lds_units sb = (lds_units)(uintptr_t)(lds_addr(sk0) + wave * kStoreBytes);
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
-    if (!rvalid[rb]) continue;
+    const int nvalid = min(32, nrows - (row0 + 32 * rb));
+    if (nvalid <= 0) continue;
     if (it.part < 0) {
       const float inv = ltot[rb] > 0.f ? 1.f / ltot[rb] : 0.f;
-      uint16_t *out = (uint16_t *)p.out + orow[rb] * kDV;
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const int dv = 128 * wave + 32 * db + jj * 8 + g * 4;
-          __bf16 v4[4];
-#pragma unroll
-          for (int x = 0; x < 4; ++x) v4[x] = (__bf16)(o[db][rb][jj * 4 + x] * inv);
-          *(uint2 *)(out + dv) = __builtin_bit_cast(uint2, v4);
-        }
-      if (p.lse && wave == 0 && g == 0)
+      store_block_bf16(o[0][rb], o[1][rb], o[2][rb], o[3][rb], inv, sb, lane, nvalid,
+                       (int)orow[rb], (uint16_t *)p.out + 128 * wave, kDV);
+      if (p.lse && rvalid[rb] && wave == 0 && g == 0)
         p.lse[orow[rb]] =
             ltot[rb] > 0.f ? (m_used[rb] + log2f(ltot[rb])) * 0.69314718055994531f : -INFINITY;
     } else {
       const int64_t prow = it.part + (orow[rb] - (int64_t)R.q0 * p.n_q_heads);
-      float *po = p.part_o + prow * kDV;
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const int dv = 128 * wave + 32 * db + jj * 8 + g * 4;
-          *(float4 *)(po + dv) = make_float4(o[db][rb][jj * 4], o[db][rb][jj * 4 + 1],
-                                             o[db][rb][jj * 4 + 2], o[db][rb][jj * 4 + 3]);
-        }
-      if (wave == 0 && g == 0) {
+      store_block_f32(o[0][rb], o[1][rb], o[2][rb], o[3][rb], sb, lane, nvalid, (int)prow,
+                      p.part_o + 128 * wave, kDV);
+      if (rvalid[rb] && wave == 0 && g == 0) {
         p.part_m[prow] = ltot[rb] > 0.f ? m_used[rb] : -INFINITY;
         p.part_l[prow] = ltot[rb];
       }

@@ -717,10 +717,14 @@ struct SplitCost {
 // requests the longest request's pieces set the time: an MLA decode step of
 // 32 requests over 4..14 links took 58 us in 8 pieces each).
 // tiles, blocks, rows: per request its key tiles, its workgroups per piece
-// and its output rows.
+// and its output rows. share: the mean part of its tiles that its row blocks
+// walk (below 1 with per-query limits; pieces past a block's part are empty
+// and cost next to nothing), so S pieces are share x S + 1 - share workgroups
+// per row block.
 std::vector<int32_t> choose_splits(const std::vector<int32_t> &tiles,
                                    const std::vector<int32_t> &blocks,
-                                   const std::vector<int64_t> &rows, const SplitCost &c) {
+                                   const std::vector<int64_t> &rows,
+                                   const std::vector<double> &share, const SplitCost &c) {
   const size_t n = tiles.size();
   // ceil(tiles / L); + 0.5 keeps the product off the integers it is cut at
   auto pieces = [&](size_t r, int32_t L, double inv) {
@@ -729,23 +733,24 @@ std::vector<int32_t> choose_splits(const std::vector<int32_t> &tiles,
   };
   auto total = [&](int32_t L) {
     const double inv = 1.0 / L;
-    int64_t t = 0;
-    for (size_t r = 0; r < n; ++r) t += (int64_t)blocks[r] * pieces(r, L, inv);
+    double t = 0;
+    for (size_t r = 0; r < n; ++r)
+      t += blocks[r] * (pieces(r, L, inv) * share[r] + 1 - share[r]);
     return t;
   };
   auto cost = [&](int32_t L) {
     const double inv = 1.0 / L;
-    double work = 0, longest = 0, part = 0;
-    int64_t wgs = 0;
+    double work = 0, longest = 0, part = 0, wgs = 0;
     for (size_t r = 0; r < n; ++r) {
       if (blocks[r] == 0) continue;
       const int32_t S = pieces(r, L, inv);
-      wgs += (int64_t)blocks[r] * S;
-      work += blocks[r] * (tiles[r] + c.over * S);
+      const double held = blocks[r] * (S * share[r] + 1 - share[r]);
+      wgs += held;
+      work += blocks[r] * tiles[r] * share[r] + c.over * held;
       longest = std::max(longest, (double)((tiles[r] + S - 1) / S) + c.over);
-      if (S > 1) part += c.part * (double)rows[r] * S;
+      if (S > 1) part += c.part * (double)rows[r] * S * share[r];
     }
-    const double run = wgs <= c.slots ? longest
+    const double run = wgs <= (double)c.slots ? longest
                                       : std::max(longest, work / (double)c.slots + 0.3 * longest);
     return run + part + (part > 0 ? c.fixed : 0.0);
   };
@@ -754,7 +759,7 @@ std::vector<int32_t> choose_splits(const std::vector<int32_t> &tiles,
   int32_t best_L = most;
   double best = cost(most);
   for (int k : {1, 2, 4, 6, 8}) {          // half rounds
-    const int64_t limit = c.fit * k / 2;
+    const double limit = (double)(c.fit * k / 2);
     if (total(most) > limit) continue;
     int32_t lo = std::min(c.min_piece, most), hi = most;   // shortest L that fits
     while (lo < hi) {
@@ -936,6 +941,21 @@ SplitCost split_cost(Kern kern, int32_t cus, const pic_store_desc &d, int32_t ma
   return c;
 }
 
+// Mean over a request's row blocks of the share of its linked rows that lie
+// below the farthest limit of the block's query tokens.
+double limit_share(const Plan &P, const ReqEntry &R, int group, int rows_per_block, int64_t linked) {
+  const int64_t rows = (int64_t)R.lq * group;
+  double sum = 0;
+  int n = 0;
+  for (int64_t row0 = 0; row0 < rows; row0 += rows_per_block, ++n) {
+    const int64_t last = std::min(rows, row0 + rows_per_block) - 1;
+    int32_t far = 0;
+    for (int64_t t = row0 / group; t <= last / group; ++t) far = std::max(far, P.doc_lim[R.q0 + t]);
+    sum += linked > 0 ? (double)far / (double)linked : 0.0;
+  }
+  return n ? sum / n : 1.0;
+}
+
 // Completes a call of work items from its pieces per request (C.req_splits):
 // item counts, partial rows, request order, workspace layout.
 void apply_splits(pic_store *s, int32_t n_q_heads, int rows_per_block, Setup &C) {
@@ -955,6 +975,11 @@ void apply_splits(pic_store *s, int32_t n_q_heads, int rows_per_block, Setup &C)
   lp.num_splits = C.splits;
   lp.spread = C.kern == Kern::Stream ||
               spread_units((int64_t)C.n_items * lp.n_kv_heads, lp.nrb, lp.n_xcd);
+  // With per-query limits the early row blocks of late pieces are empty: the
+  // last row blocks start first, the empty ones fill in at the end (dispatched
+  // among the others, they delayed the start of some: S = 4 pieces 54 us, 3
+  // pieces 43 us).
+  if (C.kern == Kern::Mfma128 && lp.skip_empty && lp.nrb > 1) lp.spread = 2;
   C.part_rows = 0;
   C.comb.clear();
   if (C.splits > 1) {
@@ -1094,16 +1119,24 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     const int B = req->batch;
     std::vector<int32_t> tiles(B), blocks(B);
     std::vector<int64_t> rows(B);
+    std::vector<double> share(B, 1.0);
     for (int r = 0; r < B; ++r) {
       const ReqEntry &R = P.reqs[r];
       tiles[r] = R.tiles * (kTile / C.tile_keys);
       blocks[r] = d.n_kv_heads * ((R.lq * lp.group + rows_per_block - 1) / rows_per_block);
       rows[r] = (int64_t)R.lq * n_q_heads;
+      // d128 row blocks end at the farthest limit of their rows: count the
+      // part of the tiles they walk
+      if (kern == Kern::Mfma128 && !P.doc_lim.empty() && R.ls == 0 && R.nlinks > 0) {
+        const LinkEntry &last = P.links[R.link0 + R.nlinks - 1];
+        share[r] = limit_share(P, R, lp.group, rows_per_block, last.tok0 + last.len);
+      }
     }
+    lp.skip_empty = kern == Kern::Mfma128 && !P.doc_lim.empty();
     if (mode == Mode::Decode && num_splits > 0)
       C.req_splits.assign(B, num_splits);
     else
-      C.req_splits = choose_splits(tiles, blocks, rows,
+      C.req_splits = choose_splits(tiles, blocks, rows, share,
                                    split_cost(kern, s->shape.cus, d, P.max_rows, ss));
     apply_splits(s, n_q_heads, rows_per_block, C);
     return PIC_OK;

@@ -118,10 +118,11 @@ struct LinkParams {
   int32_t nrb;            // row blocks per (request, kv head)
   int32_t max_rows;       // most rows of one (request, kv head)
   int32_t n_groups;       // batch * n_kv_heads
-  int32_t spread;         // matrix-core kernels: row blocks of one unit on all XCDs
+  int32_t spread;         // matrix-core kernels: row blocks of one unit on all XCDs (1, 2)
   int32_t n_xcd;          // accelerator dies (XCDs) of the device, each with its own L2
   int32_t own_in_place;   // decode kernel: own KV read from k_self / v_self, an
                           // item's tok0 holds the request's first own row
+  int32_t skip_empty;     // values of partials with m = -inf are not written
   int32_t even;           // all requests have as many tiles, rows and pieces
   int32_t gang;           // MLA kernel: consecutive row blocks on one XCD
   int32_t kpar;           // stream kernel: key parts within a workgroup (1, 2 or 4)
@@ -143,7 +144,8 @@ DevShape device_shape();
 // an XCD and its L2 and are dispatched back to back. Where that would leave
 // XCDs idle (few units, or a last round of them that fills few XCDs: more
 // than a quarter of the places empty), the row blocks of every unit spread
-// over all XCDs instead.
+// over all XCDs instead: block 0 of every unit first, or (spread 2: calls with
+// per-query limits) the last one, whose rows see the most.
 inline bool spread_units(int64_t units, int32_t nrb, int32_t n_xcd) {
   return nrb > 1 && 4 * ((units + n_xcd - 1) / n_xcd * n_xcd) > 5 * units;
 }
@@ -155,7 +157,7 @@ struct UnitBlock {
 };
 __device__ __forceinline__ UnitBlock unit_of_block(int32_t b, int32_t nrb, int32_t n_xcd,
                                                    int32_t spread, int32_t units) {
-  if (spread) return UnitBlock{b % units, b / units};
+  if (spread) return UnitBlock{b % units, spread == 2 ? nrb - 1 - b / units : b / units};
   const int32_t xcd = b % n_xcd, j = b / n_xcd;
   return UnitBlock{xcd + n_xcd * (j / nrb), j % nrb};
 }
@@ -191,6 +193,70 @@ __device__ __forceinline__ ReqEntry item_request(const WorkItem &w) {
   R.doc_tiles = w.doc_tiles;
   R.tiles = w.doc_tiles + (w.ls + kTile - 1) / kTile;
   return R;
+}
+
+// Epilogue stores of the matrix-core kernels. After the 32x32 value products
+// lane (n = l % 32, g = l / 32) holds row n, value dims 32 d + 8 j + 4 g ..+3
+// of a 32-row x 128-dim block, so a store straight from the registers covers
+// 32 rows x 16 bytes (bf16) or x 32 bytes (fp32) of lines 128 bytes long. The
+// block goes through LDS instead (8 KB per wave, 16-byte chunks XOR-swizzled
+// by the row, free of bank conflicts) and leaves as whole 256-byte row pieces,
+// 4 rows per instruction. row: the output row of this lane's row n (any
+// value for rows past nvalid); out: its row 0, first of the block's dims.
+typedef float acc32x32 __attribute__((ext_vector_type(16)));
+constexpr uint32_t kStoreBytes = 8192;      // LDS per wave
+typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) u32x4v *lds_units;
+typedef __attribute__((address_space(3))) u32x2v *lds_halves;
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void store_block_units(lds_units lds, int lane, int nvalid, int row,
+                                                  char *out, int64_t row_bytes) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int r = 4 * k + (lane >> 4), c = lane & 15;
+    const u32x4v u = lds[r * 16 + (c ^ (r & 15))];
+    const int at = __shfl(row, r);
+    if (r < nvalid) *(u32x4v *)(out + at * row_bytes + 16 * c) = u;
+  }
+}
+__device__ __forceinline__ void store_block_bf16(const acc32x32 &o0, const acc32x32 &o1,
+                                                 const acc32x32 &o2, const acc32x32 &o3, float inv,
+                                                 lds_units lds, int lane, int nvalid, int row,
+                                                 uint16_t *out, int64_t stride) {
+  const int n = lane & 31, g = lane >> 5;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const acc32x32 &o = d == 0 ? o0 : d == 1 ? o1 : d == 2 ? o2 : o3;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      bf16x4v v4;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) v4[x] = (__bf16)(o[j * 4 + x] * inv);
+      ((lds_halves)lds)[(n * 16 + ((4 * d + j) ^ (n & 15))) * 2 + g] = __builtin_bit_cast(u32x2v, v4);
+    }
+  }
+  store_block_units(lds, lane, nvalid, row, (char *)out, stride * 2);
+}
+__device__ __forceinline__ void store_block_f32(const acc32x32 &o0, const acc32x32 &o1,
+                                                const acc32x32 &o2, const acc32x32 &o3, lds_units lds,
+                                                int lane, int nvalid, int row, float *out,
+                                                int64_t stride) {
+  const int n = lane & 31, g = lane >> 5;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {       // dims 64 h .. 64 h + 63
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      const acc32x32 &o = h == 0 ? (d == 0 ? o0 : o1) : (d == 0 ? o2 : o3);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        lds[n * 16 + ((8 * d + 2 * j + g) ^ (n & 15))] = __builtin_bit_cast(
+            u32x4v, (f32x4v){o[j * 4], o[j * 4 + 1], o[j * 4 + 2], o[j * 4 + 3]});
+    }
+    store_block_units(lds, lane, nvalid, row, (char *)(out + 64 * h), stride * 4);
+  }
 }
 
 // Launchers (each returns the launch status).

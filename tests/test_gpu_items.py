@@ -5,15 +5,18 @@ boundaries on links and inside the own KV, own KV read in place by the decode
 kernel around its tile and limit, few (request, kv head) units over many row
 blocks, MLA runs of row blocks that do not fill an XCD's share, and the
 no-alloc entry's charge. All against the fp64 oracle to the parity bar."""
+import dataclasses
 import math
 
 import numpy as np
 import pytest
 import torch
 
-from paper_2602_01519_amd import pic
+import parity_gate as G
+from paper_2602_01519_amd import pic, runner
 from paper_2602_01519_amd import workloads as W
 
+from test_gpu_blend import ref_link, run_link
 from test_gpu_link import run_and_check
 
 pytestmark = pytest.mark.gpu
@@ -96,3 +99,68 @@ def test_noalloc_charge_is_the_uniform_layout():
         assert not bool((out == 7.0).all())
     finally:
         store.close()
+
+
+@pytest.mark.parametrize("pattern", ["rising", "falling", "edges", "none_seen"])
+def test_limited_row_blocks(pattern):
+    """Cross-only calls with per-query limits whose row blocks end at different
+    tiles (five 256-row blocks, a split call): rising limits as recomputed
+    tokens have, falling ones, limits on tile and link edges, and row blocks
+    that see nothing at all."""
+    q = (300, 40)
+    cfg = uneven("limited", q, None, d_k=128, n_q_heads=8, n_kv_heads=2)
+    wl = W.make_workload(cfg)
+    links = [LONG, [4, 3]]
+    idx = np.array([c for l in links for c in l], dtype=np.int64)
+    co = np.array([0, len(links[0]), len(idx)], np.int32)
+    rows = [sum(LENS[c] for c in l) for l in links]
+    lims = []
+    for n, total in zip(q, rows):
+        if pattern == "rising":
+            lims.append(np.sort(np.random.default_rng(n).integers(1, total + 1, n)))
+        elif pattern == "falling":
+            lims.append(np.linspace(total, 0, n).astype(int))
+        elif pattern == "edges":
+            edges = [0, 1, 63, 64, 65, 699, 700, 701, 764, total - 1, total]
+            lims.append(np.array([min(edges[i % len(edges)], total) for i in range(n)]))
+        else:
+            lims.append(np.where(np.arange(n) < 130, 0, total))
+    lims = np.concatenate(lims).astype(np.int32)
+    dw = runner.upload(dataclasses.replace(wl, plan=dataclasses.replace(
+        wl.plan, chunk_offsets=co, chunk_index=idx)))
+    try:
+        out, lse = run_link(dw.store, cfg, co, wl.chunk_ids[idx], wl.plan.q_offsets, None, wl.q,
+                            None, None, lims=lims)
+        ref, ref_lse = ref_link(cfg, [[dw.chunks[c] for c in l] for l in links], wl.q,
+                                wl.plan.q_offsets, lims=lims)
+        bad = G.failures(G.BF16, out, ref, lse, ref_lse)
+        assert not bad, bad
+    finally:
+        dw.close()
+
+
+@pytest.mark.parametrize("d,dtype,hq,q", [(128, W.BF16, 8, 40), (128, W.BF16, 8, 300),
+                                          (64, W.BF16, 6, 70), (64, W.F32, 6, 70)])
+def test_unaligned_tensors(d, dtype, hq, q):
+    """Query and output tensors that start one element past a 16-byte boundary
+    give the bits aligned ones give."""
+    cfg = W.small_config("unaligned", dtype=dtype, d_k=d, n_q_heads=hq, n_kv_heads=2,
+                         chunk_lens=(700, 130), batch=1, links=(2, 2), q_len=q, self_len=None)
+    wl = W.make_workload(cfg)
+    p = wl.plan
+    dw = runner.upload(wl)
+    try:
+        outs = []
+        for off in (0, 1):
+            buf = torch.zeros(dw.q.numel() + 8, dtype=dw.q.dtype, device="cuda")
+            buf[off:off + dw.q.numel()] = dw.q.reshape(-1)
+            res = torch.zeros(dw.out.numel() + 8, dtype=dw.out.dtype, device="cuda")
+            pic.link_attn(dw.store, p.chunk_offsets, wl.link_ids(), p.q_offsets, None, hq,
+                          buf[off:], None, None, float(np.float32(cfg.scale)), res[off:],
+                          stream=torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            outs.append(res[off:off + dw.out.numel()].clone())
+            assert int((res[:off] != 0).sum()) == 0 and int((res[off + dw.out.numel():] != 0).sum()) == 0
+        assert torch.equal(outs[0], outs[1])
+    finally:
+        dw.close()
