@@ -896,8 +896,9 @@ constexpr int32_t kOwnInPlace = 128;
 // decode 5 us per wave (32 keys, eight waves per CU on the HBM stream),
 // stream kernel below. Partials move at about 4 TB/s, written and read; a
 // combine launch is about 4.5 us.
+// uneven_rows: some request has fewer row blocks than another.
 SplitCost split_cost(Kern kern, int32_t cus, const pic_store_desc &d, int32_t max_rows,
-                     const StreamShape &ss) {
+                     const StreamShape &ss, bool uneven_rows) {
   const double part_us = (d.d_v + 2) * 8.0 / 4e6;
   SplitCost c{};
   c.max_splits = 256;
@@ -928,14 +929,15 @@ SplitCost split_cost(Kern kern, int32_t cus, const pic_store_desc &d, int32_t ma
     const double cyc = d.dtype == PIC_F32 ? 32.0 * d.d_k * ss.rows / 16 : 22.0 * ss.rows;
     us = 2 * cyc / 2200.0 / ss.kpar;
     c.slots = 2 * (int64_t)cus;
-    // a round planned full to the last place runs over on some XCD, as row
-    // blocks of ragged requests stay empty (8 requests of 30..300 tokens,
-    // 32/8 heads x 64: 176 us full, 148 us with a twentieth left free)
-    c.fit = c.slots * 19 / 20;
     c.over = 6.0 / us;
     c.min_piece = 2 * ss.kpar;
   }
-  if (c.fit == 0) c.fit = c.slots;
+  // Where requests have different numbers of row blocks, the empty ones leave
+  // the XCDs and CUs unevenly filled, and a round planned full runs over on
+  // some of them: an eighth stays free (12 fp32 requests of 20..130 tokens:
+  // 77 us with a twentieth free, 64 us with a tenth or more; 8 bf16 requests
+  // of 30..300 tokens, 64-wide heads: 168 us full, 147 us).
+  c.fit = uneven_rows ? c.slots * 7 / 8 : c.slots;
   c.part = part_us / us;
   c.fixed = 4.5 / us;
   return c;
@@ -1120,11 +1122,13 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     std::vector<int32_t> tiles(B), blocks(B);
     std::vector<int64_t> rows(B);
     std::vector<double> share(B, 1.0);
+    bool uneven_rows = false;
     for (int r = 0; r < B; ++r) {
       const ReqEntry &R = P.reqs[r];
       tiles[r] = R.tiles * (kTile / C.tile_keys);
       blocks[r] = d.n_kv_heads * ((R.lq * lp.group + rows_per_block - 1) / rows_per_block);
       rows[r] = (int64_t)R.lq * n_q_heads;
+      uneven_rows |= blocks[r] != d.n_kv_heads * lp.nrb;
       // d128 row blocks end at the farthest limit of their rows: count the
       // part of the tiles they walk
       if (kern == Kern::Mfma128 && !P.doc_lim.empty() && R.ls == 0 && R.nlinks > 0) {
@@ -1137,7 +1141,7 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
       C.req_splits.assign(B, num_splits);
     else
       C.req_splits = choose_splits(tiles, blocks, rows, share,
-                                   split_cost(kern, s->shape.cus, d, P.max_rows, ss));
+                                   split_cost(kern, s->shape.cus, d, P.max_rows, ss, uneven_rows));
     apply_splits(s, n_q_heads, rows_per_block, C);
     return PIC_OK;
   }
