@@ -391,8 +391,9 @@ __global__ __launch_bounds__(kWaves * 64, 8 / kWaves) void link_mfma_d128_kernel
   int t_end = min(it.t_end, vis);
   // Per-query limits, documents only: nor does a tile past the farthest limit
   // of the block's rows (recomputed tokens see the rows up to their own
-  // position, so the row blocks of early tokens need few tiles).
-  if (kLim && R.ls == 0) t_end = limit_end(p, it, R.q0 + row0 / group,
+  // position, so the row blocks of early tokens need few tiles). Not for an
+  // empty piece (more pieces than tiles), which names no link to walk from.
+  if (kLim && R.ls == 0 && t_begin < t_end) t_end = limit_end(p, it, R.q0 + row0 / group,
                                            R.q0 + min(nrows - 1, row0 + kRows - 1) / group,
                                            c.lane, t_end);
 

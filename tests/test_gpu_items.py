@@ -139,6 +139,33 @@ def test_limited_row_blocks(pattern):
         dw.close()
 
 
+@pytest.mark.parametrize("splits", [2, 5, 100])
+@pytest.mark.parametrize("d", [64, 128])
+def test_limited_empty_pieces(d, splits):
+    """Cross-only decode calls with per-query limits cut into more pieces than
+    their requests have tiles (3, 1 and 11): the empty pieces, those of the
+    table's last link among them, walk no links."""
+    q = (16, 4, 9)
+    cfg = uneven("limited_empty", q, None, d_k=d, n_q_heads=8, n_kv_heads=2, decode=True)
+    wl = W.make_workload(cfg)
+    links = [[0, 1], [2], [3]]
+    idx = np.array([c for l in links for c in l], dtype=np.int64)
+    co = np.array([0, 2, 3, 4], np.int32)
+    lims = np.concatenate([np.linspace(0, sum(LENS[c] for c in l), n).astype(int)
+                           for l, n in zip(links, q)]).astype(np.int32)
+    dw = runner.upload(dataclasses.replace(wl, plan=dataclasses.replace(
+        wl.plan, chunk_offsets=co, chunk_index=idx)))
+    try:
+        out, lse = run_link(dw.store, cfg, co, wl.chunk_ids[idx], wl.plan.q_offsets, None, wl.q,
+                            None, None, lims=lims, decode=True, splits=splits)
+        ref, ref_lse = ref_link(cfg, [[dw.chunks[c] for c in l] for l in links], wl.q,
+                                wl.plan.q_offsets, lims=lims)
+        bad = G.failures(G.BF16, out, ref, lse, ref_lse)
+        assert not bad, bad
+    finally:
+        dw.close()
+
+
 @pytest.mark.parametrize("d,dtype,hq,q", [(128, W.BF16, 8, 40), (128, W.BF16, 8, 300),
                                           (64, W.BF16, 6, 70), (64, W.F32, 6, 70)])
 def test_unaligned_tensors(d, dtype, hq, q):
