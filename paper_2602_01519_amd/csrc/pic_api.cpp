@@ -1917,6 +1917,11 @@ pic_status pic_link_decode_noalloc(pic_store *s, const pic_link_req *req, int32_
                 "the call needs %zu bytes of scratch (tables, own KV, split partials); the static "
                 "scratch holds %zu", charge, kStaticScratchBytes);
   if (C.small) {
+    // What a given split count needs is what it is charged for; the stream
+    // kernel's own choice stays below it (fewer than 1024 workgroups of at
+    // most 128 rows x 66 or 64 x 130 floats: 35 MB).
+    if (C.part_bytes > kStaticScratchBytes)
+      return fail(PIC_ERR_INVALID, "the call's split partials exceed the static scratch");
     DeviceGuard dg(s->device);
     if (!dg.ok) return fail(PIC_ERR_HIP, "cannot select the store's device");
     void *base = nullptr;
