@@ -665,8 +665,8 @@ StreamShape stream_shape(int dtype, int d, int max_rows, bool small) {
 
 // Measured against the vector-ALU kernel these calls ran before (kernel time,
 // one MI355X): fp32 8/2 heads x 64, 12 ragged requests of 20..130 tokens over
-// 3..10 links 395 -> 99 us; bf16 32/8 x 64, 8 requests of 30..300 tokens
-// 3320 -> 190 us. At 512 tokens x 16 links x 1024, batch 4 (no ragged edges):
+// 3..10 links 395 -> 53 us; bf16 32/8 x 64, 8 requests of 30..300 tokens
+// 3320 -> 139 us. At 512 tokens x 16 links x 1024, batch 4 (no ragged edges):
 // bf16 d 64 584 TFLOP/s (876 with the second product of the lo parts), fp32
 // 109 TFLOP/s of the 154 a large library product reaches. Decode, 64 requests
 // x 16 links x 1024: bf16 5.9 TB/s, fp32 5.6 TB/s.
