@@ -15,6 +15,14 @@
 //   softmax against a running max that only moves when a score passes it by
 //   2^64 (fp32 keeps its relative precision at any such magnitude)
 //   O^T[D][16 rows] += V^T P^T
+// A wave whose sums come out beyond 2^115, infinite or NaN takes its rows
+// again one by one on the vector ALU (rows_alone): the max follows every key,
+// so probabilities stay at or below one and sums overflow only where the
+// values' own sums do, and a key that a row does not see adds nothing to it
+// whatever it holds (0 x infinity is NaN). Other calls pay one compare per sum
+// at the end of a piece; a max that follows every tile instead took 8 ragged
+// bf16 requests of 30..300 tokens from 148 to 176 us, 12 fp32 ones of 20..130
+// tokens from 65.1 to 67.1.
 // The scores a lane receives are the keys its operand of the value product
 // needs, so probabilities never leave its registers:
 //   fp32 (v_mfma_f32_16x16x4_f32): A lane l = (row l % 16, k-slot l / 16);
@@ -55,6 +63,9 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 constexpr int kT = 32;            // keys per tile
 constexpr int kWaves = 4;
 constexpr float kJump = 64.0f;    // log2: the running max moves past it
+// Sums up to this size stay finite when the parts of a workgroup and the
+// pieces of a request (at most 4 x 256) are added up.
+constexpr float kSafeSum = 0x1p115f;
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
@@ -359,8 +370,174 @@ __device__ __forceinline__ void store4<uint16_t>(uint16_t *out, float a, float b
   *(uint2 *)out = __builtin_bit_cast(uint2, v);
 }
 
+// max / sum over the 32 lanes of a half wave
+__device__ __forceinline__ float half_max(float x) {
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
+  return x;
+}
+__device__ __forceinline__ float half_sum(float x) {
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) x += __shfl_xor(x, o);
+  return x;
+}
+__device__ __forceinline__ float value_of(float x) { return x; }
+__device__ __forceinline__ float value_of(uint16_t x) { return __uint_as_float((uint32_t)x << 16); }
+
+// A workgroup's piece of work and a wave's part of it.
+struct Piece {
+  ReqEntry R;
+  Cursor cur;            // at the first tile (if there is one)
+  int part_row;          // first partial row of the piece, -1: not split
+  int nrows, wg_row0, row0;
+  int t_begin, t_end;    // the wave's tiles
+};
+
 // kSmall: a small call, whose tables are kernel arguments and whose own-KV
-// tiles are read in place (no prologue kernel before it).
+// tiles are read in place (no prologue kernel before it). False: no such
+// piece. kR: rows per wave.
+template <bool kSmall, int kR>
+__device__ __forceinline__ bool piece_of(const LinkParams &p, const_links links, const_reqs reqs,
+                                         const_ints order, int block, int wave, int lane,
+                                         Piece &w) {
+  const int units = p.n_kv_heads * (kSmall ? p.batch * p.num_splits : p.n_items);
+  const UnitBlock ub = unit_of_block(block, p.nrb, p.n_xcd, p.spread, units);
+  if (ub.u >= units) return false;
+  int p_begin = 0, p_end = 0;   // the piece, in 32-key tiles
+  ReqEntry &R = w.R;
+  Cursor &cur = w.cur;
+  w.part_row = -1;
+  if constexpr (kSmall) {
+    const int grp = ub.u / p.num_splits, split = ub.u % p.num_splits;
+    cur.kvh = grp % p.n_kv_heads;
+    const_reqs rq = reqs + order[grp / p.n_kv_heads];
+    R.link0 = rq->link0;
+    R.nlinks = rq->nlinks;
+    R.q0 = rq->q0;
+    R.lq = rq->lq;
+    R.s0 = rq->s0;
+    R.ls = rq->ls;
+    R.doc_tiles = rq->doc_tiles;
+    R.tiles = rq->tiles;
+    p_begin = (int)((int64_t)2 * R.tiles * split / p.num_splits);
+    p_end = (int)((int64_t)2 * R.tiles * (split + 1) / p.num_splits);
+    if (p.num_splits > 1) w.part_row = (split * p.total_q + R.q0) * p.n_q_heads;
+    cur.links = links + R.link0;
+  } else {
+    const WorkItem it = load_item(p.items, ub.u / p.n_kv_heads);
+    cur.kvh = ub.u % p.n_kv_heads;
+    R = item_request(it);
+    p_begin = it.t_begin;
+    p_end = it.t_end;
+    w.part_row = it.part;
+    cur.links = links + it.link;
+    cur.li = 0;
+    cursor_set(cur, it.k, it.v, it.len, it.lp, it.tile0, it.tok0);
+  }
+  cur.doc_tiles = 2 * R.doc_tiles;
+  const int kpar = p.kpar;
+  w.nrows = R.lq * p.group;
+  w.wg_row0 = ub.rb * (kWaves / kpar) * kR;
+  if (w.wg_row0 >= w.nrows) return false;
+  w.row0 = w.wg_row0 + (wave / kpar) * kR;
+
+  // the piece's tiles up to the last own key the wave's last row sees, cut
+  // into kpar parts
+  w.t_begin = w.t_end = 0;
+  if (w.row0 < w.nrows) {
+    const int own_last = min(w.nrows - 1, w.row0 + kR - 1) / p.group + R.ls - R.lq;
+    const int vis = own_last >= 0 ? min(2 * R.tiles, 2 * R.doc_tiles + own_last / kT + 1)
+                                  : 2 * R.doc_tiles;
+    const int n = max(0, min(p_end, vis) - p_begin), part = wave % kpar;
+    w.t_begin = p_begin + n * part / kpar;
+    w.t_end = p_begin + n * (part + 1) / kpar;
+  }
+  if constexpr (kSmall)
+    if (w.t_begin < w.t_end) {
+      cur.li = seek_link(cur.links, R.nlinks, w.t_begin / (kTile / kT), lane);
+      cursor_load(cur);
+    }
+  return true;
+}
+
+// The own rows of a small call's request, for one kv head.
+template <typename T, int D>
+__device__ __forceinline__ OwnRows own_rows(const LinkParams &p, const ReqEntry &R, int kvh) {
+  OwnRows own{};
+  if (R.ls > 0) {
+    const int64_t at = ((int64_t)R.s0 * p.n_kv_heads + kvh) * D * (int)sizeof(T);
+    own.k = (const char *)p.k_self + at;
+    own.v = (const char *)p.v_self + at;
+    own.stride = (int64_t)p.n_kv_heads * D * sizeof(T);
+    own.last = R.ls - 1;
+  }
+  return own;
+}
+
+// A wave's rows over its tiles, one row at a time: (m, l, O) of row i to sm[i],
+// sl[i], so[i * stride + dim]. Lane l takes key l % 32 of
+// a tile and half of its head dims for the scores, value dims l and l + 64 for
+// the sums, which run over the keys the row sees and no others.
+template <typename T, int D, bool kSmall>
+__device__ __forceinline__ void rows_alone(const LinkParams &p, const Piece &w, int rows,
+                                           int lane, float *so, int stride, float *sm,
+                                           float *sl) {
+  const ReqEntry &R = w.R;
+  const OwnRows own = own_rows<T, D>(p, R, w.cur.kvh);
+  constexpr int kDims = D > 64 ? 2 : 1;
+  const int key = lane & 31, half = lane >> 5;
+  const int dim = D < 64 ? lane % D : lane;
+#pragma unroll 1
+  for (int i = 0; i < min(rows, w.nrows - w.row0); ++i) {
+    const int row = w.row0 + i, qi = row / p.group;
+    const int qh = w.cur.kvh * p.group + row % p.group;
+    const int lim = qi + R.ls - R.lq;
+    const int dl = p.doc_lim ? p.doc_lim[R.q0 + qi] : kNoLimit;
+    const T *q = (const T *)p.q + ((int64_t)(R.q0 + qi) * p.n_q_heads + qh) * D + half * (D / 2);
+    float m = -INFINITY, l = 0.f, o[kDims];
+#pragma unroll
+    for (int j = 0; j < kDims; ++j) o[j] = 0.f;
+    Cursor cur = w.cur;
+#pragma unroll 1
+    for (int t = w.t_begin; t < w.t_end; ++t) {
+      const TileInfo x = tile_info<T, D>(cur, t);
+      const int last = x.own ? min(lim - x.j0, x.nvalid - 1) : min(dl - x.tok, x.nvalid) - 1;
+      if (last < 0) continue;
+      const bool place = kSmall && x.own;
+      const T *k = place ? (const T *)(own.k + min(x.j0 + key, own.last) * own.stride)
+                         : (const T *)x.k + key * D;
+      k += half * (D / 2);
+      float s = 0.f;
+#pragma unroll 4
+      for (int e = 0; e < D / 2; ++e) s += value_of(q[e]) * value_of(k[e]);
+      s += __shfl_xor(s, 32);
+      s = key <= last ? s * p.scale_log2 : -INFINITY;
+      const float mnew = fmaxf(m, half_max(s));
+      const float base = mnew == -INFINITY ? 0.f : mnew;
+      const float pr = key <= last ? exp2f(s - base) : 0.f;
+      const float alpha = exp2f(m - base);
+      l = l * alpha + half_sum(pr);
+      m = mnew;
+#pragma unroll
+      for (int j = 0; j < kDims; ++j) {
+        const int e = dim + 64 * j;
+        const T *v = place ? (const T *)(own.v + x.j0 * own.stride) + e : (const T *)x.v + e * kT;
+        const int64_t step = place ? own.stride / (int)sizeof(T) : 1;
+        float a = o[j] * alpha;
+        for (int kk = 0; kk <= last; ++kk) a += __shfl(pr, kk) * value_of(v[kk * step]);
+        o[j] = a;
+      }
+    }
+    if (D >= 64 || lane < D)
+#pragma unroll
+      for (int j = 0; j < kDims; ++j) so[i * stride + dim + 64 * j] = o[j];
+    if (lane == 0) {
+      sm[i] = m;
+      sl[i] = l;
+    }
+  }
+}
+
 template <typename T, int D, int CB, bool kSmall>
 __device__ __forceinline__ void stream_body(const LinkParams &p, const_links links,
                                             const_reqs reqs, const_ints order) {
@@ -374,58 +551,13 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
   const int wave = uni(threadIdx.x >> 6);
   const int lr = lane & 15, lg = lane >> 4;
 
-  const int units = p.n_kv_heads * (kSmall ? p.batch * p.num_splits : p.n_items);
-  const UnitBlock ub = unit_of_block(blockIdx.x, p.nrb, p.n_xcd, p.spread, units);
-  const int rb = ub.rb;
-  if (ub.u >= units) return;
-  int kvh, part_row = -1, p_begin = 0, p_end = 0;   // the piece, in 32-key tiles
-  ReqEntry R{};
-  Cursor cur;
-  if constexpr (kSmall) {
-    const int grp = ub.u / p.num_splits, split = ub.u % p.num_splits;
-    kvh = grp % p.n_kv_heads;
-    const_reqs rq = reqs + order[grp / p.n_kv_heads];
-    R.link0 = rq->link0;
-    R.nlinks = rq->nlinks;
-    R.q0 = rq->q0;
-    R.lq = rq->lq;
-    R.s0 = rq->s0;
-    R.ls = rq->ls;
-    R.doc_tiles = rq->doc_tiles;
-    R.tiles = rq->tiles;
-    p_begin = (int)((int64_t)2 * R.tiles * split / p.num_splits);
-    p_end = (int)((int64_t)2 * R.tiles * (split + 1) / p.num_splits);
-    if (p.num_splits > 1) part_row = (split * p.total_q + R.q0) * p.n_q_heads;
-    cur.links = links + R.link0;
-  } else {
-    const WorkItem it = load_item(p.items, ub.u / p.n_kv_heads);
-    kvh = ub.u % p.n_kv_heads;
-    R = item_request(it);
-    p_begin = it.t_begin;
-    p_end = it.t_end;
-    part_row = it.part;
-    cur.links = links + it.link;
-    cur.li = 0;
-    cursor_set(cur, it.k, it.v, it.len, it.lp, it.tile0, it.tok0);
-  }
-  const int group = p.group, kpar = p.kpar;
-  const int nrows = R.lq * group;
-  const int wg_row0 = rb * (kWaves / kpar) * kR;
-  if (wg_row0 >= nrows) return;
-  const int row0 = wg_row0 + (wave / kpar) * kR;
-  const bool active = row0 < nrows;
-
-  // the piece's tiles up to the last own key the wave's last row sees, cut
-  // into kpar parts
-  int t_begin = 0, t_end = 0;
-  if (active) {
-    const int own_last = min(nrows - 1, row0 + kR - 1) / group + R.ls - R.lq;
-    const int vis = own_last >= 0 ? min(2 * R.tiles, 2 * R.doc_tiles + own_last / kT + 1)
-                                  : 2 * R.doc_tiles;
-    const int n = max(0, min(p_end, vis) - p_begin), part = wave % kpar;
-    t_begin = p_begin + n * part / kpar;
-    t_end = p_begin + n * (part + 1) / kpar;
-  }
+  Piece w;
+  if (!piece_of<kSmall, kR>(p, links, reqs, order, blockIdx.x, wave, lane, w)) return;
+  const ReqEntry &R = w.R;
+  Cursor &cur = w.cur;
+  const int group = p.group, kpar = p.kpar, kvh = cur.kvh, part_row = w.part_row;
+  const int nrows = w.nrows, wg_row0 = w.wg_row0, row0 = w.row0;
+  const int t_begin = w.t_begin, t_end = w.t_end;
 
   int lim[CB], dl[CB], wmin = kNoLimit;
   int64_t orow[CB];
@@ -449,20 +581,11 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
     wmin = kNoLimit;
   }
 
-  cur.kvh = kvh;
-  cur.doc_tiles = 2 * R.doc_tiles;
   const uint32_t koff =
       (uint32_t)((S::F32 ? lr : 8 * (lr >> 2) + (lr & 3)) * D * (int)sizeof(T) + 16 * lg);
   const uint32_t voff = (uint32_t)(lr * kT * (int)sizeof(T) + 16 * lg);
 
-  OwnRows own{};
-  if (kSmall && R.ls > 0) {
-    const int64_t at = ((int64_t)R.s0 * p.n_kv_heads + kvh) * D * (int)sizeof(T);
-    own.k = (const char *)p.k_self + at;
-    own.v = (const char *)p.v_self + at;
-    own.stride = (int64_t)p.n_kv_heads * D * sizeof(T);
-    own.last = R.ls - 1;
-  }
+  const OwnRows own = kSmall ? own_rows<T, D>(p, R, kvh) : OwnRows{};
   Tile<T, D> ta, tb;
   TileInfo ia{}, ib{};
   auto load = [&](int t, bool live, TileInfo &i, Tile<T, D> &x) {
@@ -472,13 +595,7 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
     else
       load_tile<T, D>(i, kSmall || live ? koff : 0, kSmall || live ? voff : 0, x);
   };
-  if (t_begin < t_end) {
-    if constexpr (kSmall) {
-      cur.li = seek_link(cur.links, R.nlinks, t_begin / (kTile / kT), lane);
-      cursor_load(cur);
-    }
-    load(t_begin, true, ia, ta);
-  }
+  if (t_begin < t_end) load(t_begin, true, ia, ta);
   uint4 qf[CB][S::KU];
 #pragma unroll
   for (int c = 0; c < CB; ++c) {
@@ -515,7 +632,24 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
   float ltot[CB];
 #pragma unroll
   for (int c = 0; c < CB; ++c) ltot[c] = col_sum(st.l[c]);
-  if (kpar == 1) {
+  bool alone = false;
+#pragma unroll
+  for (int c = 0; c < CB; ++c)
+#pragma unroll
+    for (int b = 0; b < S::NB; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) alone |= !(fabsf(st.o[c][b][i]) <= kSafeSum);
+  const bool redo = __builtin_expect(__any(alone), 0);
+  if (redo) {
+    // the piece anew: kept over the loop above, it would cost it registers
+    int block = blockIdx.x;
+    asm volatile("" : "+s"(block));
+    Piece again;
+    if (piece_of<kSmall, kR>(p, links, reqs, order, block, wave, lane, again))
+      rows_alone<T, D, kSmall>(p, again, kR, lane, so[wave], kOS, sm[wave], sl[wave]);
+    __builtin_amdgcn_wave_barrier();     // its lanes read each other's sums below
+  }
+  if (kpar == 1 && !redo) {
     // each lane holds 4 consecutive value dims of its rows
 #pragma unroll
     for (int c = 0; c < CB; ++c) {
@@ -544,55 +678,66 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
     }
     return;
   }
-  // merge the kpar parts of every row block through LDS
-#pragma unroll
-  for (int c = 0; c < CB; ++c) {
-    float *o = &so[wave][(16 * c + lr) * kOS + 4 * lg];
-#pragma unroll
-    for (int b = 0; b < S::NB; ++b)
-      store4<float>(o + 16 * b, st.o[c][b][0], st.o[c][b][1], st.o[c][b][2], st.o[c][b][3]);
-    if (lg == 0) {
-      sm[wave][16 * c + lr] = ltot[c] > 0.f ? st.m[c] : -INFINITY;
-      sl[wave][16 * c + lr] = ltot[c];
+  // (m, l, O) of rows in LDS to out or the partials: units of 4 value dims idx,
+  // idx + step ... of n rows from row `begin` on, the sum of `parts` waves' from
+  // wave0 on.
+  auto write_rows = [&](int idx, int step, int n, int begin, int wave0, int parts) {
+    constexpr int kQ = D / 4;                      // 4-wide units per row
+    for (; idx < n * kQ; idx += step) {
+      const int rr = idx / kQ, e = idx % kQ * 4;
+      const int row = begin + rr;
+      if (row >= nrows) break;                     // later units are later rows
+      const int w0 = wave0 + rr / kR * parts, rl = rr % kR;
+      float M = -INFINITY;
+      for (int w = 0; w < parts; ++w) M = fmaxf(M, sm[w0 + w][rl]);
+      float L = 0.f;
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int w = 0; w < parts; ++w) {
+        const float mw = sm[w0 + w][rl];
+        const float wt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
+        const float4 v = *(const float4 *)&so[w0 + w][rl * kOS + e];
+        L += wt * sl[w0 + w][rl];
+        a.x += wt * v.x;
+        a.y += wt * v.y;
+        a.z += wt * v.z;
+        a.w += wt * v.w;
+      }
+      const int64_t orw = (int64_t)(R.q0 + row / group) * p.n_q_heads + kvh * group + row % group;
+      if (part_row < 0) {
+        const float inv = L > 0.f ? 1.f / L : 0.f;
+        store4<T>((T *)p.out + orw * D + e, a.x * inv, a.y * inv, a.z * inv, a.w * inv);
+        if (p.lse && e == 0)
+          p.lse[orw] = L > 0.f ? (M + log2f(L)) * 0.69314718055994531f : -INFINITY;
+      } else {
+        const int64_t prow = part0 + orw;
+        store4<float>(p.part_o + prow * D + e, a.x, a.y, a.z, a.w);
+        if (e == 0) {
+          p.part_m[prow] = M;
+          p.part_l[prow] = L;
+        }
+      }
     }
+  };
+  if (kpar == 1) {
+    write_rows(lane, 64, kR, row0, wave, 1);
+    return;
   }
-  __syncthreads();
-  constexpr int kQ = D / 4;                      // 4-wide units per row
-  const int rows = (kWaves / kpar) * kR;
-  for (int idx = threadIdx.x; idx < rows * kQ; idx += 64 * kWaves) {
-    const int rr = idx / kQ, e = idx % kQ * 4;
-    const int row = wg_row0 + rr;
-    if (row >= nrows) break;                     // later units are later rows
-    const int w0 = rr / kR * kpar, rl = rr % kR;
-    float M = -INFINITY;
-    for (int w = 0; w < kpar; ++w) M = fmaxf(M, sm[w0 + w][rl]);
-    float L = 0.f;
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int w = 0; w < kpar; ++w) {
-      const float mw = sm[w0 + w][rl];
-      const float wt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
-      const float4 v = *(const float4 *)&so[w0 + w][rl * kOS + e];
-      L += wt * sl[w0 + w][rl];
-      a.x += wt * v.x;
-      a.y += wt * v.y;
-      a.z += wt * v.z;
-      a.w += wt * v.w;
-    }
-    const int64_t orw = (int64_t)(R.q0 + row / group) * p.n_q_heads + kvh * group + row % group;
-    if (part_row < 0) {
-      const float inv = L > 0.f ? 1.f / L : 0.f;
-      store4<T>((T *)p.out + orw * D + e, a.x * inv, a.y * inv, a.z * inv, a.w * inv);
-      if (p.lse && e == 0)
-        p.lse[orw] = L > 0.f ? (M + log2f(L)) * 0.69314718055994531f : -INFINITY;
-    } else {
-      const int64_t prow = part0 + orw;
-      store4<float>(p.part_o + prow * D + e, a.x, a.y, a.z, a.w);
-      if (e == 0) {
-        p.part_m[prow] = M;
-        p.part_l[prow] = L;
+  // merge the kpar parts of every row block through LDS
+  if (!redo) {
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      float *o = &so[wave][(16 * c + lr) * kOS + 4 * lg];
+#pragma unroll
+      for (int b = 0; b < S::NB; ++b)
+        store4<float>(o + 16 * b, st.o[c][b][0], st.o[c][b][1], st.o[c][b][2], st.o[c][b][3]);
+      if (lg == 0) {
+        sm[wave][16 * c + lr] = ltot[c] > 0.f ? st.m[c] : -INFINITY;
+        sl[wave][16 * c + lr] = ltot[c];
       }
     }
   }
+  __syncthreads();
+  write_rows(threadIdx.x, 64 * kWaves, (kWaves / kpar) * kR, wg_row0, 0, kpar);
 }
 
 // Two waves per SIMD, one for the widest fp32 heads (two tiles in flight of

@@ -1,0 +1,177 @@
+"""Values at the ends of the fp32 range, and infinities and NaN in the caches.
+
+The streaming kernel of fp32 and narrow bf16 GQA calls keeps its probabilities
+at or below one, so sums of values stay finite as long as the values' own sums
+do; keys a query row does not see (rows past a limit that cuts a link inside a
+page, own keys after the row's token) do not reach its output, whatever they
+hold; a visible infinite value gives an infinite output."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_01519_amd import pic, runner
+from paper_2602_01519_amd import workloads as W
+
+from test_gpu_blend import ref_link, run_link, stream as cur_stream
+
+pytestmark = pytest.mark.gpu
+
+# the streaming kernel's shapes (a group of 3 keeps small calls off the lean kernel)
+STREAM = [(W.F32, 32), (W.F32, 64), (W.F32, 128), (W.BF16, 32), (W.BF16, 64)]
+
+
+def narrow(dtype, d, lens, batch, q, own, decode=False, hq=6):
+    return W.small_config("range", dtype=dtype, d_k=d, n_q_heads=hq, n_kv_heads=2, chunk_lens=lens,
+                          batch=batch, links=(0, 0), q_len=q, self_len=own, decode=decode)
+
+
+def to_store(cfg, x):
+    """fp32 host array in the store's dtype."""
+    return W.f32_to_bf16_bits(x) if x is not None and cfg.dtype == W.BF16 else x
+
+
+def run_calls(cfg, calls, links, q, lims=None, splits=0):
+    """Outputs of one call per chunk set in `calls` (each a list of fp32 (k, v, n)), all with
+    the same links (chunk numbers per request) and query."""
+    co = np.cumsum([0] + [len(l) for l in links]).astype(np.int32)
+    ids = np.array([1 + c for l in links for c in l], np.uint64)
+    n = q.shape[0] // len(links)
+    qo = (np.arange(len(links) + 1) * n).astype(np.int32)
+    res = []
+    for chunks, own in calls:
+        store = pic.Store(cfg.kind, cfg.dtype, cfg.n_kv_heads, cfg.d_k, cfg.d_v,
+                          sum((len(k) + 63) // 64 * 64 for k, _ in chunks))
+        try:
+            for i, (k, v) in enumerate(chunks):
+                store.put(1 + i, len(k), runner.to_device(to_store(cfg, k), "cuda"),
+                          None if v is None else runner.to_device(to_store(cfg, v), "cuda"),
+                          cur_stream())
+            so = None
+            if own is not None:
+                m = own[0].shape[0] // len(links)
+                so = (np.arange(len(links) + 1) * m).astype(np.int32)
+            res.append(run_link(store, cfg, co, ids, qo, so, to_store(cfg, q),
+                                None if own is None else to_store(cfg, own[0]),
+                                None if own is None else to_store(cfg, own[1]), lims=lims,
+                                decode=cfg.decode, splits=splits))
+        finally:
+            store.close()
+    return res
+
+
+def normal(rng, *shape):
+    return rng.standard_normal(shape, dtype=np.float32)
+
+
+@pytest.mark.parametrize("batch,splits", [(1, None), (9, None), (1, 0), (9, 3)])
+@pytest.mark.parametrize("dtype,d", STREAM)
+def test_large_values_stay_finite(dtype, d, batch, splits):
+    """Scores that grow by 2^29 from chunk to chunk (20 in natural logs) beside
+    values of size 2^110: a probability above one would overflow their sums."""
+    rng = np.random.default_rng(d + batch)
+    q_len = 2 if splits is not None else 21
+    lens = (70, 90, 333)
+    cfg = narrow(dtype, d, lens, batch, (q_len,) * batch, None, decode=splits is not None)
+    q = 1 + np.float32(0.1) * normal(rng, batch * q_len, 6, d)
+    chunks = []
+    for i, n in enumerate(lens):
+        k = np.float32(0.1) * normal(rng, n, 2, d) + np.float32(10 * i / (cfg.scale * d))
+        chunks.append((k, np.float32(2.0 ** 110) * normal(rng, n, 2, d)))
+    links = [[0, 1, 2]] * batch
+    (out, lse), = run_calls(cfg, [(chunks, None)], links, q, splits=splits or 0)
+    unit = [(to_store(cfg, k), to_store(cfg, v * np.float32(2.0 ** -110))) for k, v in chunks]
+    qo = (np.arange(batch + 1) * q_len).astype(np.int32)
+    ref, ref_lse = ref_link(cfg, [[unit[c] for c in l] for l in links], to_store(cfg, q), qo)
+    assert np.isfinite(out).all()
+    # a score of size 20 carries fp32 rounding of some 2^-24 x 20, the output the same
+    bad = np.linalg.norm(out * 2.0 ** -110 - ref) / np.linalg.norm(ref)
+    assert bad <= (2.0 ** -7 if dtype == W.BF16 else 64 * 2.0 ** -24 * 20), bad
+    assert np.abs(lse - ref_lse).max() <= 64 * 2.0 ** -24 * 20
+
+
+def same(cfg, a, b, sel=np.s_[:]):
+    """Results of the same sums in another order: fp32 sums of some hundred
+    terms, rounded to the store's type."""
+    tol = 2.0 ** -8 if cfg.dtype == W.BF16 else 2e-6
+    (x, lx), (y, ly) = (a[0][sel], a[1][sel]), (b[0][sel], b[1][sel])
+    assert np.isfinite(x).all() and np.isfinite(y).all()
+    assert np.linalg.norm(x - y) <= tol * np.linalg.norm(y)
+    assert np.abs(lx - ly).max() <= 1e-5
+
+
+BAD = [math.inf, -math.inf, math.nan]
+
+
+def spoil(a, rows):
+    """A copy of a with the given rows full of infinities and NaN."""
+    b = a.copy()
+    for i, r in enumerate(rows):
+        b[r] = BAD[i % 3]
+    return b
+
+
+@pytest.mark.parametrize("form", ["small", "items", "decode"])
+@pytest.mark.parametrize("dtype,d", STREAM)
+def test_rows_past_a_uniform_limit(dtype, d, form):
+    """Every query row sees 100 of a chunk's 200 rows: the link is cut inside a
+    page, whose other rows hold infinities and NaN."""
+    rng = np.random.default_rng(d)
+    batch, q_len = (9, 7) if form == "items" else (1, 2 if form == "decode" else 30)
+    cfg = narrow(dtype, d, (64, 200), batch, (q_len,) * batch, None, decode=form == "decode")
+    q = normal(rng, batch * q_len, 6, d) * np.float32(cfg.q_std)
+    first = (normal(rng, 64, 2, d), normal(rng, 64, 2, d))
+    k, v = normal(rng, 200, 2, d), normal(rng, 200, 2, d)
+    lims = np.full(batch * q_len, 164, np.int32)
+    hidden = range(100, 200)
+    clean, dirty = run_calls(cfg, [([first, (k, v)], None),
+                                   ([first, (spoil(k, hidden), spoil(v, hidden))], None)],
+                             [[0, 1]] * batch, q, lims=lims)
+    same(cfg, dirty, clean)
+
+
+@pytest.mark.parametrize("batch", [1, 9])
+@pytest.mark.parametrize("dtype,d", STREAM)
+def test_keys_hidden_from_some_rows(dtype, d, batch):
+    """Own keys after a row's token, and linked rows past its own limit, hold
+    infinities and NaN: the rows that do not see them keep their result."""
+    rng = np.random.default_rng(d + 7)
+    n = 130
+    cfg = narrow(dtype, d, (64, 200), batch, (n,) * batch, (n,) * batch)
+    q = normal(rng, batch * n, 6, d) * np.float32(cfg.q_std)
+    chunks = [(normal(rng, 64, 2, d), normal(rng, 64, 2, d)),
+              (normal(rng, 200, 2, d), normal(rng, 200, 2, d))]
+    ks, vs = normal(rng, batch * n, 2, d), normal(rng, batch * n, 2, d)
+    late = [r * n + t for r in range(batch) for t in range(100, n)]
+    clean, dirty = run_calls(cfg, [(chunks, (ks, vs)), (chunks, (spoil(ks, late), spoil(vs, late)))],
+                             [[0, 1]] * batch, q)
+    see = np.arange(batch * n) % n < 100
+    same(cfg, dirty, clean, see)
+    # linked rows: the second chunk's rows 70.. are seen by every third row only
+    lims = np.where(np.arange(batch * n) % 3 == 0, 264, 134).astype(np.int32)
+    cross = narrow(dtype, d, (64, 200), batch, (n,) * batch, None)
+    bad = (chunks[1][0], spoil(chunks[1][1], range(70, 200)))
+    clean, dirty = run_calls(cross, [(chunks, None), ([chunks[0], bad], None)], [[0, 1]] * batch, q,
+                             lims=lims)
+    same(cfg, dirty, clean, lims == 134)
+
+
+@pytest.mark.parametrize("batch", [1, 9])
+@pytest.mark.parametrize("dtype,d", STREAM)
+def test_visible_infinite_value(dtype, d, batch):
+    """One infinite value seen by every row: its dim is infinite, the others
+    keep their result."""
+    rng = np.random.default_rng(d + 8)
+    cfg = narrow(dtype, d, (64, 200), batch, (20,) * batch, (20,) * batch)
+    q = normal(rng, batch * 20, 6, d) * np.float32(cfg.q_std)
+    chunks = [(normal(rng, 64, 2, d), normal(rng, 64, 2, d)),
+              (normal(rng, 200, 2, d), normal(rng, 200, 2, d))]
+    own = (normal(rng, batch * 20, 2, d), normal(rng, batch * 20, 2, d))
+    v = chunks[1][1].copy()
+    v[33, :, 5] = math.inf
+    clean, dirty = run_calls(cfg, [(chunks, own), ([chunks[0], (chunks[1][0], v)], own)],
+                             [[0, 1]] * batch, q)
+    assert (dirty[0][:, :, 5] == math.inf).all()
+    rest = np.arange(d) != 5
+    same(cfg, (dirty[0][:, :, rest], dirty[1]), (clean[0][:, :, rest], clean[1]))
