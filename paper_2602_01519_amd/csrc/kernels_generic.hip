@@ -881,17 +881,23 @@ __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
 #pragma unroll
     for (int i = 0; i < kB; ++i) {
       const int si = s0 + i * kGpr;
-      const int64_t pr = (int64_t)min(si, S - 1) * rows + prow;   // past the last: reread it, weight 0
+      // past the last: its maximum reread, zeros for its values (weight 0 x an
+      // infinite sum is NaN)
+      const int64_t pr = (int64_t)min(si, S - 1) * rows + prow;
       mb[i] = p.part_m[pr];
       lb[i] = p.part_l[pr];
       const float *po = p.part_o + pr * dv;
 #pragma unroll
       for (int c = 0; c < kChunks; ++c) {
         const int e = 4 * (kLanes * c + lane);
-        vb[i][c] = e < dv && (!kSkip || mb[i] != -INFINITY) ? *(const float4 *)(po + e)
-                                                            : make_float4(0.f, 0.f, 0.f, 0.f);
+        vb[i][c] = e < dv && si < S && (!kSkip || mb[i] != -INFINITY)
+                       ? *(const float4 *)(po + e)
+                       : make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      if (si >= S) mb[i] = -INFINITY;
+      if (si >= S) {
+        mb[i] = -INFINITY;
+        lb[i] = 0.f;
+      }
     }
     float bm = M;
 #pragma unroll

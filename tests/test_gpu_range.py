@@ -175,3 +175,20 @@ def test_visible_infinite_value(dtype, d, batch):
     assert (dirty[0][:, :, 5] == math.inf).all()
     rest = np.arange(d) != 5
     same(cfg, (dirty[0][:, :, rest], dirty[1]), (clean[0][:, :, rest], clean[1]))
+
+
+@pytest.mark.parametrize("splits", [2, 3, 5, 6, 9, 21, 30])
+def test_infinite_value_in_the_last_piece(splits):
+    """Split counts that leave the combine's last group of pieces part empty: an
+    infinite sum of the last piece stays infinite."""
+    rng = np.random.default_rng(splits)
+    cfg = narrow(W.BF16, 128, (640, 1300), 1, (2,), None, decode=True)
+    q = normal(rng, 2, 6, 128) * np.float32(cfg.q_std)
+    chunks = [(normal(rng, n, 2, 128), normal(rng, n, 2, 128)) for n in (640, 1300)]
+    v = chunks[1][1].copy()
+    v[1299, :, 5] = math.inf
+    clean, dirty = run_calls(cfg, [(chunks, None), ([chunks[0], (chunks[1][0], v)], None)],
+                             [[0, 1]], q, splits=splits)
+    assert (dirty[0][:, :, 5] == math.inf).all()
+    rest = np.arange(128) != 5
+    assert np.array_equal(clean[0][:, :, rest], dirty[0][:, :, rest])
