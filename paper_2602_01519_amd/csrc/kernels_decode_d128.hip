@@ -136,7 +136,9 @@ __device__ __forceinline__ void load_tile(const TileInfo &r, int lane, bool live
 
 // Own-KV tile read in place: keys j0 .. of the request's token-major own rows
 // (k, v: its first own row, kv head applied; stride: bytes per token). Keys
-// past the last own one reread it; they are masked.
+// past the last own one reread it: their scores are masked, and their values
+// are zeros here, since the last key's would turn an infinite sum into NaN
+// (0 x infinity).
 __device__ __forceinline__ void load_own(const char *k, const char *v, int64_t stride, int j0,
                                          int last, int lane, Tile &x) {
   const int grp = lane >> 4, m = lane & 15;
@@ -153,9 +155,11 @@ __device__ __forceinline__ void load_own(const char *k, const char *v, int64_t s
     for (int i = 0; i < 4; ++i) w[b][i] = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const uint16_t *row = (const uint16_t *)(v + min(j0 + 8 * grp + i, last) * stride) + m;
+    const int key = j0 + 8 * grp + i;
+    const uint16_t *row = (const uint16_t *)(v + min(key, last) * stride) + m;
+    const uint32_t keep = key <= last ? 0xffffu : 0u;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) w[b][i >> 1] |= (uint32_t)row[16 * b] << (16 * (i & 1));
+    for (int b = 0; b < 8; ++b) w[b][i >> 1] |= (row[16 * b] & keep) << (16 * (i & 1));
   }
 #pragma unroll
   for (int b = 0; b < 8; ++b) x.v[b] = make_uint4(w[b][0], w[b][1], w[b][2], w[b][3]);

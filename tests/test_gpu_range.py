@@ -192,3 +192,20 @@ def test_infinite_value_in_the_last_piece(splits):
     assert (dirty[0][:, :, 5] == math.inf).all()
     rest = np.arange(128) != 5
     assert np.array_equal(clean[0][:, :, rest], dirty[0][:, :, rest])
+
+
+@pytest.mark.parametrize("own", [1, 5, 40])
+def test_decode_last_own_value_infinite(own):
+    """The decode kernel's in-place own tile reads past the last own key as that
+    key again, masked: an infinite value of it stays infinite."""
+    rng = np.random.default_rng(own)
+    cfg = narrow(W.BF16, 128, (64, 200), 1, (1,), (own,), decode=True)
+    q = normal(rng, 1, 6, 128) * np.float32(cfg.q_std)
+    chunks = [(normal(rng, n, 2, 128), normal(rng, n, 2, 128)) for n in (64, 200)]
+    ks, vs = normal(rng, own, 2, 128), normal(rng, own, 2, 128)
+    bad = vs.copy()
+    bad[own - 1, :, 5] = math.inf
+    clean, dirty = run_calls(cfg, [(chunks, (ks, vs)), (chunks, (ks, bad))], [[0, 1]], q)
+    assert (dirty[0][:, :, 5] == math.inf).all()
+    rest = np.arange(128) != 5
+    assert np.array_equal(clean[0][:, :, rest], dirty[0][:, :, rest])
