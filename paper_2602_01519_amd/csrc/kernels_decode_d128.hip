@@ -323,7 +323,7 @@ __global__ __launch_bounds__(256, 2) void link_decode_d128_kernel(LinkParams p) 
     for (int b = 0; b < 8; ++b)
       *(float4 *)(po + 16 * b + r4) = make_float4(st.o[b][0], st.o[b][1], st.o[b][2], st.o[b][3]);
     if (lane < 16) {
-      p.part_m[prow] = ltot > 0.f ? st.m : -INFINITY;
+      p.part_m[prow] = partial_max(st.m, ltot);
       p.part_l[prow] = ltot;
     }
   }

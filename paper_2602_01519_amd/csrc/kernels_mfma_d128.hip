@@ -561,10 +561,10 @@ __global__ __launch_bounds__(kWaves * 64, 8 / kWaves) void link_mfma_d128_kernel
   } else {
     const int64_t prow = it.part + (orow - (int64_t)R.q0 * p.n_q_heads);
     // (with limits, the combine reads no values where m is -inf)
-    if (!kLim || __any(ltot > 0.f))
+    if (!kLim || __any(!(ltot == 0.f)))
       store_block_f32(a.o[0], a.o[1], a.o[2], a.o[3], sb, c.lane, nvalid, (int)prow, p.part_o, kD);
     if (rvalid && c.g == 0) {
-      p.part_m[prow] = ltot > 0.f ? a.m_used : -INFINITY;
+      p.part_m[prow] = partial_max(a.m_used, ltot);
       p.part_l[prow] = ltot;
     }
   }

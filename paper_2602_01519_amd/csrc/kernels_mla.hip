@@ -487,7 +487,7 @@ __global__ __launch_bounds__(256, 1) void link_mla_kernel(LinkParams p) {
       store_block_f32(o[0][rb], o[1][rb], o[2][rb], o[3][rb], sb, lane, nvalid, (int)prow,
                       p.part_o + 128 * wave, kDV);
       if (rvalid[rb] && wave == 0 && g == 0) {
-        p.part_m[prow] = ltot[rb] > 0.f ? m_used[rb] : -INFINITY;
+        p.part_m[prow] = partial_max(m_used[rb], ltot[rb]);
         p.part_l[prow] = ltot[rb];
       }
     }

@@ -532,7 +532,7 @@ __device__ __forceinline__ void rows_alone(const LinkParams &p, const Piece &w, 
 #pragma unroll
       for (int j = 0; j < kDims; ++j) so[i * stride + dim + 64 * j] = o[j];
     if (lane == 0) {
-      sm[i] = m;
+      sm[i] = partial_max(m, l);
       sl[i] = l;
     }
   }
@@ -671,7 +671,7 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
         for (int b = 0; b < S::NB; ++b)
           store4<float>(po + 16 * b, st.o[c][b][0], st.o[c][b][1], st.o[c][b][2], st.o[c][b][3]);
         if (lg == 0) {
-          p.part_m[prow] = ltot[c] > 0.f ? st.m[c] : -INFINITY;
+          p.part_m[prow] = partial_max(st.m[c], ltot[c]);
           p.part_l[prow] = ltot[c];
         }
       }
@@ -731,7 +731,7 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
       for (int b = 0; b < S::NB; ++b)
         store4<float>(o + 16 * b, st.o[c][b][0], st.o[c][b][1], st.o[c][b][2], st.o[c][b][3]);
       if (lg == 0) {
-        sm[wave][16 * c + lr] = ltot[c] > 0.f ? st.m[c] : -INFINITY;
+        sm[wave][16 * c + lr] = partial_max(st.m[c], ltot[c]);
         sl[wave][16 * c + lr] = ltot[c];
       }
     }

@@ -195,6 +195,13 @@ __device__ __forceinline__ ReqEntry item_request(const WorkItem &w) {
   return R;
 }
 
+// The running max a partial (m, l, O) is stored with: -inf only where it holds
+// no key, which is what the combine passes over. A NaN sum stays in the merge
+// (the max beside it is -inf where every score is NaN).
+__device__ __forceinline__ float partial_max(float m, float l) {
+  return l == 0.f ? -INFINITY : m == -INFINITY ? 0.f : m;
+}
+
 // Epilogue stores of the matrix-core kernels. After the 32x32 value products
 // lane (n = l % 32, g = l / 32) holds row n, value dims 32 d + 8 j + 4 g ..+3
 // of a 32-row x 128-dim block, so a store straight from the registers covers

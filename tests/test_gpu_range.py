@@ -4,7 +4,8 @@ The streaming kernel of fp32 and narrow bf16 GQA calls keeps its probabilities
 at or below one, so sums of values stay finite as long as the values' own sums
 do; keys a query row does not see (rows past a limit that cuts a link inside a
 page, own keys after the row's token) do not reach its output, whatever they
-hold; a visible infinite value gives an infinite output."""
+hold; a visible infinite value gives an infinite output. In every kernel a NaN
+score makes the row NaN also where its keys are split over several pieces."""
 import math
 
 import numpy as np
@@ -18,6 +19,7 @@ from test_gpu_blend import ref_link, run_link, stream as cur_stream
 
 pytestmark = pytest.mark.gpu
 
+MLA = dict(kind=W.MLA, n_q_heads=16, d_k=576, d_v=512, q_std=1.0, scale=1 / math.sqrt(192))
 # the streaming kernel's shapes (a group of 3 keeps small calls off the lean kernel)
 STREAM = [(W.F32, 32), (W.F32, 64), (W.F32, 128), (W.BF16, 32), (W.BF16, 64)]
 
@@ -209,3 +211,44 @@ def test_decode_last_own_value_infinite(own):
     assert (dirty[0][:, :, 5] == math.inf).all()
     rest = np.arange(128) != 5
     assert np.array_equal(clean[0][:, :, rest], dirty[0][:, :, rest])
+
+
+NAN_FORMS = {
+    # (config arguments, query tokens, splits (None: prefill), limits)
+    "d128": (dict(d_k=128, n_q_heads=8, n_kv_heads=2), 40, None, False),
+    "d128_limits": (dict(d_k=128, n_q_heads=8, n_kv_heads=2), 40, None, True),
+    "decode_d128": (dict(d_k=128, n_q_heads=8, n_kv_heads=2), 1, 5, False),
+    "mla": (MLA, 9, None, False),
+    "stream_f32": (dict(d_k=64, dtype=W.F32, n_q_heads=6, n_kv_heads=2), 9, None, False),
+    "stream_bf16": (dict(d_k=64, n_q_heads=6, n_kv_heads=2), 9, None, False),
+    "stream_decode": (dict(d_k=64, n_q_heads=6, n_kv_heads=2), 2, 7, False),
+    "small_decode": (dict(d_k=64, n_q_heads=6, n_kv_heads=2), 2, 7, False),
+}
+
+
+@pytest.mark.parametrize("every", [False, True])
+@pytest.mark.parametrize("name", sorted(NAN_FORMS))
+def test_nan_survives_a_split(name, every):
+    """NaN keys that every row sees, in one piece of a split call or in every
+    piece: the output rows are NaN, not the other pieces' result and not zero."""
+    kw, q_len, splits, limited = NAN_FORMS[name]
+    rng = np.random.default_rng(3)
+    batch = 1 if name == "small_decode" else 9
+    cfg = W.small_config("nan", chunk_lens=(640,) * 8, batch=batch, links=(0, 0),
+                         q_len=(q_len,) * batch, self_len=None, decode=splits is not None, **kw)
+    hkv, mla = cfg.n_kv_heads, cfg.kind == W.MLA
+    q = normal(rng, batch * q_len, cfg.n_q_heads, cfg.d_k) * np.float32(cfg.q_std)
+    chunks = []
+    for i in range(8):
+        k = normal(rng, 640, hkv, cfg.d_k)
+        if every:
+            k[::8] = math.nan
+        elif i == 2:
+            k[5] = math.nan
+        chunks.append((k, None if mla else normal(rng, 640, hkv, cfg.d_v)))
+    lims = None
+    if limited:
+        lims = (8 * 640 - np.arange(batch * q_len)).astype(np.int32)
+    (out, _), = run_calls(cfg, [(chunks, None)], [list(range(8))] * batch, q, lims=lims,
+                          splits=splits or 0)
+    assert np.isnan(out).all()
