@@ -1010,6 +1010,23 @@ void apply_splits(pic_store *s, int32_t n_q_heads, int rows_per_block, Setup &C)
   C.part_bytes = (size_t)C.part_rows * (s->desc.d_v + 2) * sizeof(float);
 }
 
+// Most bytes of split partials the library's own choice of pieces may take.
+// Four rounds of workgroups, the most choose_splits plans, write 4 x CUs x
+// workgroups per CU x rows x (d_v + 2) fp32: 130 MiB for the d128 kernel, 128
+// MLA, 132 for narrow bf16 heads, less for the others. Only calls with
+// per-query limits reach the bound: the row blocks that walk next to nothing
+// of a piece cost no time, so they are not counted as workgroups, but a piece
+// has room for the partial rows of all of them (4096 query tokens x 32 heads
+// that see one linked row of 65,536, but for the last: 32 pieces, 2.2 GB).
+constexpr size_t kMostPartBytes = size_t(144) << 20;
+
+// Cuts the pieces of the requests that have the most, by at least an eighth.
+void fewer_pieces(pic_store *s, int32_t n_q_heads, Setup &C) {
+  const int32_t most = C.splits - (C.splits + 7) / 8;
+  for (int32_t &S : C.req_splits) S = std::min(S, most);
+  apply_splits(s, n_q_heads, C.rows_per_block, C);
+}
+
 // Bytes of static scratch a pic_link_decode_noalloc call is charged for (its
 // limit, stated in pic.h): tables, the own KV laid out, and partials of one
 // split count for all requests, num_splits or, for 0, the one that gives
@@ -1137,12 +1154,14 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
       }
     }
     lp.skip_empty = kern == Kern::Mfma128 && !P.doc_lim.empty();
-    if (mode == Mode::Decode && num_splits > 0)
+    const bool given = mode == Mode::Decode && num_splits > 0;
+    if (given)
       C.req_splits.assign(B, num_splits);
     else
       C.req_splits = choose_splits(tiles, blocks, rows, share,
                                    split_cost(kern, s->shape.cus, d, P.max_rows, ss, uneven_rows));
     apply_splits(s, n_q_heads, rows_per_block, C);
+    while (!given && C.part_bytes > kMostPartBytes && C.splits > 1) fewer_pieces(s, n_q_heads, C);
     return PIC_OK;
   }
 

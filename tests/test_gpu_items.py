@@ -191,3 +191,39 @@ def test_unaligned_tensors(d, dtype, hq, q):
         assert torch.equal(outs[0], outs[1])
     finally:
         dw.close()
+
+
+def test_limited_workspace_is_bounded():
+    """A limited call whose row blocks walk almost none of its tiles (4095 of
+    4096 query tokens see one linked row, the last sees 65,536): empty pieces
+    cost next to no time but their rows of partials take memory all the same,
+    so the pieces are bounded by it (144 MiB; cutting them by time alone took
+    32 pieces and 2.2 GB)."""
+    n, links = 4096, 64
+    store = pic.Store(W.GQA, W.BF16, 8, 128, 128, 1024)
+    try:
+        g = torch.Generator(device="cuda").manual_seed(1)
+        k = torch.randn(1024, 8, 128, device="cuda", generator=g).bfloat16()
+        v = torch.randn(1024, 8, 128, device="cuda", generator=g).bfloat16()
+        store.put(1, 1024, k, v)
+        q = torch.randn(n, 32, 128, device="cuda", generator=g).bfloat16() / 8
+        out = torch.empty_like(q)
+        lims = np.ones(n, np.int32)
+        lims[-1] = 1024 * links
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        free = torch.cuda.mem_get_info()[0]
+        pic.link_attn(store, np.array([0, links], np.int32), [1] * links,
+                      np.array([0, n], np.int32), None, 32, q, None, None, 1.0, out,
+                      q_doc_limits=lims)
+        torch.cuda.synchronize()
+        used = free - torch.cuda.mem_get_info()[0]
+        assert used <= 160 << 20, used
+        # one linked row: its value; the repeated chunk: attention over it once
+        want = v[0].repeat_interleave(4, 0).expand(n - 1, -1, -1)
+        assert torch.equal(out[:-1], want)
+        s = torch.einsum("hd,thd->ht", q[-1].float(), k.float().repeat_interleave(4, 1))
+        ref = torch.einsum("ht,thd->hd", s.softmax(1), v.float().repeat_interleave(4, 1))
+        assert float((out[-1].float() - ref).norm() / ref.norm()) <= 2.0 ** -7
+    finally:
+        store.close()
