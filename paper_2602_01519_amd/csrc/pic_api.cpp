@@ -1162,6 +1162,14 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
                                    split_cost(kern, s->shape.cus, d, P.max_rows, ss, uneven_rows));
     apply_splits(s, n_q_heads, rows_per_block, C);
     while (!given && C.part_bytes > kMostPartBytes && C.splits > 1) fewer_pieces(s, n_q_heads, C);
+    // A decode call that the no-alloc entry takes (by its charge) fits its
+    // scratch, also where uneven requests are cut into more pieces than the
+    // charge counts or the work items need more than its slack. Cut here, for
+    // both entries, so that their results are the same.
+    if (mode == Mode::Decode && noalloc_charge(s, C, num_splits) <= kStaticScratchBytes)
+      while (table_layout(C).bytes + C.work_bytes() > kStaticScratchBytes + kStaticScratchSlack &&
+             C.splits > 1)
+        fewer_pieces(s, n_q_heads, C);
     return PIC_OK;
   }
 
@@ -1948,15 +1956,8 @@ pic_status pic_link_decode_noalloc(pic_store *s, const pic_link_req *req, int32_
     return launch_small(s->desc, C, C.P.links.data(), base, q, k_self, v_self, softmax_scale,
                         out, lse, (hipStream_t)stream);
   }
-  // scratch layout: [tables][workspace]. Uneven requests may be cut into more
-  // pieces than the call is charged for: then into fewer, until it fits.
-  TableLayout t = table_layout(C);
-  while (t.bytes + C.work_bytes() > kStaticScratchBytes + kStaticScratchSlack && C.splits > 1) {
-    const int32_t most = C.splits / 2;
-    for (int32_t &S : C.req_splits) S = std::min(S, most);
-    apply_splits(s, n_q_heads, C.rows_per_block, C);
-    t = table_layout(C);
-  }
+  // scratch layout: [tables][workspace] (setup_call cut the pieces to fit)
+  const TableLayout t = table_layout(C);
   if (t.bytes + C.work_bytes() > kStaticScratchBytes + kStaticScratchSlack)
     return fail(PIC_ERR_INVALID, "the call's tables exceed the static scratch");
   DeviceGuard dg(s->device);

@@ -91,3 +91,60 @@ def test_noalloc_rejects_a_call_beyond_the_scratch():
     torch.cuda.synchronize()
     assert bool(torch.all(out == 1234)) and bool(torch.all(lse == 5.0))
     store.close()
+
+
+def _both(store, co, ids, qo, hq, q, splits):
+    """The call through both entry points: outputs of the no-alloc one, bits compared."""
+    res = []
+    for call in (pic.link_decode_noalloc, pic.link_decode):
+        out = torch.full((q.shape[0], hq, q.shape[2]), 77, dtype=q.dtype, device="cuda")
+        lse = torch.full((q.shape[0], hq), 5.0, dtype=torch.float32, device="cuda")
+        call(store, co, ids, qo, None, hq, q, None, None, 1.0, out, lse, num_splits=splits,
+             stream=torch.cuda.current_stream().cuda_stream)
+        res.append((out, lse))
+    torch.cuda.synchronize()
+    (a, la), (b, lb) = res
+    assert torch.equal(a, b) and torch.equal(la, lb), "differs from pic_link_decode"
+    return a
+
+
+def test_noalloc_pieces_cut_back_alike():
+    """Calls within the charge whose tables and partials exceed the scratch: the
+    pieces are cut back, in both entry points, so the bits stay the same.
+    1900 one-token requests in 256 pieces (63 MiB of partials and 31 MB of
+    work items); four requests of 16 tokens x 256 heads over 65,536 linked rows
+    among 40 short ones (77 MB of partials where the charge counts one
+    split count for all)."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def rnd(*shape):
+        return torch.randn(shape, device="cuda", generator=g).bfloat16()
+
+    store = pic.Store(W.GQA, W.BF16, 1, 32, 32, 64)
+    try:
+        k, v, n = rnd(50, 1, 32), rnd(50, 1, 32), 1900
+        store.put(1, 50, k, v)
+        q = rnd(n, 1, 32) / 6
+        co = np.arange(n + 1, dtype=np.int32)
+        out = _both(store, co, [1] * n, co, 1, q, 256)
+        ref = (q[:, 0].float() @ k[:, 0].float().t()).softmax(1) @ v[:, 0].float()
+        assert float((out[:, 0].float() - ref).norm() / ref.norm()) <= 2.0 ** -7
+    finally:
+        store.close()
+    store = pic.Store(W.GQA, W.BF16, 8, 128, 128, 1024)
+    try:
+        k, v = rnd(1024, 8, 128), rnd(1024, 8, 128)
+        store.put(1, 1024, k, v)
+        links, toks = [64] * 4 + [1] * 40, [16] * 4 + [1] * 40
+        co = np.cumsum([0] + links).astype(np.int32)
+        qo = np.cumsum([0] + toks).astype(np.int32)
+        q = rnd(sum(toks), 256, 128) / 11
+        out = _both(store, co, [1] * sum(links), qo, 256, q, 0)
+        # a chunk linked 64 times gives what it gives once
+        for h in range(8):
+            qh = q[:, 32 * h:32 * h + 32].float().reshape(-1, 128)
+            ref = (qh @ k[:, h].float().t()).softmax(1) @ v[:, h].float()
+            got = out[:, 32 * h:32 * h + 32].float().reshape(-1, 128)
+            assert float((got - ref).norm() / ref.norm()) <= 2.0 ** -7
+    finally:
+        store.close()
