@@ -802,6 +802,9 @@ StreamShape stream_shape(int dtype, int d, int max_rows, bool small) {
   if (small)
     while (!small_built(dtype == 0 ? 4 : 2, d, cb)) cb /= 2;
   StreamShape s;
+  // one workgroup (a wave per SIMD) for the widest fp32 heads, see kMinWaves;
+  // the others hold at least two
+  s.per_cu = d * (dtype == 0 ? 4 : 2) > 256 ? 1 : 2;
   s.rows = 16 * cb;
   const int blocks = (max_rows + s.rows - 1) / s.rows;
   s.kpar = blocks <= 1 ? 4 : blocks == 2 ? 2 : 1;

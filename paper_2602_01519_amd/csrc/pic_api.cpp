@@ -703,6 +703,7 @@ struct SplitCost {
   double part;         // writing and merging one partial row
   double fixed;        // the combine launch
   int32_t min_piece;   // fewest tiles of a piece
+  bool lockstep;       // see choose_splits
   int32_t max_splits;
 };
 
@@ -712,7 +713,12 @@ struct SplitCost {
 // costs its longest piece if the workgroups all run at once, else the
 // average work per slot plus 0.3 of the longest piece (in-order dispatch
 // leaves the last pieces uneven), and in both cases the partials its splits
-// write and merge. Requests are cut into equal pieces of at most L tiles, so
+// write and merge. lockstep: like pieces of the fp32 128-wide stream kernel,
+// one workgroup per CU bound by its matrix instructions, start and end
+// together, so a call takes a shortest piece for every round begun, and up to
+// eight rounds of short pieces are considered (9 requests of 300 tokens x 24/8
+// heads over 6 links of 1024: unsplit, 2.25 rounds, 2475 us, in 3 pieces 2030).
+// Requests are cut into equal pieces of at most L tiles, so
 // a ragged batch gets pieces of like length (with one split count for all
 // requests the longest request's pieces set the time: an MLA decode step of
 // 32 requests over 4..14 links took 58 us in 8 pieces each).
@@ -740,7 +746,7 @@ std::vector<int32_t> choose_splits(const std::vector<int32_t> &tiles,
   };
   auto cost = [&](int32_t L) {
     const double inv = 1.0 / L;
-    double work = 0, longest = 0, part = 0, wgs = 0;
+    double work = 0, longest = 0, shortest = 1e30, part = 0, wgs = 0;
     for (size_t r = 0; r < n; ++r) {
       if (blocks[r] == 0) continue;
       const int32_t S = pieces(r, L, inv);
@@ -748,17 +754,23 @@ std::vector<int32_t> choose_splits(const std::vector<int32_t> &tiles,
       wgs += held;
       work += blocks[r] * tiles[r] * share[r] + c.over * held;
       longest = std::max(longest, (double)((tiles[r] + S - 1) / S) + c.over);
+      shortest = std::min(shortest, (double)(tiles[r] / S) + c.over);
       if (S > 1) part += c.part * (double)rows[r] * S * share[r];
     }
-    const double run = wgs <= (double)c.slots ? longest
-                                      : std::max(longest, work / (double)c.slots + 0.3 * longest);
+    double run = longest;
+    if (c.lockstep)
+      run = std::max({longest, work / (double)c.slots + 0.3 * (longest - shortest),
+                      std::ceil(wgs / (double)c.slots) * shortest});
+    else if (wgs > (double)c.slots)
+      run = std::max(longest, work / (double)c.slots + 0.3 * longest);
     return run + part + (part > 0 ? c.fixed : 0.0);
   };
   int32_t most = 1;
   for (size_t r = 0; r < n; ++r) most = std::max(most, tiles[r]);
   int32_t best_L = most;
   double best = cost(most);
-  for (int k : {1, 2, 4, 6, 8}) {          // half rounds
+  for (int k : {1, 2, 4, 6, 8, 10, 12, 14, 16}) {          // half rounds
+    if (k > 8 && !c.lockstep) break;
     const double limit = (double)(c.fit * k / 2);
     if (total(most) > limit) continue;
     int32_t lo = std::min(c.min_piece, most), hi = most;   // shortest L that fits
@@ -923,12 +935,22 @@ SplitCost split_cost(Kern kern, int32_t cus, const pic_store_desc &d, int32_t ma
     c.over = 2;
     c.min_piece = 1;
   } else {
-    // two workgroups per CU; fp32: a 32-key tile is D/16 x 16 matrix
-    // instructions of 32 cycles per 16 rows and wave; bf16: 36 cycles per
-    // score and lane; the waves of a workgroup share a tile kpar ways
-    const double cyc = d.dtype == PIC_F32 ? 32.0 * d.d_k * ss.rows / 16 : 22.0 * ss.rows;
-    us = 2 * cyc / 2200.0 / ss.kpar;
-    c.slots = 2 * (int64_t)cus;
+    // Cycles of a wave's 32-key tile. fp32: D / 16 x 16 matrix instructions of
+    // 32 cycles per 16 rows. bf16: 22 per row. Measured, 8 requests x 512 tokens
+    // x 32/8 heads over 16 links of 1024, two workgroups per CU: 1.65 us per
+    // tile for bf16 x 64 (28 cycles per row at 2.2 GHz), 1.32 for bf16 x 32
+    // (22), 4.15 for fp32 x 64, and 4.24 for fp32 x 128, one workgroup per CU.
+    // The waves of a workgroup share a tile kpar ways.
+    const double cyc = d.dtype == PIC_F32 ? 2.0 * d.d_k * ss.rows : 22.0 * ss.rows;
+    // Requests with different numbers of row blocks fill the CUs unevenly; with
+    // one workgroup per CU they are planned as for two, in finer pieces than
+    // the rounds ask for (12 requests of 20..130 tokens over 6 links of 700,
+    // 32/8, 24/8 and 6/2 heads: 737, 543 and 176 us, planned for one 772, 594
+    // and 191).
+    c.lockstep = ss.per_cu == 1 && !uneven_rows;
+    const int wgs = c.lockstep ? 1 : 2;
+    us = wgs * cyc / 2200.0 / ss.kpar;
+    c.slots = wgs * (int64_t)cus;
     c.over = 6.0 / us;
     c.min_piece = 2 * ss.kpar;
   }
@@ -1117,7 +1139,7 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     return fail(PIC_ERR_UNSUPPORTED, "head widths d_k=%d d_v=%d exceed the generic kernel's LDS",
                 d.d_k, d.d_v);
   C.kern = kern;
-  StreamShape ss{0, 1};
+  StreamShape ss{0, 1, 4};
   if (kern == Kern::Stream) ss = stream_shape(d.dtype, d.d_k, P.max_rows, C.small);
   lp.kpar = ss.kpar;
   C.stream_rows = ss.rows;
@@ -1179,9 +1201,9 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     if (num_splits > 0) {
       splits = num_splits;
     } else {
-      // workgroups for eight rounds of the CUs (stream kernel: two per CU),
-      // never more splits than tiles
-      const int64_t items = (kern == Kern::Stream ? 2 : 8) * (int64_t)s->shape.cus;
+      // eight workgroups per CU (stream kernel: one round), never more splits
+      // than tiles
+      const int64_t items = (kern == Kern::Stream ? ss.per_cu : 8) * (int64_t)s->shape.cus;
       splits = (int32_t)std::max<int64_t>(1, std::min<int64_t>((items + blocks - 1) / blocks, 256));
       splits = std::min(splits, std::max(1, P.max_tiles));
     }
@@ -1190,7 +1212,7 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     // longest request's pieces no longer than the average work per resident
     // workgroup, at least min_piece tiles (1 for the vector-ALU kernel, whose
     // tiles are slow), at most 16 pieces.
-    const int64_t slots = (int64_t)s->shape.cus * (kern == Kern::Stream ? 2 : 4);
+    const int64_t slots = (int64_t)s->shape.cus * ss.per_cu;
     const int min_piece = kern == Kern::Stream ? 2 * ss.kpar : 1;
     int64_t work = 0;   // tiles summed over all non-empty workgroups
     for (const ReqEntry &R : P.reqs) {
@@ -1199,6 +1221,10 @@ pic_status setup_call(pic_store *s, const pic_link_req *req, int32_t n_q_heads, 
     }
     const int64_t per_slot = std::max<int64_t>(min_piece, (work + slots - 1) / slots);
     splits = (int32_t)std::min<int64_t>(16, (P.max_tiles + per_slot - 1) / per_slot);
+    // one workgroup per CU (lockstep, see choose_splits): as many pieces as
+    // fill one round
+    if (kern == Kern::Stream && ss.per_cu == 1 && blocks < slots)
+      splits = std::max(splits, (int32_t)std::min<int64_t>(16, slots / blocks));
     splits = std::max(1, std::min(splits, P.max_tiles / min_piece));
   }
   C.splits = splits;

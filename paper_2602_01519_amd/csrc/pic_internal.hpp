@@ -368,6 +368,7 @@ int decode_d128_max_rows();
 bool stream_supported(int dtype, int d_k, int d_v);
 struct StreamShape {
   int32_t rows, kpar;
+  int32_t per_cu;         // resident workgroups per CU that a call is planned with
 };
 StreamShape stream_shape(int dtype, int d, int max_rows, bool small);
 hipError_t launch_link_stream(const LinkParams &p, int dtype, int rows, hipStream_t st,
