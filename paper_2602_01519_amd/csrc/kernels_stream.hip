@@ -19,10 +19,10 @@
 // again one by one on the vector ALU (rows_alone): the max follows every key,
 // so probabilities stay at or below one and sums overflow only where the
 // values' own sums do, and a key that a row does not see adds nothing to it
-// whatever it holds (0 x infinity is NaN). Other calls pay one compare per sum
-// at the end of a piece; a max that follows every tile instead took 8 ragged
-// bf16 requests of 30..300 tokens from 148 to 176 us, 12 fp32 ones of 20..130
-// tokens from 65.1 to 67.1.
+// whatever it holds (0 x infinity is NaN). Other calls pay half a maximum per
+// sum at the end of a piece: 8 ragged bf16 requests of 30..300 tokens 148.1 ->
+// 148.6 us, 12 fp32 ones of 20..130 tokens 65.1 -> 65.3 (a max that follows
+// every tile instead: 176 and 67.1).
 // The scores a lane receives are the keys its operand of the value product
 // needs, so probabilities never leave its registers:
 //   fp32 (v_mfma_f32_16x16x4_f32): A lane l = (row l % 16, k-slot l / 16);
@@ -632,15 +632,15 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
   float ltot[CB];
 #pragma unroll
   for (int c = 0; c < CB; ++c) ltot[c] = col_sum(st.l[c]);
-  bool alone = false;
+  float most = 0.f;            // (NaN stays in it)
 #pragma unroll
   for (int c = 0; c < CB; ++c)
 #pragma unroll
     for (int b = 0; b < S::NB; ++b)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) alone |= !(fabsf(st.o[c][b][i]) <= kSafeSum);
-  const bool redo = __builtin_expect(__any(alone), 0);
-  if (redo) {
+      for (int i = 0; i < 4; ++i) most = __builtin_elementwise_maximum(most, fabsf(st.o[c][b][i]));
+  const bool redo = __any(!(most <= kSafeSum));
+  if (__builtin_expect(redo, 0)) {
     // the piece anew: kept over the loop above, it would cost it registers
     int block = blockIdx.x;
     asm volatile("" : "+s"(block));
@@ -649,7 +649,7 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
       rows_alone<T, D, kSmall>(p, again, kR, lane, so[wave], kOS, sm[wave], sl[wave]);
     __builtin_amdgcn_wave_barrier();     // its lanes read each other's sums below
   }
-  if (kpar == 1 && !redo) {
+  if (__builtin_expect(kpar == 1 && !redo, 1)) {
     // each lane holds 4 consecutive value dims of its rows
 #pragma unroll
     for (int c = 0; c < CB; ++c) {
@@ -679,20 +679,22 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
     return;
   }
   // (m, l, O) of rows in LDS to out or the partials: units of 4 value dims idx,
-  // idx + step ... of n rows from row `begin` on, the sum of `parts` waves' from
-  // wave0 on.
-  auto write_rows = [&](int idx, int step, int n, int begin, int wave0, int parts) {
+  // idx + step ... of n rows from row `begin` on, the sum of kParts waves' from
+  // wave0 on (a constant: their reads of LDS go out together).
+  auto write_rows = [&](int idx, int step, int n, int begin, int wave0, auto parts) {
+    constexpr int kParts = decltype(parts)::value;
     constexpr int kQ = D / 4;                      // 4-wide units per row
     for (; idx < n * kQ; idx += step) {
       const int rr = idx / kQ, e = idx % kQ * 4;
       const int row = begin + rr;
       if (row >= nrows) break;                     // later units are later rows
-      const int w0 = wave0 + rr / kR * parts, rl = rr % kR;
-      float M = -INFINITY;
-      for (int w = 0; w < parts; ++w) M = fmaxf(M, sm[w0 + w][rl]);
-      float L = 0.f;
+      const int w0 = wave0 + rr / kR * kParts, rl = rr % kR;
+      float M = -INFINITY, L = 0.f;
+#pragma unroll
+      for (int w = 0; w < kParts; ++w) M = fmaxf(M, sm[w0 + w][rl]);
       float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int w = 0; w < parts; ++w) {
+#pragma unroll
+      for (int w = 0; w < kParts; ++w) {
         const float mw = sm[w0 + w][rl];
         const float wt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
         const float4 v = *(const float4 *)&so[w0 + w][rl * kOS + e];
@@ -719,7 +721,7 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
     }
   };
   if (kpar == 1) {
-    write_rows(lane, 64, kR, row0, wave, 1);
+    write_rows(lane, 64, kR, row0, wave, std::integral_constant<int, 1>());
     return;
   }
   // merge the kpar parts of every row block through LDS
@@ -737,7 +739,10 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
     }
   }
   __syncthreads();
-  write_rows(threadIdx.x, 64 * kWaves, (kWaves / kpar) * kR, wg_row0, 0, kpar);
+  if (kpar == 2)
+    write_rows(threadIdx.x, 64 * kWaves, 2 * kR, wg_row0, 0, std::integral_constant<int, 2>());
+  else
+    write_rows(threadIdx.x, 64 * kWaves, kR, wg_row0, 0, std::integral_constant<int, 4>());
 }
 
 // Two waves per SIMD, one for the widest fp32 heads (two tiles in flight of
