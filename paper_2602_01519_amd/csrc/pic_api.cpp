@@ -590,7 +590,6 @@ struct Setup {
   int32_t n_items = 0;
   bool lean = false;             // a small call the lean kernel runs
   bool small = false;            // tables as a kernel argument, own KV in place
-  bool own_in_place = false;     // the kernel reads own KV from k_self / v_self
   int32_t rows_per_block = 0;    // rows of a workgroup (decode kernel: wave)
   int32_t stream_rows = 0;       // stream kernel: rows per wave
   LinkParams lp{};               // shapes only: no tables, tensors or scale yet
@@ -639,7 +638,7 @@ void write_items(const Setup &C, const LinkEntry *links, WorkItem *out) {
         w.tile0 = L.tile0;
         w.tok0 = L.tok0;
       }
-      if (C.own_in_place) w.tok0 = R.s0;   // the decode kernel masks no linked rows
+      if (C.kern == Kern::Decode128) w.tok0 = R.s0;   // it masks no linked rows
       w.link = li;
       w.q0 = R.q0;
       w.lq = R.lq;
@@ -898,11 +897,6 @@ bool small_tables(const Plan &P) {
 // more than the prologue saves once there are several.
 constexpr int kStreamSmallRows = 128;
 
-// Most own tokens of a request whose own KV the decode kernel reads in place
-// (2-byte gathers of the token-major values, once per kv head) instead of
-// having the prologue lay it out; a plan's runs then need no prologue.
-constexpr int32_t kOwnInPlace = 128;
-
 // Costs of a kernel's pieces in its tiles (see choose_splits). Tile times on
 // a full GPU: d128 1.75 us per workgroup (64 keys), MLA 2.0 us (64 keys),
 // decode 5 us per wave (32 keys, eight waves per CU on the HBM stream),
@@ -1021,14 +1015,9 @@ void apply_splits(pic_store *s, int32_t n_q_heads, int rows_per_block, Setup &C)
     balance_order_d128(s, P, lp, rows_per_block,
                        s->shape.cus / s->shape.xcds * mfma_d128_blocks_per_cu());
   }
-  if (C.kern == Kern::Decode128) {
-    int32_t own = 0;
-    for (const ReqEntry &R : P.reqs) own = std::max(own, R.ls);
-    C.own_in_place = own > 0 && own <= kOwnInPlace;
-    lp.own_in_place = C.own_in_place;
-    if (C.own_in_place) P.max_own_lp = 0;      // nothing to lay out
-  }
-  C.part_off = C.own_in_place ? 0 : round_up(P.own_bytes, 256);
+  // The decode kernel reads the own KV in place: nothing to lay out.
+  if (C.kern == Kern::Decode128) P.max_own_lp = 0;
+  C.part_off = C.kern == Kern::Decode128 ? 0 : round_up(P.own_bytes, 256);
   C.part_bytes = (size_t)C.part_rows * (s->desc.d_v + 2) * sizeof(float);
 }
 

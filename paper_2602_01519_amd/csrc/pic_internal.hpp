@@ -73,7 +73,8 @@ __host__ __device__ __forceinline__ int visible_tiles(const ReqEntry &r, int q_l
 // that load waits for one table read (the request order, the request and a
 // walk over its links were three and more dependent ones). The link fields
 // are those of the entry that holds tile t_begin; later links follow at
-// links[link + 1] ...
+// links[link + 1] ... (for the decode kernel, which masks no linked rows, tok0
+// is the request's first own row)
 struct WorkItem {
   const void *k, *v;
   int32_t len, lp, tile0, tok0;
@@ -120,8 +121,6 @@ struct LinkParams {
   int32_t n_groups;       // batch * n_kv_heads
   int32_t spread;         // matrix-core kernels: row blocks of one unit on all XCDs (1, 2)
   int32_t n_xcd;          // accelerator dies (XCDs) of the device, each with its own L2
-  int32_t own_in_place;   // decode kernel: own KV read from k_self / v_self, an
-                          // item's tok0 holds the request's first own row
   int32_t skip_empty;     // values of partials with m = -inf are not written
   int32_t even;           // all requests have as many tiles, rows and pieces
   int32_t gang;           // MLA kernel: consecutive row blocks on one XCD

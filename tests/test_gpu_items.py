@@ -65,13 +65,41 @@ def test_uneven_batches(name):
 @pytest.mark.parametrize("own", [1, 31, 32, 33, 63, 64, 65, 127, 128, 129])
 @pytest.mark.parametrize("splits", [0, 7])
 def test_decode_own_in_place(own, splits):
-    """Own KV around the decode kernel's 32-key tiles and around the most it
-    reads in place (128 tokens), beside requests with other lengths and
-    none linked; 1, 2 and 4 query tokens (causal inside the own tiles)."""
+    """Own KV, which the decode kernel reads in place, around its 32-key tiles,
+    beside requests with other lengths and none linked; 1, 2 and 4 query
+    tokens (causal inside the own tiles)."""
     q = (1, 2, 4, 1)
     cfg = uneven(f"own_{own}", q, tuple(max(a, b) for a, b in zip(q, (own, own, own, 5))), d_k=128,
                  n_q_heads=8, n_kv_heads=2, decode=True)
     run_and_check(cfg, num_splits=splits, links=[[3, 0], [], [4], LONG])
+
+
+@pytest.mark.parametrize("own,splits", [(513, 0), (3000, 0), (3000, 7), (4097, 100)])
+def test_decode_long_own(own, splits):
+    """Own KV longer than the documents, cut into pieces of its own, on both the
+    call and a plan's run (the same bits)."""
+    q = (1, 2, 4, 1)
+    cfg = uneven(f"long_own_{own}", q, (own, own + 1, 4, own - 1), d_k=128, n_q_heads=8,
+                 n_kv_heads=2, decode=True)
+    links = [[3, 0], [], [4], [1]]
+    out, lse = run_and_check(cfg, num_splits=splits, links=links)
+    wl = W.make_workload(cfg)
+    p = wl.plan
+    idx = np.array([c for l in links for c in l], dtype=np.int64)
+    co = np.cumsum([0] + [len(l) for l in links]).astype(np.int32)
+    dw = runner.upload(dataclasses.replace(wl, plan=dataclasses.replace(
+        p, chunk_offsets=co, chunk_index=idx)))
+    try:
+        plan = pic.LinkPlan(dw.store, co, wl.chunk_ids[idx], p.q_offsets, p.self_offsets,
+                            cfg.n_q_heads, mode=pic.DECODE, num_splits=splits)
+        plan.run(0, dw.q, dw.k_self, dw.v_self, float(np.float32(cfg.scale)), dw.out, dw.lse,
+                 stream=torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        a, la = dw.results()
+        plan.close()
+        assert np.array_equal(a, out) and np.array_equal(la, lse)
+    finally:
+        dw.close()
 
 
 def test_noalloc_charge_is_the_uniform_layout():
