@@ -502,12 +502,12 @@ hipError_t launch_link_mla(LinkParams p, hipStream_t st, const char **name) {
   *name = "link_mla_kernel";
   // A batch of like requests (p.even) gives each XCD one contiguous eighth of
   // all row blocks, whole requests where it can. With uneven requests the
-  // heaviest ones would fall to one XCD; runs of 32 row blocks, what an
-  // XCD's CUs hold at once, are dealt round-robin instead (20 ragged requests
+  // heaviest ones would fall to one XCD; runs of p.gang row blocks, what an
+  // XCD's CUs hold at once (32), are dealt round-robin instead (20 ragged requests
   // of 2..51 tokens over 3..16 links: 142 -> 130 us; 8 like requests of 256
   // tokens over 12 links of 512: 409 us contiguous, 413 in runs).
   const int64_t blocks = (int64_t)p.n_items * p.nrb;
-  p.gang = p.even && blocks % p.n_xcd == 0 ? (int32_t)(blocks / p.n_xcd) : 32;
+  if (p.even && blocks % p.n_xcd == 0) p.gang = (int32_t)(blocks / p.n_xcd);
   const int64_t per_round = (int64_t)p.gang * p.n_xcd;
   const dim3 grid((unsigned)((blocks + per_round - 1) / per_round * per_round));
   if (p.doc_lim)

@@ -991,6 +991,7 @@ void apply_splits(pic_store *s, int32_t n_q_heads, int rows_per_block, Setup &C)
   }
   lp.n_items = C.n_items;
   lp.num_splits = C.splits;
+  lp.gang = std::max(1, s->shape.cus / s->shape.xcds);
   lp.spread = C.kern == Kern::Stream ||
               spread_units((int64_t)C.n_items * lp.n_kv_heads, lp.nrb, lp.n_xcd);
   // With per-query limits the early row blocks of late pieces are empty: the

@@ -123,7 +123,7 @@ struct LinkParams {
   int32_t n_xcd;          // accelerator dies (XCDs) of the device, each with its own L2
   int32_t skip_empty;     // values of partials with m = -inf are not written
   int32_t even;           // all requests have as many tiles, rows and pieces
-  int32_t gang;           // MLA kernel: consecutive row blocks on one XCD
+  int32_t gang;           // MLA kernel: consecutive row blocks on one XCD (planned: its CUs)
   int32_t kpar;           // stream kernel: key parts within a workgroup (1, 2 or 4)
   float scale_log2;       // softmax_scale * log2(e)
 };
