@@ -2,7 +2,7 @@
 where the cutting, the work mapping or the merge can go wrong: one long
 request among short and empty ones, requests without query rows, piece
 boundaries on links and inside the own KV, own KV read in place by the decode
-kernel around its tile and limit, few (request, kv head) units over many row
+kernel around its tiles and long, few (request, kv head) units over many row
 blocks, MLA runs of row blocks that do not fill an XCD's share, and the
 no-alloc entry's charge. All against the fp64 oracle to the parity bar."""
 import dataclasses
@@ -12,6 +12,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import parity_gate as G
 from paper_2602_01519_amd import pic, runner
 from paper_2602_01519_amd import workloads as W
@@ -104,9 +105,10 @@ def test_decode_long_own(own, splits):
 
 def test_noalloc_charge_is_the_uniform_layout():
     """A call is refused by what the uniform layout of its own KV and partials
-    would take, also where the kernels need less: 4 requests of 16 tokens x
-    128 heads x 250 splits of 128-wide partials are 1.1 GB, refused, outputs
-    untouched; 1 split is accepted."""
+    would take: 4 requests of 16 tokens x 128 heads x 250 splits of 128-wide
+    partials are 1.1 GB, refused, outputs untouched; 1 split is accepted; 40
+    one-token requests of 2000 own tokens are refused for 164 MB of own KV,
+    which the decode kernel would read in place."""
     store = pic.Store(W.GQA, W.BF16, 8, 128, 128, 64)
     try:
         k = torch.randn(64, 8, 128, device="cuda").bfloat16()
@@ -125,6 +127,16 @@ def test_noalloc_charge_is_the_uniform_layout():
         pic.link_decode_noalloc(*args, num_splits=1)
         torch.cuda.synchronize()
         assert not bool((out == 7.0).all())
+        n, own = 40, 2000
+        one = np.arange(n + 1, dtype=np.int32)
+        ks = torch.zeros(n * own, 8, 128, device="cuda", dtype=torch.bfloat16)
+        out = torch.full((n, 32, 128), 7.0, device="cuda", dtype=torch.bfloat16)
+        with pytest.raises(pic.PicError) as e:
+            pic.link_decode_noalloc(store, one, [1] * n, one, one * own, 32, qt[:n, :32].contiguous(),
+                                    ks, ks, 1.0, out)
+        assert e.value.status == pic.ERR_INVALID
+        torch.cuda.synchronize()
+        assert bool((out == 7.0).all())
     finally:
         store.close()
 
@@ -194,29 +206,50 @@ def test_limited_empty_pieces(d, splits):
         dw.close()
 
 
-@pytest.mark.parametrize("d,dtype,hq,q", [(128, W.BF16, 8, 40), (128, W.BF16, 8, 300),
-                                          (64, W.BF16, 6, 70), (64, W.F32, 6, 70)])
-def test_unaligned_tensors(d, dtype, hq, q):
-    """Query and output tensors that start one element past a 16-byte boundary
-    give the bits aligned ones give."""
+@pytest.mark.parametrize("d,dtype,hq,q,own,decode", [
+    (128, W.BF16, 8, 40, None, False), (128, W.BF16, 8, 300, None, False),
+    (64, W.BF16, 6, 70, None, False), (64, W.F32, 6, 70, None, False),
+    (128, W.BF16, 8, 2, 70, True),                                    # decode kernel, own in place
+    (128, W.BF16, 8, 40, 70, False), (64, W.F32, 6, 70, 90, False),   # own laid out
+    (64, W.BF16, 6, 20, 50, False), (64, W.F32, 6, 20, 50, False),    # small calls, own in place
+    (64, W.BF16, 8, 20, 50, False)])                                  # lean
+def test_unaligned_tensors(d, dtype, hq, q, own, decode):
+    """Query, own KV and output tensors that start one element past a 16-byte
+    boundary give the bits aligned ones give, which match the oracle."""
     cfg = W.small_config("unaligned", dtype=dtype, d_k=d, n_q_heads=hq, n_kv_heads=2,
-                         chunk_lens=(700, 130), batch=1, links=(2, 2), q_len=q, self_len=None)
+                         chunk_lens=(700, 130), batch=1, links=(2, 2), q_len=q, self_len=own,
+                         decode=decode)
     wl = W.make_workload(cfg)
     p = wl.plan
     dw = runner.upload(wl)
+    n = dw.out.numel()
+
+    def shifted(t, off):
+        if t is None:
+            return None
+        buf = torch.zeros(t.numel() + 8, dtype=t.dtype, device="cuda")
+        buf[off:off + t.numel()] = t.reshape(-1)
+        return buf[off:]
+
     try:
         outs = []
         for off in (0, 1):
-            buf = torch.zeros(dw.q.numel() + 8, dtype=dw.q.dtype, device="cuda")
-            buf[off:off + dw.q.numel()] = dw.q.reshape(-1)
-            res = torch.zeros(dw.out.numel() + 8, dtype=dw.out.dtype, device="cuda")
-            pic.link_attn(dw.store, p.chunk_offsets, wl.link_ids(), p.q_offsets, None, hq,
-                          buf[off:], None, None, float(np.float32(cfg.scale)), res[off:],
-                          stream=torch.cuda.current_stream().cuda_stream)
+            res = torch.zeros(n + 8, dtype=dw.out.dtype, device="cuda")
+            lse = torch.zeros(dw.lse.numel(), dtype=torch.float32, device="cuda")
+            call = pic.link_decode if decode else pic.link_attn
+            call(dw.store, p.chunk_offsets, wl.link_ids(), p.q_offsets, p.self_offsets, hq,
+                 shifted(dw.q, off), shifted(dw.k_self, off), shifted(dw.v_self, off),
+                 float(np.float32(cfg.scale)), res[off:], lse,
+                 stream=torch.cuda.current_stream().cuda_stream)
             torch.cuda.synchronize()
-            outs.append(res[off:off + dw.out.numel()].clone())
-            assert int((res[:off] != 0).sum()) == 0 and int((res[off + dw.out.numel():] != 0).sum()) == 0
-        assert torch.equal(outs[0], outs[1])
+            outs.append((res[off:off + n].clone(), lse))
+            assert int((res[:off] != 0).sum()) == 0 and int((res[off + n:] != 0).sum()) == 0
+        assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+        ref, ref_lse = oracle.run_workload(wl, dw.chunks)
+        out = runner.to_host(outs[0][0].reshape(dw.out.shape), dtype)
+        bad = G.failures(G.F32 if dtype == W.F32 else G.BF16, out, ref,
+                         outs[0][1].reshape(dw.lse.shape).cpu().numpy().astype(np.float64), ref_lse)
+        assert not bad, bad
     finally:
         dw.close()
 
