@@ -47,6 +47,10 @@ KERNEL_SOURCES = {
     "link_decode_d128_kernel": "kernels_decode_d128.hip",
     "link_mla_kernel": "kernels_mla.hip",
     "link_valu_kernel": "kernels_generic.hip",
+    # two kernels report this name: the small-call form of the streaming kernel
+    # (its own entries first), and that of the vector-ALU kernel
+    "link_small_kernel<float,stream>": "kernels_stream.hip",
+    "link_small_kernel<bf16,stream>": "kernels_stream.hip",
     "link_small_kernel": "kernels_generic.hip",
     "link_lean_kernel": "kernels_generic.hip",
     "link_stream_kernel": "kernels_stream.hip",
