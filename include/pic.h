@@ -242,7 +242,8 @@ pic_status pic_link_attn(pic_store *store, const pic_link_req *req, int32_t n_q_
  * the same function as pic_link_attn (a generated token is treated like a
  * query token, Sec. 4), computed by splitting each request's keys into
  * num_splits ranges whose partial softmax states are merged exactly
- * (log-sum-exp). num_splits = 0 lets the library choose; otherwise 1..256.
+ * (log-sum-exp). num_splits = 0 lets the library choose; otherwise 1..256
+ * (a call within pic_link_decode_noalloc's limit may get fewer, see there).
  * Each request may have at most 16 query tokens.
  * Errors: as pic_link_attn. */
 pic_status pic_link_decode(pic_store *store, const pic_link_req *req, int32_t n_q_heads,
@@ -255,23 +256,28 @@ pic_status pic_link_decode(pic_store *store, const pic_link_req *req, int32_t n_
  * hipMalloc. Same arguments, kernels, split choice and result as
  * pic_link_decode, but the call's tables, own-KV layout and split partials
  * live in the library's static device scratch, a file-scope array of
- * 64 MiB that each GPU the library runs on holds until the process ends;
+ * 72 MiB that each GPU the library runs on holds until the process ends;
  * the call allocates nothing (no hipMalloc, hipFree, pinned staging or
  * event). The host tables are copied with hipMemcpyAsync from pageable
  * memory, which the runtime completes before returning (the host therefore
  * waits for the stream's earlier work). Small calls (at most 32 links and 8
- * requests, no per-query limits, a shape without a matrix-core kernel) run
- * the kernels pic_link_decode runs for them, which take the tables as a
- * kernel argument and read the own KV in place: they use the scratch for
- * split partials only and copy nothing. Every kernel writes what it later
- * reads, so nothing in the scratch has to start at zero.
+ * requests, no per-query limits, any store but bf16 GQA of d 128 and bf16
+ * MLA of 576 / 512) run the kernels pic_link_decode runs for them, which take
+ * the tables as a kernel argument and read the own KV in place: they use the
+ * scratch for split partials only and copy nothing. Every kernel writes what
+ * it later reads, so nothing in the scratch has to start at zero.
  * All calls on one GPU share its scratch: calls must not overlap on a GPU
  * (enqueue them on one stream, or order them); calls that overlap race.
- * Errors: as pic_link_decode, and INVALID when the call needs more than the
- * 64 MiB (about 256 B of tables per link and request, plus
- * ceil(L_s / 64) * 64 own tokens * H_kv * (d_k + d_v) * esize per request,
- * plus Tq * H_q * splits * (d_v + 2) * 4 B when the keys are split); such a
- * call launches nothing. */
+ * Errors: as pic_link_decode, and INVALID when the call is charged more than
+ * 64 MiB: its tables (32 B per link and for a request's own KV, 36 B per
+ * request, 4 B per query token where limits differ), ceil(L_s / 64) * 64 own tokens *
+ * H_kv * (d_k + d_v) * esize per request (also where the kernel reads them in
+ * place), and Tq * H_q * splits * (d_v + 2) * 4 B when the keys are split, with
+ * one split count for all requests (num_splits, or for 0 about eight
+ * workgroups per CU). Such a call launches nothing. A call within the charge
+ * whose requests are cut into more pieces than that, or whose 64 B of work
+ * item per piece do not fit the other 8 MiB, is cut into fewer pieces, here
+ * and in pic_link_decode alike. */
 pic_status pic_link_decode_noalloc(pic_store *store, const pic_link_req *req, int32_t n_q_heads,
                                    const void *q, const void *k_self, const void *v_self,
                                    float softmax_scale, int32_t num_splits, void *out, float *lse,
@@ -288,9 +294,9 @@ pic_status pic_link_decode_noalloc(pic_store *store, const pic_link_req *req, in
  *   mode PIC_PREFILL (num_splits must be 0) computes as pic_link_attn,
  *   PIC_DECODE as pic_link_decode with the given num_splits (0 = auto),
  *   with the same kernels and split choice, so a run returns the bits the
- *   direct call returns (small calls, at most 32 links and 8 requests on
- *   the generic kernel, pass the tables as a kernel argument from the
- *   plan's host copy of each layer's table, as the direct calls do).
+ *   direct call returns (small calls, see pic_link_decode_noalloc, pass the
+ *   tables as a kernel argument from the plan's host copy of each layer's
+ *   table, as the direct calls do).
  *   Blocking: copies the tables to the device before returning. The plan
  *   keeps no pointer into req; the store must outlive it
  *   (pic_store_destroy refuses while plans are alive).

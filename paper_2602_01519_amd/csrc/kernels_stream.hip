@@ -43,10 +43,14 @@
 // with few rows split the keys over the waves too and merge the (m, l, O) of
 // the parts through LDS at the end.
 //
-// What bounds it: fp32, the matrix cores (157 TFLOP/s; the exponentials are
-// a fiftieth of the matrix cycles); bf16 at D = 64, the vector ALU (about 36
-// cycles per score and lane for exponential, sum and the hi / lo split,
-// against 24 matrix cycles). Measured figures stand at launch_link_stream.
+// What bounds it (counters of the two ragged batches above): a wave's own
+// chain of instructions, since such batches keep 0.95 waves per SIMD. bf16 at
+// D = 64: 41 cycles of vector issue per score and lane (exponential, sum, the
+// hi / lo split; 6 of them the matrix instructions' issue) and 24 matrix
+// cycles; the vector ALU issues in 42% of the SIMD cycles, the matrix cores are
+// busy in 25%. fp32: matrix cores 41%, vector ALU 11%, and two thirds of the
+// wave cycles wait for a matrix instruction before the next. Measured figures
+// stand at launch_link_stream.
 #include "pic_internal.hpp"
 
 #include <cstddef>

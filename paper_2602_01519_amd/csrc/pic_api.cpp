@@ -892,9 +892,14 @@ bool small_tables(const Plan &P) {
          P.doc_lim.empty();
 }
 
-// Most rows per kv head of a stream-kernel call that reads its own KV in
-// place: every row block gathers the token-major values anew, which costs
-// more than the prologue saves once there are several.
+// Most rows per kv head of a prefill call of the stream kernel that takes the
+// small form (no prologue, but own values gathered by every row block and one
+// split count for all requests). Small against other form, 24/8 heads, one
+// request over 10 links of 512 unless said: bf16 x 64, 129 rows 20.3 against
+// 25.2 us, 6 requests of 129 / 192 / 384 rows over 4 links 28.5 / 31.0 / 55.5
+// against 31.7 / 34.9 / 45.3; fp32 x 64, 48 / 96 / 129 / 288 rows 28.5 / 37.8 /
+// 40.5 / 60.7 against 29.7 / 32.5 / 42.7 / 56.2. Up to 128 rows bf16 always
+// gains; fp32 gains or loses with how its split count falls.
 constexpr int kStreamSmallRows = 128;
 
 // Costs of a kernel's pieces in its tiles (see choose_splits). Tile times on
@@ -992,6 +997,11 @@ void apply_splits(pic_store *s, int32_t n_q_heads, int rows_per_block, Setup &C)
   lp.n_items = C.n_items;
   lp.num_splits = C.splits;
   lp.gang = std::max(1, s->shape.cus / s->shape.xcds);
+  // The stream kernel always spreads the row blocks of a unit over the XCDs:
+  // its row blocks are short and many, and ragged batches leave XCDs idle
+  // otherwise (12 requests of 20..130 tokens, 24/8 heads, over 6 links of 700:
+  // fp32 x 64 279 us, by the rule 451; bf16 x 64 92, 124; bf16 x 32 77, 99; even
+  // batches of 256 and 512 tokens within 2% of each other).
   lp.spread = C.kern == Kern::Stream ||
               spread_units((int64_t)C.n_items * lp.n_kv_heads, lp.nrb, lp.n_xcd);
   // With per-query limits the early row blocks of late pieces are empty: the

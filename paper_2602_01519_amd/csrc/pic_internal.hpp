@@ -144,7 +144,8 @@ DevShape device_shape();
 // XCDs idle (few units, or a last round of them that fills few XCDs: more
 // than a quarter of the places empty), the row blocks of every unit spread
 // over all XCDs instead: block 0 of every unit first, or (spread 2: calls with
-// per-query limits) the last one, whose rows see the most.
+// per-query limits) the last one, whose rows see the most. (The stream kernel
+// spreads them always, see apply_splits.)
 inline bool spread_units(int64_t units, int32_t nrb, int32_t n_xcd) {
   return nrb > 1 && 4 * ((units + n_xcd - 1) / n_xcd * n_xcd) > 5 * units;
 }
@@ -399,7 +400,7 @@ hipError_t static_scratch(void **out);
 // max_rows: most rows of one p.comb entry (unused when p.comb is NULL).
 hipError_t launch_combine(const LinkParams &p, int dtype, int32_t max_rows, hipStream_t st);
 
-// Tables of a small generic-kernel call, passed by value as a kernel
+// Tables of a small call (vector-ALU or streaming kernel), passed by value as a kernel
 // argument: the call then needs neither the table copy nor the own-KV
 // layout of the prologue (see link_small_kernel).
 constexpr int kSmallLinks = 32, kSmallReqs = 8;
