@@ -939,8 +939,13 @@ __global__ __launch_bounds__(256) void combine_kernel(LinkParams p) {
     if (e < dv)
       store_quad<T>(out + e, make_float4(acc[c].x * inv, acc[c].y * inv, acc[c].z * inv, acc[c].w * inv));
   }
-  if (p.lse && lane == 0)
-    p.lse[orow] = M == -INFINITY ? -INFINITY : (M + log2f(L)) * 0.69314718055994531f;
+  if (p.lse && lane == 0) {
+    // (the wider bf16 heads' sums are of bf16 probabilities)
+    constexpr bool kOnce = sizeof(T) == 4 || kLanes == 16;
+    p.lse[orow] = M == -INFINITY ? -INFINITY
+                  : kOnce        ? log_sum(M, L)
+                                 : (M + log2f(L)) * 0.69314718055994531f;
+  }
 }
 
 size_t valu_lds_bytes(int esz, int mla, int d_k, int d_v) {

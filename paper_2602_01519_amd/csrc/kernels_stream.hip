@@ -666,8 +666,7 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
           store4<T>(out + 16 * b, st.o[c][b][0] * inv, st.o[c][b][1] * inv, st.o[c][b][2] * inv,
                     st.o[c][b][3] * inv);
         if (p.lse && lg == 0)
-          p.lse[orow[c]] =
-              ltot[c] > 0.f ? (st.m[c] + log2f(ltot[c])) * 0.69314718055994531f : -INFINITY;
+          p.lse[orow[c]] = ltot[c] > 0.f ? log_sum(st.m[c], ltot[c]) : -INFINITY;
       } else {
         const int64_t prow = part0 + orow[c];
         float *po = p.part_o + prow * D + 4 * lg;
@@ -713,7 +712,7 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
         const float inv = L > 0.f ? 1.f / L : 0.f;
         store4<T>((T *)p.out + orw * D + e, a.x * inv, a.y * inv, a.z * inv, a.w * inv);
         if (p.lse && e == 0)
-          p.lse[orw] = L > 0.f ? (M + log2f(L)) * 0.69314718055994531f : -INFINITY;
+          p.lse[orw] = L > 0.f ? log_sum(M, L) : -INFINITY;
       } else {
         const int64_t prow = part0 + orw;
         store4<float>(p.part_o + prow * D + e, a.x, a.y, a.z, a.w);

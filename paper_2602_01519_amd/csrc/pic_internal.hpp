@@ -202,6 +202,16 @@ __device__ __forceinline__ float partial_max(float m, float l) {
   return l == 0.f ? -INFINITY : m == -INFINITY ? 0.f : m;
 }
 
+// ln(2^m l), the log-sum-exp of a running max and its sum, rounded once. (m +
+// log2 l) ln 2 in fp32 rounds three times, and where the max lags behind, as in
+// the streaming kernel, l is larger and its logarithm coarser: fp32 lse was up
+// to a tenth further from 64 bits than the vector kernel's.
+__device__ __forceinline__ float log_sum(float m, float l) {
+  int e;
+  const float f = frexpf(l, &e);
+  return (float)(((double)m + e) * 0.69314718055994530942 + (double)logf(f));
+}
+
 // Epilogue stores of the matrix-core kernels. After the 32x32 value products
 // lane (n = l % 32, g = l / 32) holds row n, value dims 32 d + 8 j + 4 g ..+3
 // of a 32-row x 128-dim block, so a store straight from the registers covers
