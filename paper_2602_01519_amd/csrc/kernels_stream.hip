@@ -16,10 +16,11 @@
 //   2^64 (fp32 keeps its relative precision at any such magnitude)
 //   O^T[D][16 rows] += V^T P^T
 // A wave whose sums come out beyond 2^115, infinite or NaN takes its rows
-// again one by one on the vector ALU (rows_alone): the max follows every key,
-// so probabilities stay at or below one and sums overflow only where the
-// values' own sums do, and a key that a row does not see adds nothing to it
-// whatever it holds (0 x infinity is NaN). Other calls pay half a maximum per
+// again on the vector ALU (rows_alone), but for rows whose probabilities sum
+// to NaN, which stay NaN in any order. There the max follows every key, so
+// probabilities stay at or below one and sums overflow only where the values'
+// own sums do, and a key that a row does not see adds nothing to it whatever
+// it holds (0 x infinity is NaN). Other calls pay half a maximum per
 // sum at the end of a piece: 8 ragged bf16 requests of 30..300 tokens 148.1 ->
 // 148.6 us, 12 fp32 ones of 20..130 tokens 65.1 -> 65.3 (a max that follows
 // every tile instead: 176 and 67.1).
@@ -374,19 +375,13 @@ __device__ __forceinline__ void store4<uint16_t>(uint16_t *out, float a, float b
   *(uint2 *)out = __builtin_bit_cast(uint2, v);
 }
 
-// max / sum over the 32 lanes of a half wave
-__device__ __forceinline__ float half_max(float x) {
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-  return x;
+// Element i of a 16-byte unit.
+template <typename T>
+__device__ __forceinline__ float element(const uint4 &u, int i) {
+  if constexpr (sizeof(T) == 4) return unit(u, i);
+  const uint32_t w = i < 2 ? u.x : i < 4 ? u.y : i < 6 ? u.z : u.w;
+  return __uint_as_float(i & 1 ? w & 0xffff0000u : w << 16);
 }
-__device__ __forceinline__ float half_sum(float x) {
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) x += __shfl_xor(x, o);
-  return x;
-}
-__device__ __forceinline__ float value_of(float x) { return x; }
-__device__ __forceinline__ float value_of(uint16_t x) { return __uint_as_float((uint32_t)x << 16); }
 
 // A workgroup's piece of work and a wave's part of it.
 struct Piece {
@@ -478,66 +473,120 @@ __device__ __forceinline__ OwnRows own_rows(const LinkParams &p, const ReqEntry 
   return own;
 }
 
-// A wave's rows over its tiles, one row at a time: (m, l, O) of row i to sm[i],
-// sl[i], so[i * stride + dim]. Lane l takes key l % 32 of
-// a tile and half of its head dims for the scores, value dims l and l + 64 for
-// the sums, which run over the keys the row sees and no others.
+// A wave's rows over its tiles, four at a time: (m, l, O) of row i to sm[i],
+// sl[i], so[i * stride + dim]. Lane l takes key l % 32 of a tile and half of its
+// head dims for the scores, value dims l and l + 64 for the sums, to which a
+// row's hidden keys add zero. Four rows share each 16-byte load of keys and
+// values: a call of 8 x 128 tokens over 8 x 512 rows, 32 heads on 8, all of
+// whose rows come here takes 2.5 ms (bf16, 64 wide; one row at a time with
+// element-wide loads 20, the vector-ALU kernel of the other shapes 1.6), where
+// the matrix instructions take 0.08.
 template <typename T, int D, bool kSmall>
 __device__ __forceinline__ void rows_alone(const LinkParams &p, const Piece &w, int rows,
                                            int lane, float *so, int stride, float *sm,
                                            float *sl) {
+  constexpr int kG = 4, E = Shape<T, D>::E, kUnits = D / 2 / E, kDims = D > 64 ? 2 : 1;
   const ReqEntry &R = w.R;
   const OwnRows own = own_rows<T, D>(p, R, w.cur.kvh);
-  constexpr int kDims = D > 64 ? 2 : 1;
-  const int key = lane & 31, half = lane >> 5;
+  const int key = lane & 31, half = (lane >> 5) * (D / 2);
   const int dim = D < 64 ? lane % D : lane;
+  const int n = min(rows, w.nrows - w.row0);
 #pragma unroll 1
-  for (int i = 0; i < min(rows, w.nrows - w.row0); ++i) {
-    const int row = w.row0 + i, qi = row / p.group;
-    const int qh = w.cur.kvh * p.group + row % p.group;
-    const int lim = qi + R.ls - R.lq;
-    const int dl = p.doc_lim ? p.doc_lim[R.q0 + qi] : kNoLimit;
-    const T *q = (const T *)p.q + ((int64_t)(R.q0 + qi) * p.n_q_heads + qh) * D + half * (D / 2);
-    float m = -INFINITY, l = 0.f, o[kDims];
+  for (int i0 = 0; i0 < n; i0 += kG) {
+    const T *q[kG];
+    int lim[kG], dl[kG];
+    float m[kG], l[kG], o[kG][kDims];
 #pragma unroll
-    for (int j = 0; j < kDims; ++j) o[j] = 0.f;
+    for (int g = 0; g < kG; ++g) {
+      const int row = w.row0 + min(i0 + g, n - 1), qi = row / p.group;
+      const int qh = w.cur.kvh * p.group + row % p.group;
+      q[g] = (const T *)p.q + ((int64_t)(R.q0 + qi) * p.n_q_heads + qh) * D + half;
+      lim[g] = qi + R.ls - R.lq;
+      dl[g] = p.doc_lim ? p.doc_lim[R.q0 + qi] : kNoLimit;
+      m[g] = -INFINITY;
+      l[g] = 0.f;
+#pragma unroll
+      for (int j = 0; j < kDims; ++j) o[g][j] = 0.f;
+    }
     Cursor cur = w.cur;
 #pragma unroll 1
     for (int t = w.t_begin; t < w.t_end; ++t) {
       const TileInfo x = tile_info<T, D>(cur, t);
-      const int last = x.own ? min(lim - x.j0, x.nvalid - 1) : min(dl - x.tok, x.nvalid) - 1;
-      if (last < 0) continue;
+      int last[kG], most = -1;
+#pragma unroll
+      for (int g = 0; g < kG; ++g) {
+        last[g] = x.own ? min(lim[g] - x.j0, x.nvalid - 1) : min(dl[g] - x.tok, x.nvalid) - 1;
+        most = max(most, last[g]);
+      }
+      if (most < 0) continue;
       const bool place = kSmall && x.own;
       const T *k = place ? (const T *)(own.k + min(x.j0 + key, own.last) * own.stride)
                          : (const T *)x.k + key * D;
-      k += half * (D / 2);
-      float s = 0.f;
-#pragma unroll 4
-      for (int e = 0; e < D / 2; ++e) s += value_of(q[e]) * value_of(k[e]);
-      s += __shfl_xor(s, 32);
-      s = key <= last ? s * p.scale_log2 : -INFINITY;
-      const float mnew = fmaxf(m, half_max(s));
-      const float base = mnew == -INFINITY ? 0.f : mnew;
-      const float pr = key <= last ? exp2f(s - base) : 0.f;
-      const float alpha = exp2f(m - base);
-      l = l * alpha + half_sum(pr);
-      m = mnew;
+      float s[kG], pr[kG];
+#pragma unroll
+      for (int g = 0; g < kG; ++g) s[g] = 0.f;
+#pragma unroll 2
+      for (int u = 0; u < kUnits; ++u) {
+        const uint4 ku = *(const uint4 *)(k + half + u * E);
+#pragma unroll
+        for (int g = 0; g < kG; ++g) {
+          const uint4 qu = *(const uint4 *)(q[g] + u * E);
+#pragma unroll
+          for (int e = 0; e < E; ++e) s[g] += element<T>(qu, e) * element<T>(ku, e);
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < kG; ++g) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(s[g]),
+                                                        __float_as_uint(s[g]), false, false);
+        s[g] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        s[g] = key <= last[g] ? s[g] * p.scale_log2 : -INFINITY;
+        const float mnew = fmaxf(m[g], wave_max(s[g]));
+        const float base = mnew == -INFINITY ? 0.f : mnew;
+        pr[g] = key <= last[g] ? exp2f(s[g] - base) : 0.f;
+        const float alpha = exp2f(m[g] - base);
+        l[g] = l[g] * alpha + 0.5f * wave_sum(pr[g]);     // both halves hold the keys
+        m[g] = mnew;
+#pragma unroll
+        for (int j = 0; j < kDims; ++j) o[g][j] *= alpha;
+      }
 #pragma unroll
       for (int j = 0; j < kDims; ++j) {
         const int e = dim + 64 * j;
-        const T *v = place ? (const T *)(own.v + x.j0 * own.stride) + e : (const T *)x.v + e * kT;
-        const int64_t step = place ? own.stride / (int)sizeof(T) : 1;
-        float a = o[j] * alpha;
-        for (int kk = 0; kk <= last; ++kk) a += __shfl(pr, kk) * value_of(v[kk * step]);
-        o[j] = a;
+        float v[kT];
+        if (place) {
+#pragma unroll
+          for (int kk = 0; kk < kT; ++kk) {
+            const T t1 = *((const T *)(own.v + min(x.j0 + kk, own.last) * own.stride) + e);
+            v[kk] = sizeof(T) == 4 ? (float)t1 : __uint_as_float((uint32_t)t1 << 16);
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < kT / E; ++u) {
+            const uint4 vu = *(const uint4 *)((const T *)x.v + e * kT + u * E);
+#pragma unroll
+            for (int b = 0; b < E; ++b) v[u * E + b] = element<T>(vu, b);
+          }
+        }
+#pragma unroll
+        for (int kk = 0; kk < kT; ++kk)
+#pragma unroll
+          for (int g = 0; g < kG; ++g) {
+            const float pk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(pr[g]), kk));
+            o[g][j] += pk * (kk <= last[g] ? v[kk] : 0.f);
+          }
       }
     }
-    if (D >= 64 || lane < D)
 #pragma unroll
-      for (int j = 0; j < kDims; ++j) so[i * stride + dim + 64 * j] = o[j];
-    if (lane == 0) {
-      sm[i] = partial_max(m, l);
-      sl[i] = l;
+    for (int g = 0; g < kG; ++g) {
+      if (i0 + g >= n) break;
+      if (D >= 64 || lane < D)
+#pragma unroll
+        for (int j = 0; j < kDims; ++j) so[(i0 + g) * stride + dim + 64 * j] = o[g][j];
+      if (lane == 0) {
+        sm[i0 + g] = partial_max(m[g], l[g]);
+        sl[i0 + g] = l[g];
+      }
     }
   }
 }
@@ -636,13 +685,18 @@ __device__ __forceinline__ void stream_body(const LinkParams &p, const_links lin
   float ltot[CB];
 #pragma unroll
   for (int c = 0; c < CB; ++c) ltot[c] = col_sum(st.l[c]);
-  float most = 0.f;            // (NaN stays in it)
+  // (NaN stays in the maxima; a row whose probabilities sum to NaN sees a NaN
+  // score, and no order of its sums changes what it gives)
+  float most = 0.f;
 #pragma unroll
-  for (int c = 0; c < CB; ++c)
+  for (int c = 0; c < CB; ++c) {
+    float mc = 0.f;
 #pragma unroll
     for (int b = 0; b < S::NB; ++b)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) most = __builtin_elementwise_maximum(most, fabsf(st.o[c][b][i]));
+      for (int i = 0; i < 4; ++i) mc = __builtin_elementwise_maximum(mc, fabsf(st.o[c][b][i]));
+    most = __builtin_elementwise_maximum(most, ltot[c] == ltot[c] ? mc : 0.f);
+  }
   const bool redo = __any(!(most <= kSafeSum));
   if (__builtin_expect(redo, 0)) {
     // the piece anew: kept over the loop above, it would cost it registers

@@ -212,6 +212,35 @@ __device__ __forceinline__ float log_sum(float m, float l) {
   return (float)(((double)m + e) * 0.69314718055994530942 + (double)logf(f));
 }
 
+// All-lane max / sum of a wave without LDS round trips: DPP moves inside
+// each 16-lane row (lane ^ 1, lane ^ 2 by quad permutes, then the mirrors
+// of each 8-lane half and of the row), then lanes l ^ 16 and l ^ 32 by the
+// permlane swaps. Every lane ends with the wave's result.
+template <int kCtrl>
+__device__ __forceinline__ float dpp_mov(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_max(float x) {
+  x = fmaxf(x, dpp_mov<0xB1>(x));    // quad_perm [1,0,3,2]
+  x = fmaxf(x, dpp_mov<0x4E>(x));    // quad_perm [2,3,0,1]
+  x = fmaxf(x, dpp_mov<0x141>(x));   // row_half_mirror
+  x = fmaxf(x, dpp_mov<0x140>(x));   // row_mirror
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float wave_sum(float x) {
+  x += dpp_mov<0xB1>(x);
+  x += dpp_mov<0x4E>(x);
+  x += dpp_mov<0x141>(x);
+  x += dpp_mov<0x140>(x);
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Epilogue stores of the matrix-core kernels. After the 32x32 value products
 // lane (n = l % 32, g = l / 32) holds row n, value dims 32 d + 8 j + 4 g ..+3
 // of a 32-row x 128-dim block, so a store straight from the registers covers
